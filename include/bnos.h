@@ -116,13 +116,26 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
                             int64_t *device_bytes);
 
 /*
+ * Kept entries (measurement).  A parent set that one of its own subsets beats
+ * by 60 nats, and two of them beat at all, is neither the best nor the second
+ * best of any order that can use it, and its term is below e^-60 of the largest
+ * one; the build lists every row's other entries apart, in descending score, and
+ * scoring and chains with the score bound on (bnos_table_score_bound) read those
+ * alone.  *entries = kept entries of all rows, 0 for a table that has none listed
+ * (a row of more than 65,536, or no memory for them within BNOS_MAX_DEVICE_BYTES);
+ * the streaming pass then serves it.
+ */
+bnos_status bnos_table_kept(bnos_table t, int64_t *entries);
+
+/*
  * Autotuner: times scoring launches of the B orders (DEVICE int32 [B][n]) for
  * every chunk length (powers of two dividing the row padding) and every
  * number of orders per block (1, 2, 4, 8, at most B), and, when K <= 4, the
  * gather pass (each block enumerates the consistent parent sets of a node
  * with a given top member and reads only their scores, at their ranks in the
  * row: Alg. 2's traversal on the dense table), `reps` launches each after one
- * warm-up, and keeps the fastest for this table and batch size (batch sizes
+ * warm-up (a table scored from its kept entries has one launch whatever the
+ * shape, which is timed once), and keeps the fastest for this table and batch size (batch sizes
  * are bucketed as 1, 2-3, 4-7, 8-15, 16+).  Outputs (may be NULL): the chosen
  * chunk steps and orders per block of the streaming pass, whether the gather
  * pass won (1) or not (0), and the mean time per launch in ms.  Both passes and
@@ -441,7 +454,9 @@ bnos_status bnos_table_timing(bnos_table t, int32_t enable);
  * skipping, and the sub-tiles of one full pass (n * padded entries / 64).
  * Such a launch also reads every tile summary of each pass (8 B per 256
  * entries) and, with one order per block, every sub-tile summary (8 B per 64
- * entries).  Synchronous.
+ * entries).  For a table with kept entries tiles_read counts the 64-entry tiles
+ * (768 B) of the kept rows that each order's scan reads, and the streaming pass's
+ * sub-tiles only while the score bound is off.  Synchronous.
  */
 bnos_status bnos_table_tile_skip(bnos_table t, int32_t enable);
 
@@ -461,7 +476,10 @@ bnos_status bnos_table_tile_skip(bnos_table t, int32_t enable);
  * the max score, the best parent sets and the second best are unchanged, and
  * the log-sum-exp is the same up to that bound (bitwise, in every case tested).
  * A block of several orders reads a tile if any of its orders needs it, and
- * each order folds only the tiles it needs.
+ * each order folds only the tiles it needs.  A table with kept entries
+ * (bnos_table_kept) is then served from those; with the bound off the streaming
+ * pass adds all the others, with the same results, bit for bit, in every case
+ * tested.
  */
 bnos_status bnos_table_score_bound(bnos_table t, int32_t enable);
 

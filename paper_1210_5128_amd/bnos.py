@@ -64,6 +64,7 @@ _SIGS = {
     "bnos_build_score_table": (i32, [P, i64, i32, P, i32, f64, P, P, P, P]),
     "bnos_table_free": (None, [P]),
     "bnos_table_info": (i32, [P, P, P, P, P]),
+    "bnos_table_kept": (i32, [P, P]),
     "bnos_table_export": (i32, [P, i32, P, P, i64]),
     "bnos_table_node_features": (i32, [P, P]),
     "bnos_counts": (i32, [P, i32, P, P, P, i64]),
@@ -156,6 +157,12 @@ class Table:
         _check(_lib.bnos_table_info(self._h, ctypes.byref(n), ctypes.byref(K), ctypes.byref(S),
                                     ctypes.byref(b)))
         return dict(n=n.value, K=K.value, entries_per_node=S.value, device_bytes=b.value)
+
+    def kept_entries(self) -> int:
+        """Kept entries of all rows (bnos_table_kept); 0 when the streaming pass serves the table."""
+        k = i64()
+        _check(_lib.bnos_table_kept(self._h, ctypes.byref(k)))
+        return k.value
 
     def export(self, node: int):
         S = self.info()["entries_per_node"]

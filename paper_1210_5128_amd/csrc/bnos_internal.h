@@ -47,6 +47,23 @@ constexpr int kBoundCands = 192;
 constexpr int kBoundSlots = 64 + kBoundCands;   // per node: slot s < 63 {slot s}, 63 the empty set, then the list
 constexpr float kBoundGap = 60.0f;
 
+// Kept entries.  A parent set m of a row can be left out of every order's
+// result at build when its own subsets already rule it out: an order that can
+// use m can use every subset of m, so if one of them scores kBoundGap nats
+// above m and two of them score above m, m is neither the best nor the second
+// best of any order that can use it and its term is below e^-kBoundGap of the
+// largest one -- the score bound's own criterion, from subsets instead of
+// candidates, once for all orders.  A build therefore lists each row's other
+// entries, the kept ones, apart: at n = 60, K = 4, N = 5,000 they are 1,200 to
+// 6,200 of 489,406 per row, depending on the data.  Rows of more than kKeptCap
+// kept entries stay with the streaming pass, which shares each streamed tile
+// between orders (a scan of 65,536 entries takes about what the streaming pass
+// spends on a pair of order and node at that size).
+constexpr int kKeptCap = 65536;
+constexpr int kKeptRun = 16384;           // sort keys of one block: 128 KB of LDS
+constexpr int kKeptTiles = 8;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
+constexpr int64_t kKeptSubsetCap = (int64_t)1 << 26;   // (node, subset) records of the build's pass over subsets
+
 // Partial-reduction record written by each scoring block (one per order).
 struct Partial {
     float m, s;          // running max and sum of exp(x - m) over consistent entries
@@ -83,6 +100,19 @@ struct TableT {
     uint64_t *d_cmask = nullptr;    // [n][kBoundSlots]: bound candidates (node-space mask; ~0 for none)
     float *d_cscore = nullptr;      // [n][kBoundSlots]: their scores (-inf for none)
     bool score_bound = true;        // one-order blocks skip tiles by the score bound
+
+    // kept entries (null when the table has none listed): row i's sit at i * kept_stride, in
+    // descending score, equal scores in ascending mask order, padded with (~0, -inf) to a
+    // multiple of 64 * kKeptTiles
+    uint64_t *d_kmask = nullptr;    // [n][kept_stride]
+    float *d_kscore = nullptr;      // [n][kept_stride]
+    int32_t *d_klen = nullptr;      // [n] kept entries, then [n] the nodes in descending order of them
+    float *d_kpm = nullptr;         // [n][n]: largest kept score of row i among the sets holding node m
+    uint8_t *d_kept = nullptr;      // [n * S_pad / 4]: bit e of byte g set when entry 4 g + e is kept
+    int64_t kept_stride = 0;
+    int64_t kept_total = 0;         // kept entries of all rows
+    int64_t kept_steps = 0;         // scan steps of all kept rows
+    int kept_steps_max = 0;         // and of the longest one
 
     // order-scoring workspace: per (order, node, chunk) partial reductions
     void *d_part = nullptr;
@@ -137,12 +167,20 @@ struct TableT {
     {
         int c = chunks_for(B) > n ? chunks_for(B) : n;
         if (chain_chunks_for(B) > c) c = chain_chunks_for(B);
+        c += d_kmask ? 1 : 0;                    // the kept entries' slot
         return (int64_t)B * n * c * (int64_t)sizeof(Partial);
     }
     // the partials, then (256-byte aligned) each order's score-bound cut per node
     int64_t cuts_offset_for(int B) const { return (partial_bytes_for(B) + 255) & ~(int64_t)255; }
     int64_t workspace_bytes_for(int B) const { return cuts_offset_for(B) + (int64_t)B * n * (int64_t)sizeof(float); }
     bool gather_for(int B) const { return K <= 4 && tuned_gather[bucket(B)] != 0; }
+    // the kept rows alone serve scoring and chains (with the score bound off, the streaming pass
+    // adds the other entries)
+    bool kept_rows() const { return d_kmask != nullptr && score_bound && tile_skip; }
+    int64_t kept_bytes() const
+    {
+        return (int64_t)n * kept_stride * 12 + (int64_t)n * 8 + (int64_t)n * n * 4 + (int64_t)n * (S_pad / 4);
+    }
 };
 
 constexpr uint32_t kMagic = 0xB0A5C0DEu;

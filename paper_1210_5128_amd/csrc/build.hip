@@ -48,7 +48,8 @@ int64_t TableT::device_bytes() const
     return (int64_t)n * S_pad * (int64_t)(sizeof(uint64_t) + sizeof(float)) + (int64_t)n * N_pad +
            (int64_t)n * (int64_t)(sizeof(int32_t) + n * sizeof(double) + 5 * sizeof(double)) + 64 * 8 * 8 +
            part_bytes + (int64_t)n * (S_pad / 256) * 8 + (int64_t)n * (S_pad / 64) * 8 +
-           (int64_t)n * (S_pad / 4) * 8 + (int64_t)n * (S_pad / 256) * 4 + (int64_t)n * kBoundSlots * 12;
+           (int64_t)n * (S_pad / 4) * 8 + (int64_t)n * (S_pad / 256) * 4 + (int64_t)n * kBoundSlots * 12 +
+           (d_kmask ? kept_bytes() : 0);
 }
 
 // ------------------------------------------------------------------ device helpers
@@ -735,6 +736,317 @@ __global__ __launch_bounds__(256) void k_anchor(const uint64_t *__restrict__ mas
     anchor[g] = (m == ~0ull) ? (1ull << (n - 1)) : ((m & low) | ((m >> 1) & ~low));
 }
 
+// ---- kept entries (see kKeptCap)
+//
+// Subset records: sub[node][r], r the rank of a set among those of at most K - 1
+// members, holds (the largest score among the set's subsets and itself, its own
+// score).  A set of j members takes its j immediate subsets' records, so the
+// passes run over j = 0, 1, ... K - 1.
+
+struct SubRec {
+    float top, own;
+};
+
+// This block's copy of nsets as 32-bit numbers (ranks are below 2^31: a row has fewer entries).
+__device__ __forceinline__ void load_nsets32(const int64_t *__restrict__ nsets, int *s_ns)
+{
+    for (int i = threadIdx.x; i < 512; i += blockDim.x) s_ns[i] = (int)nsets[i];
+    __syncthreads();
+}
+
+// The largest score among a set's proper subsets, and the second largest of its
+// immediate subsets' own scores and the empty set's (distinct entries for two or more
+// members), for slot-space mask m (at least one member).  The rank of m without member
+// t is the sum of the weights of the members above t at their own places and of those
+// below t one place up; places count down from `k`, the size limit of the ranks' space.
+__device__ __forceinline__ void subset_bounds(uint64_t m, int k, const int *__restrict__ s_ns,
+                                              const SubRec *__restrict__ sub, float empty, float &top, float &sec)
+{
+    int below = 0;                                 // members below the removed one, one place up
+    {
+        int t = 0;
+        for (uint64_t x = m; x; ++t) {
+            const int b = 63 - __builtin_clzll(x);
+            x &= ~(1ull << b);
+            if (t > 0) below += s_ns[b * 8 + (k - t + 1)];
+        }
+    }
+    int above = 0, t = 0;
+    top = -INFINITY;
+    float s1 = empty, s2 = -INFINITY;
+    for (uint64_t x = m; x; ++t) {
+        const int b = 63 - __builtin_clzll(x);
+        x &= ~(1ull << b);
+        if (t > 0) below -= s_ns[b * 8 + (k - t + 1)];
+        const SubRec r = sub[above + below];
+        top = fmaxf(top, r.top);
+        s2 = fmaxf(s2, fminf(s1, r.own));
+        s1 = fmaxf(s1, r.own);
+        if (k - t >= 0) above += s_ns[b * 8 + (k - t)];
+    }
+    sec = s2;
+}
+
+// The e-th mask over `bits` bits with at most k members, from the block's copy of nsets.
+__device__ __forceinline__ uint64_t unrank32(int e, int bits, int k, const int *__restrict__ s_ns)
+{
+    uint64_t m = 0;
+    for (int b = bits - 1; b >= 0 && k > 0; --b) {
+        const int c = s_ns[b * 8 + k];
+        if (e >= c) {
+            m |= 1ull << b;
+            e -= c;
+            --k;
+        }
+    }
+    return m;
+}
+
+// Records of one node's sets of at most K - 1 members, one block per node, the sets of j
+// members after those of j - 1.
+__global__ __launch_bounds__(1024) void k_keep_subsets(const float *__restrict__ scores,
+                                                       const int64_t *__restrict__ nsets, int n, int K,
+                                                       int64_t S_pad, int64_t sub_row, SubRec *sub)
+{
+    __shared__ int s_ns[512];
+    load_nsets32(nsets, s_ns);
+    const int node = blockIdx.x;
+    const float *row = scores + (int64_t)node * S_pad;
+    SubRec *out = sub + (int64_t)node * sub_row;
+    for (int j = 0; j < K; ++j) {
+        const int sets = s_ns[(n - 1) * 8 + j];                      // of at most j members
+        for (int g = threadIdx.x; g < sets; g += 1024) {
+            const uint64_t m = unrank32(g, n - 1, j, s_ns);
+            if (__popcll(m) != j) continue;
+            int full = 0, mine = 0, t = 0;         // ranks in the row and among the sets of at most K - 1
+            for (uint64_t x = m; x; ++t) {
+                const int b = 63 - __builtin_clzll(x);
+                x &= ~(1ull << b);
+                full += s_ns[b * 8 + (K - t)];
+                mine += s_ns[b * 8 + (K - 1 - t)];
+            }
+            const float own = row[full];
+            float top = own;
+            if (j > 0) {
+                float below, sec;
+                subset_bounds(m, K - 1, s_ns, out, row[0], below, sec);
+                top = fmaxf(top, below);
+            }
+            out[mine] = {top, own};
+        }
+        __syncthreads();
+    }
+}
+
+// b - kBoundGap, or -inf where FP32 cannot hold that gap below b.
+__device__ __forceinline__ float keep_gap_below(float b)
+{
+    const float g = b - kBoundGap;
+    return (b - g >= kBoundGap) ? g : -INFINITY;
+}
+
+// One thread per 4-entry group of a row: which of its entries are kept (the byte of
+// `kept`), and a sort key for each, appended to the node's list (in any order: the sort
+// fixes it).  A key's high half falls as the score rises, its low half is the place in
+// the row, so ascending keys list descending scores and, among equal ones, ascending masks.
+// The counter goes on past the capacity; the host then lists no kept rows.
+__global__ __launch_bounds__(256) void k_keep_entries(const uint64_t *__restrict__ masks,
+                                                      const float *__restrict__ scores,
+                                                      const int64_t *__restrict__ nsets, int n, int K, int64_t S,
+                                                      int64_t S_pad, int64_t sub_row, const SubRec *__restrict__ sub,
+                                                      int64_t stride, uint8_t *__restrict__ kept,
+                                                      uint64_t *__restrict__ keys, int32_t *__restrict__ cnt)
+{
+    __shared__ int s_ns[512];
+    load_nsets32(nsets, s_ns);
+    const int node = blockIdx.y;
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;       // the row's 4-entry group (S_pad / 4 is a multiple of 256)
+    const int lane = threadIdx.x & 63;
+    const int64_t row = (int64_t)node * S_pad;
+    const SubRec *srow = sub + (int64_t)node * sub_row;
+    const float empty = scores[row];
+    uint32_t bits = 0u;
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int64_t at = 4 * q + e;
+        x[e] = scores[row + at];
+        if (at >= S) continue;
+        const uint64_t nm = masks[row + at];
+        const uint64_t low = (1ull << node) - 1ull;
+        const uint64_t m = (nm & low) | ((nm >> 1) & ~low);          // slot space
+        bool keep = true;
+        if (__popcll(m) >= 2) {
+            float top, sec;
+            subset_bounds(m, K - 1, s_ns, srow, empty, top, sec);
+            keep = !(x[e] < keep_gap_below(top) && x[e] < sec);
+        }
+        bits |= keep ? (1u << e) : 0u;
+    }
+    kept[row / 4 + q] = (uint8_t)bits;
+    // places of this wavefront's kept entries: one counter update per wavefront
+    int mine = __popc(bits), before = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(before, off, 64);
+        if (lane >= off) before += o;
+    }
+    const int total = __shfl(before, 63, 64);
+    if (total == 0) return;                                          // uniform per wavefront
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&cnt[node], total);
+    base = __shfl(base, 0, 64) + before - mine;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if ((bits >> e) & 1u) {
+            if (base < stride) {
+                const uint32_t u = __float_as_uint(x[e] + 0.0f);     // -0 sorts as +0
+                const uint32_t up = (u >> 31) ? ~u : (u | 0x80000000u);   // rises with the score
+                keys[(int64_t)node * stride + base] = ((uint64_t)~up << 32) | (uint32_t)(4 * q + e);
+            }
+            ++base;
+        }
+}
+
+// One node's kept row from its sorted runs of keys (one block): each key's place is its place
+// in its own run plus the smaller keys of the other runs (keys are distinct); the entries after
+// the last one, up to a whole step of a scan, are padding.  With it the largest kept score among
+// the sets holding each node (the first place that holds it), the row's score-bound candidates
+// (as k_bound_cands lists them, but the top kept entries), and the row's place among the rows
+// in descending length, after the lengths.
+struct KeepOut {
+    uint64_t *kmask;
+    float *kscore, *kpm;
+    int32_t *klen;
+    uint64_t *cmask;
+    float *cscore;
+    int64_t stride;
+};
+
+__device__ __forceinline__ void keep_finish(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
+                                            const uint64_t *keys, const KeepOut &O)
+{
+    __shared__ int s_first[64];
+    const int node = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int len = O.klen[node];
+    uint64_t *cm = O.cmask + (int64_t)node * kBoundSlots, *krow = O.kmask + (int64_t)node * O.stride;
+    float *cs = O.cscore + (int64_t)node * kBoundSlots, *xrow = O.kscore + (int64_t)node * O.stride;
+    if (tid < 64) {
+        s_first[tid] = 0x7fffffff;
+        const int o = tid < n ? O.klen[tid] : -1;
+        const int before = __popcll(__ballot(o > len || (o == len && tid < node)));
+        if (tid == 0) O.klen[n + before] = node;
+    }
+    if (tid < kBoundSlots) {
+        cm[tid] = ~0ull;
+        cs[tid] = -INFINITY;
+    }
+    __syncthreads();
+    constexpr int kStep = 64 * kKeptTiles;
+    const int padded = (len + kStep - 1) / kStep * kStep;            // at most stride
+    for (int i = tid; i < padded; i += 1024) {
+        int place = i;
+        uint64_t m = ~0ull;
+        float x = -INFINITY;
+        if (i < len) {
+            const uint64_t key = keys[i];
+            const int own = i / kKeptRun;
+            place = i - own * kKeptRun;
+            for (int r = 0; r * kKeptRun < len; ++r) {
+                if (r == own) continue;
+                int lo = r * kKeptRun, hi = lo + kKeptRun < len ? lo + kKeptRun : len;
+                const int lo0 = lo;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (keys[mid] < key) lo = mid + 1;
+                    else hi = mid;
+                }
+                place += lo - lo0;
+            }
+            const int64_t at = (int64_t)node * S_pad + (uint32_t)key;
+            m = masks[at];
+            x = scores[at];
+            for (uint64_t r = m; r; r &= r - 1) {
+                const int b = __builtin_ctzll(r);
+                if (place < s_first[b]) atomicMin(&s_first[b], place);
+            }
+            if (__popcll(m) < 2) {                                   // the empty set and the singletons
+                const int b = m ? __builtin_ctzll(m) : 64;
+                const int to = m == 0ull ? 63 : (b < node ? b : b - 1);
+                cm[to] = m;
+                cs[to] = x;
+            }
+        }
+        krow[place] = m;
+        xrow[place] = x;
+    }
+    __syncthreads();
+    if (tid < n) {
+        const int f = s_first[tid];
+        O.kpm[(int64_t)node * n + tid] = f < len ? xrow[f] : -INFINITY;
+    }
+    if (tid < 64) {                                                  // one wavefront
+        int at = 64;
+        for (int i0 = 0; i0 < len && at < kBoundSlots; i0 += 64) {   // uniform
+            const int i = i0 + tid;
+            const uint64_t m = i < len ? krow[i] : ~0ull;
+            const float x = i < len ? xrow[i] : -INFINITY;
+            const bool list = i < len && __popcll(m) >= 2;
+            const uint64_t bal = __ballot(list);
+            const int to = at + __popcll(bal & ((1ull << tid) - 1ull));
+            if (list && to < kBoundSlots) {
+                cm[to] = m;
+                cs[to] = x;
+            }
+            at += __popcll(bal);
+        }
+    }
+}
+
+// Sort of one run of a node's keys (bitonic, in LDS); with a single run per node, the kept row
+// too.  Nothing is done where the list overflowed.
+__global__ __launch_bounds__(1024) void k_keep_sort(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
+                                                    uint64_t *keys, KeepOut O)
+{
+    __shared__ uint64_t s_key[kKeptRun];
+    const int node = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int all = O.klen[node], first = blockIdx.y * kKeptRun;
+    if (all > O.stride || first >= all) return;                      // uniform
+    const int len = all - first < kKeptRun ? all - first : kKeptRun;
+    int P = 64;
+    while (P < len) P <<= 1;                                         // P <= kKeptRun
+    uint64_t *run = keys + (int64_t)node * O.stride + first;
+    for (int i = tid; i < P; i += 1024) s_key[i] = i < len ? run[i] : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j >= 1; j >>= 1) {
+            for (int i = tid; i < P / 2; i += 1024) {
+                const int a = 2 * i - (i & (j - 1)), b = a + j;       // the i-th pair at distance j
+                const uint64_t x = s_key[a], y = s_key[b];
+                const bool up = (a & k) == 0;
+                if ((x > y) == up) {
+                    s_key[a] = y;
+                    s_key[b] = x;
+                }
+            }
+            __syncthreads();
+        }
+    if (gridDim.y == 1) {
+        keep_finish(masks, scores, n, S_pad, s_key, O);
+        return;
+    }
+    for (int i = tid; i < len; i += 1024) run[i] = s_key[i];
+}
+
+__global__ __launch_bounds__(1024) void k_keep_finish(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
+                                                      const uint64_t *keys, KeepOut O)
+{
+    if (O.klen[blockIdx.x] > O.stride) return;                       // uniform
+    keep_finish(masks, scores, n, S_pad, keys + (int64_t)blockIdx.x * O.stride, O);
+}
+
 // Counts for explicit (node, parent mask) queries, with the build's counting code.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_counts(
@@ -846,6 +1158,78 @@ static int cells_cap_for(int max_cells)
     return c;
 }
 
+static void free_kept(TableT *t)
+{
+    hipFree(t->d_kmask);                           // one allocation holds all of them
+    t->d_kmask = nullptr;
+    t->d_kscore = nullptr;
+    t->d_klen = nullptr;
+    t->d_kpm = nullptr;
+    t->d_kept = nullptr;
+}
+
+// Lists the table's kept rows after its rows are built (waits for the stream).  A table
+// without them (a row of more than kKeptCap kept entries, a memory cap they would pass, no
+// memory for them) is served by the streaming pass, so nothing here fails the build but a
+// device error.
+static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
+{
+    const int n = t->n, K = t->K;
+    const int64_t sub_row = K >= 1 ? sets_upto(n - 1, K - 1) : 1;
+    if (sub_row * n > kKeptSubsetCap) return hipSuccess;
+    constexpr int64_t kStep = 64 * kKeptTiles;
+    t->kept_stride = std::min<int64_t>((t->S + kStep - 1) / kStep * kStep, kKeptCap);
+    if (max_bytes > 0 && t->device_bytes() + t->kept_bytes() > max_bytes) return hipSuccess;
+    // one allocation for the table (kept_bytes() of it) and one for the build's passes
+    const int64_t cells = (int64_t)n * t->kept_stride;
+    char *own = nullptr, *tmp = nullptr;
+    if (hipMalloc((void **)&own, (size_t)t->kept_bytes()) != hipSuccess ||
+        hipMalloc((void **)&tmp, (size_t)(cells * 8 + sub_row * n * (int64_t)sizeof(SubRec))) != hipSuccess) {
+        (void)hipGetLastError();
+        hipFree(own);
+        return hipSuccess;
+    }
+    t->d_kmask = reinterpret_cast<uint64_t *>(own);
+    t->d_kscore = reinterpret_cast<float *>(own + cells * 8);
+    t->d_kpm = reinterpret_cast<float *>(own + cells * 12);
+    t->d_klen = reinterpret_cast<int32_t *>(own + cells * 12 + (int64_t)n * n * 4);
+    t->d_kept = reinterpret_cast<uint8_t *>(own + cells * 12 + (int64_t)n * n * 4 + (int64_t)n * 8);
+    uint64_t *keys = reinterpret_cast<uint64_t *>(tmp);
+    SubRec *sub = reinterpret_cast<SubRec *>(tmp + cells * 8);
+    std::vector<int32_t> len(n);
+    hipError_t e = hipMemsetAsync(t->d_klen, 0, sizeof(int32_t) * n, st);
+    if (e == hipSuccess) {
+        const KeepOut O = {t->d_kmask, t->d_kscore, t->d_kpm, t->d_klen, t->d_cmask, t->d_cscore, t->kept_stride};
+        const unsigned runs = (unsigned)((t->kept_stride + kKeptRun - 1) / kKeptRun);
+        hipLaunchKernelGGL(k_keep_subsets, dim3(n), dim3(1024), 0, st, t->d_scores, t->d_nsets, n, K, t->S_pad,
+                           sub_row, sub);
+        hipLaunchKernelGGL(k_keep_entries, dim3((unsigned)(t->S_pad / 1024), (unsigned)n), dim3(256), 0, st,
+                           t->d_masks, t->d_scores, t->d_nsets, n, K, t->S, t->S_pad, sub_row, sub, t->kept_stride,
+                           t->d_kept, keys, t->d_klen);
+        hipLaunchKernelGGL(k_keep_sort, dim3(n, runs), dim3(1024), 0, st, t->d_masks, t->d_scores, n, t->S_pad, keys, O);
+        if (runs > 1)
+            hipLaunchKernelGGL(k_keep_finish, dim3(n), dim3(1024), 0, st, t->d_masks, t->d_scores, n, t->S_pad, keys,
+                               O);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(len.data(), t->d_klen, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    hipFree(tmp);
+    if (e != hipSuccess) return e;
+    bool fits = true;
+    for (int i = 0; i < n; ++i) {
+        fits = fits && len[i] <= t->kept_stride;
+        const int steps = (int)((len[i] + kStep - 1) / kStep);
+        t->kept_total += len[i];
+        t->kept_steps += steps;
+        t->kept_steps_max = std::max(t->kept_steps_max, steps);
+    }
+    if (!fits) {
+        free_kept(t);
+    }
+    return hipSuccess;
+}
+
 static void free_device(TableT *t)
 {
     hipFree(t->d_data);
@@ -862,6 +1246,7 @@ static void free_device(TableT *t)
     hipFree(t->d_cmask);
     hipFree(t->d_cscore);
     hipFree(t->d_part);
+    free_kept(t);
     for (auto e : t->ev_start) hipEventDestroy(e);
     for (auto e : t->ev_stop) hipEventDestroy(e);
 }
@@ -1133,13 +1518,17 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
                            t->d_scores, tiles, row_tiles, row_tiles / (4 * (int64_t)t->pad_steps), t->pad_steps,
                            t->d_tand, t->d_tsub, t->d_tmax);
         CK(hipGetLastError());
-        hipLaunchKernelGGL(k_bound_cands, dim3(n), dim3(1024), 0, st, t->d_masks, t->d_scores, n, K, t->S,
-                           t->S_pad, t->d_cmask, t->d_cscore);
-        CK(hipGetLastError());
         const int64_t groups = (int64_t)n * (t->S_pad / 4);
         hipLaunchKernelGGL(k_anchor, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, t->d_masks, n,
                            t->S_pad, t->d_anchor);
         CK(hipGetLastError());
+        const char *cap_s = std::getenv("BNOS_MAX_DEVICE_BYTES");
+        CK(list_kept(t, st, cap_s ? std::atoll(cap_s) : 0));
+        if (!t->d_kmask) {                       // else the kept rows gave the candidates
+            hipLaunchKernelGGL(k_bound_cands, dim3(n), dim3(1024), 0, st, t->d_masks, t->d_scores, n, K, t->S,
+                               t->S_pad, t->d_cmask, t->d_cscore);
+            CK(hipGetLastError());
+        }
     }
     CK(hipStreamSynchronize(st));
     hipFree(d_rows);
@@ -1173,6 +1562,15 @@ extern "C" bnos_status bnos_table_info(bnos_table h, int32_t *n, int32_t *K, int
     if (K) *K = t->K;
     if (S) *S = t->S;
     if (bytes) *bytes = t->device_bytes();
+    return BNOS_OK;
+}
+
+extern "C" bnos_status bnos_table_kept(bnos_table h, int64_t *entries)
+{
+    TableT *t = reinterpret_cast<TableT *>(h);
+    if (!handle_live(t)) { set_error("invalid table handle"); return BNOS_E_STATE; }
+    if (!entries) { set_error("NULL argument"); return BNOS_E_INVALID; }
+    *entries = t->d_kmask ? t->kept_total : 0;
     return BNOS_OK;
 }
 

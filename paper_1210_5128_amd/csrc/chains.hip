@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int chunks = V.chunks;
+    const int slots = V.slots;
     const int64_t row = (int64_t)c * n;
     const uint64_t wm = H.wmask[c];
     const bool learned = H.proposal == 1;
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
     const int cnt = s_cnt;
     {
         // lane j of the merging waves takes window node s_nodes[j]
-        const Acc r = merge_nodes(V.part + (int64_t)c * chunks * n, n, chunks, lane < cnt ? s_nodes[lane] : -1,
+        const Acc r = merge_nodes(V.part + (int64_t)c * slots * n, n, slots, lane < cnt ? s_nodes[lane] : -1,
                                   s_merge);
         if (wave == 0 && lane < cnt) {
             const int i = s_nodes[lane];
@@ -752,6 +752,13 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         V.cscore = bound ? t->d_cscore : nullptr;
         V.cuts = H.cuts;               // computed by k_worklist before each scoring launch
         V.K = t->K;
+        V.kmask = nullptr;             // the sweep's blocks stream the whole rows
+        V.kscore = nullptr;
+        V.klen = nullptr;
+        V.kept_stride = 0;
+        V.kept = nullptr;
+        V.slots = V.chunks;
+        V.slot0 = 0;
         blk_base[k + 1] = blk_base[k] + (int64_t)n * V.chunks;
         chain_base[k + 1] = chain_base[k] + C;
         node_base[k + 1] = node_base[k] + n;

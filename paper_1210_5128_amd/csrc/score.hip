@@ -46,6 +46,118 @@ __global__ __launch_bounds__(kScoreThreads) void k_bound_pre(ScoreArgs A)
     if (lane == 0) A.cut_ws[g] = c;
 }
 
+// The positions of an order's nodes (64: not listed), for the predecessor sets of all of
+// them, and whether the order is a permutation; by one wavefront, into LDS.
+__device__ __forceinline__ void order_positions(const int32_t *__restrict__ ord, int n, int lane, uint8_t *s_pos,
+                                                int *s_valid)
+{
+    const int v = lane < n ? ord[lane] : -1;
+    s_pos[lane] = 64;
+    const bool valid = order_valid(v, n, lane);
+    __builtin_amdgcn_wave_barrier();                    // the same wavefront's LDS writes stay in order
+    if (v >= 0 && v < n) s_pos[v] = (uint8_t)lane;
+    if (lane == 0) *s_valid = valid ? 1 : 0;
+}
+
+// Scoring from the kept rows, one block per order: its wavefronts take the nodes in
+// descending length of their kept rows (kept_scan), then the first wavefront forms the
+// nodes' log-sum-exps and the order's sums as k_merge does: one launch, no partials,
+// for tables of short kept rows (the rule is at launch_kept).  Bound by the latency of
+// its few dependent steps; the call, 7.4 us, by the host's launch.
+constexpr int kKeptWaves = 16;
+__global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
+{
+    __shared__ uint8_t s_pos[64];
+    __shared__ int s_valid;
+    __shared__ float s_m[64], s_s[64], s_sec[64];
+    __shared__ uint64_t s_bm[64];
+    const int b = blockIdx.x;
+    const int n = A.n;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int by_len = lane < n ? A.klen[n + lane] : 0, lens = lane < n ? A.klen[lane] : 0;
+    if (wave == 0) order_positions(A.orders + (int64_t)b * n, n, lane, s_pos, &s_valid);
+    __syncthreads();
+    const int pos = s_pos[lane];
+    for (int k = wave; k < n; k += blockDim.x >> 6) {
+        const int node = __builtin_amdgcn_readlane(by_len, k), len = __builtin_amdgcn_readlane(lens, node);
+        const int mine = __builtin_amdgcn_readlane(pos, node);
+        const uint64_t pred = __ballot(lane < n && pos < mine);
+        const int64_t row = (int64_t)node * A.kept_stride;
+        const KeptAcc a = kept_scan<true>(A.kmask + row, A.kscore + row, len, ~pred, lane);
+        if (lane == 0) {
+            s_m[node] = a.best;
+            s_s[node] = kept_sum(a);
+            s_sec[node] = a.sec;
+            s_bm[node] = a.bm;
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const bool valid = s_valid != 0;
+    double li = 0.0, mi = 0.0;
+    if (lane < n) {
+        li = (double)s_m[lane] + log((double)s_s[lane]);
+        mi = (double)s_m[lane];
+        const int64_t o = (int64_t)b * n + lane;
+        A.best[o] = valid ? s_bm[lane] : 0ull;
+        if (A.node_lse) A.node_lse[o] = valid ? li : NAN;
+        if (A.node_second) A.node_second[o] = valid ? s_sec[lane] : NAN;
+    }
+    const double l = wave_sum_f64(li, lane), m = wave_sum_f64(mi, lane);
+    if (lane == 0) {
+        A.lse[b] = valid ? l : NAN;
+        A.maxs[b] = valid ? m : NAN;
+    }
+}
+
+// The kept row's partial of every (order, node), to slot 0: W wavefronts per pair, the nodes with
+// the longest rows first.  What bounds it: the dependent steps of the longest row for few
+// orders, the vector instructions of the fold for many.  At n = 60, N = 5,000 one order takes
+// 10.4 us per call with its merge (the streaming pass: 88 us in its default shape) and 256
+// orders 22 to 38 us (755 us streamed).  STOP: down to the gap; else the whole row, for launches whose
+// streaming pass adds the other entries.
+template <int W, bool STOP>
+__global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
+{
+    __shared__ KeptLds<W> L;
+    const int64_t g = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = A.n;
+    const int k = (int)(g / A.B), b = (int)(g - (int64_t)k * A.B);
+    const int node = A.klen[n + k];
+    if (threadIdx.x == 0) kept_shared_reset(L);
+    bool valid;
+    const uint64_t np = ~wave_pred(A.orders + (int64_t)b * n, n, node, lane, valid);
+    const int64_t row = (int64_t)node * A.kept_stride;
+    KeptAcc a;
+    if (W == 1) {
+        a = kept_scan<STOP>(A.kmask + row, A.kscore + row, A.klen[node], np, lane);
+    } else {
+        __syncthreads();
+        a = kept_scan_shared<W, STOP>(A.kmask + row, A.kscore + row, A.klen[node], np, lane, wave, L);
+    }
+    if (threadIdx.x == 0) kept_store(view_of(A), b, node, a);
+}
+
+// Measurement only: the 64-entry tiles of the kept rows k_score_kept (stop) or
+// k_kept_partials reads for these orders, one count per (order, node).
+__global__ __launch_bounds__(kScoreThreads) void k_count_kept(ScoreArgs A, int stop, unsigned *__restrict__ counts)
+{
+    const int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int n = A.n;
+    if (g >= (int64_t)A.B * n) return;
+    const int b = (int)(g / n), node = (int)(g - (int64_t)b * n);
+    bool valid;
+    const uint64_t np = ~wave_pred(A.orders + (int64_t)b * n, n, node, lane, valid);
+    const int64_t row = (int64_t)node * A.kept_stride;
+    int steps = (A.klen[node] + 64 * kKeptTiles - 1) / (64 * kKeptTiles);
+    if (stop) kept_scan<true>(A.kmask + row, A.kscore + row, A.klen[node], np, lane, &steps);
+    if (lane == 0) counts[g] = (unsigned)(steps * kKeptTiles);
+}
+
 // Gather pass: see the comment at kGatherMaxK (score_device.h).
 __global__ __launch_bounds__(kScoreThreads) void k_gather(ScoreArgs A, const int64_t *__restrict__ nsets, int K)
 {
@@ -161,17 +273,16 @@ int pick_bt(const TableT *t, int B)
     return bt;
 }
 
-// Scoring workspace for up to `B` orders: the chunk partials.
-bnos_status ensure_workspace(TableT *t, int B)
+// Scoring workspace of at least `need` bytes (`want` when it has to be allocated).
+static bnos_status ensure_bytes(TableT *t, int64_t need, int64_t want)
 {
-    const int64_t need = t->workspace_bytes_for(B);
     if (t->part_bytes >= need) return BNOS_OK;
     // A launch still in flight may use the old buffer.
     BNOS_HIP(hipDeviceSynchronize());
     BNOS_HIP(hipFree(t->d_part));
     t->d_part = nullptr;
     t->part_bytes = 0;
-    const int64_t want = need > t->workspace_bytes_for(64) ? need : t->workspace_bytes_for(64);
+    if (want < need) want = need;
     hipError_t e = hipMalloc(&t->d_part, (size_t)want);
     if (e != hipSuccess) {
         set_error(std::string("hipMalloc scoring workspace: ") + hipGetErrorString(e));
@@ -180,6 +291,19 @@ bnos_status ensure_workspace(TableT *t, int B)
     }
     t->part_bytes = want;
     return BNOS_OK;
+}
+
+// For up to `B` orders: the chunk partials.
+bnos_status ensure_workspace(TableT *t, int B)
+{
+    return ensure_bytes(t, t->workspace_bytes_for(B), t->workspace_bytes_for(64));
+}
+
+// For up to `B` orders scored from the kept rows: one partial per (order, node).
+static bnos_status ensure_kept_workspace(TableT *t, int B)
+{
+    const int64_t per = (int64_t)t->n * (int64_t)sizeof(Partial);
+    return ensure_bytes(t, B * per, 64 * per);
 }
 
 // Adds the oldest timed launch in the ring to the totals and frees its slot.
@@ -260,6 +384,13 @@ ScoreArgs score_args(const TableT *t, const int32_t *orders, int B, double *lse,
     A.cut_ws = t->d_part ? reinterpret_cast<float *>(static_cast<char *>(t->d_part) + t->cuts_offset_for(B))
                          : nullptr;
     A.K = t->K;
+    A.kmask = t->d_kmask;
+    A.kscore = t->d_kscore;
+    A.klen = t->d_klen;
+    A.kept_stride = t->kept_stride;
+    A.kept = t->d_kmask ? t->d_kept : nullptr;
+    A.slot0 = A.kept ? 1 : 0;
+    A.slots = A.chunks + A.slot0;
     return A;
 }
 
@@ -281,6 +412,13 @@ static void launch_bt(const ScoreArgs &A, int nblocks_x, hipStream_t st, hipEven
     // a single slot doubles the mask); with tile skipping a wavefront folds few tiles and waits
     // on their loads, so six are kept in flight, while the full scan streams the row and keeps
     // three (fewer registers, more wavefronts resident)
+    if (A.kept) {                    // the score bound is off: every entry but the kept ones
+        if (BT == 1 && A.anchor && ((A.K >= 2 && A.n <= 63) || (A.K == 1 && A.n <= 61)))
+            launch_one<k_score<1, true, true, 3, true>>(grid, st, e0, e1, A);
+        else if (BT == 1 && A.anchor) launch_one<k_score<1, true, false, 3, true>>(grid, st, e0, e1, A);
+        else launch_one<k_score<BT, false, false, 0, true>>(grid, st, e0, e1, A);
+        return;
+    }
     const bool deep = A.tand != nullptr;
     if (BT == 1 && A.anchor && ((A.K >= 2 && A.n <= 63) || (A.K == 1 && A.n <= 61))) {
         if (deep) launch_one<k_score<1, true, true, 6>>(grid, st, e0, e1, A);
@@ -308,6 +446,9 @@ bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt,
     }
     const int nbx = t->n * A.chunks;
     ScoreArgs A2 = A;
+    if (A.kept) {
+        hipLaunchKernelGGL((k_kept_partials<1, false>), dim3((unsigned)((int64_t)A.B * A.n)), dim3(64), 0, st, A);
+    }
     if (bt > 1 && A.tmax && A.tand && A.cut_ws) {
         // every (order, node) cut once, before the blocks that stream the node's row
         const int64_t pairs = (int64_t)A.B * A.n;
@@ -329,6 +470,7 @@ bnos_status launch_gather(TableT *t, ScoreArgs &A, hipStream_t st, bool allow_ti
 {
     bnos_status s;
     A.chunks = t->n;
+    A.slots = t->n;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (allow_timing && t->timing && t->timing_seen++ % t->timing_every == 0) {
         if ((s = next_events(t, e0, e1, 0)) != BNOS_OK) return s;
@@ -348,12 +490,53 @@ bnos_status launch_merge(const ScoreArgs &A, hipStream_t st)
     return BNOS_OK;
 }
 
+template <int W>
+static void launch_partials(const ScoreArgs &A, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+{
+    const dim3 grid((unsigned)((int64_t)A.B * A.n));
+    if (e0) hipExtLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, e0, e1, 0, A);
+    else hipLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, A);
+}
+
+// Scoring from the kept rows; timed when enabled (each order makes its own pass).
+bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timing)
+{
+    bnos_status s;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (allow_timing && t->timing && t->timing_seen++ % t->timing_every == 0) {
+        if ((s = next_events(t, e0, e1, A.B)) != BNOS_OK) return s;
+    }
+    if (t->kept_steps <= kKeptWaves * 4) {
+        // short rows: four steps per wavefront of one block take less than a second launch would
+        // (8-20 nodes, one step per row: 7.4 us per call against 9.8 at up to 256 orders)
+        const dim3 grid((unsigned)A.B), block(64 * (unsigned)(t->n < kKeptWaves ? t->n : kKeptWaves));
+        if (e0) hipExtLaunchKernelGGL(k_score_kept, grid, block, 0, st, e0, e1, 0, A);
+        else hipLaunchKernelGGL(k_score_kept, grid, block, 0, st, A);
+        BNOS_HIP(hipGetLastError());
+        return BNOS_OK;
+    }
+    // W wavefronts per (order, node): a longest row of M steps takes M / W of them one after the
+    // other (0.33 us each), and every wavefront of a pair costs the chip 0.7 ns, so with P pairs
+    // W^2 = 470 M / P is the least of the sum; the power of two nearest.  (60 nodes, M = 25: one
+    // order 12.6 / 11.6 / 10.4 / 10.7 us for W = 1 / 2 / 4 / 8, 64 orders 19.7 / 20.7 / 24.8 / 36.8.)
+    const double w2 = 470.0 * t->kept_steps_max / ((double)A.B * t->n);
+    A.slots = 1;
+    if (w2 < 2.0) launch_partials<1>(A, st, e0, e1);
+    else if (w2 < 8.0) launch_partials<2>(A, st, e0, e1);
+    else if (w2 < 32.0) launch_partials<4>(A, st, e0, e1);
+    else launch_partials<8>(A, st, e0, e1);
+    BNOS_HIP(hipGetLastError());
+    return launch_merge(A, st);
+}
+
 static bnos_status score_impl(TableT *t, const int32_t *orders, int B, double *lse, double *maxs,
                               uint64_t *best, double *node_lse, float *node_second, hipStream_t st)
 {
-    bnos_status s = ensure_workspace(t, B);
+    const bool kept = t->kept_rows() && !t->gather_for(B);
+    bnos_status s = kept ? ensure_kept_workspace(t, B) : ensure_workspace(t, B);
     if (s != BNOS_OK) return s;
     ScoreArgs A = score_args(t, orders, B, lse, maxs, best, node_lse, node_second);
+    if (kept) return launch_kept(t, A, st);
     if (t->gather_for(B)) s = launch_gather(t, A, st);
     else s = launch_stream(t, A, st, 0);
     if (s != BNOS_OK) return s;
@@ -457,17 +640,29 @@ extern "C" bnos_status bnos_table_count_tiles(bnos_table h, const int32_t *order
     A.tand = t->d_tand;
     const int bt = pick_bt(t, B);
     const int nbx = t->n * A.chunks;
-    const int64_t blocks = (int64_t)nbx * ((B + bt - 1) / bt);
+    // with kept rows: their 64-entry steps, one count per (order, node); with the bound off the
+    // streaming pass's sub-tiles too
+    const int64_t pairs = t->d_kmask ? (int64_t)B * t->n : 0;
+    const bool bound = t->score_bound && t->tile_skip;
+    const bool stream = !t->d_kmask || !bound;
+    const int64_t blocks = pairs + (stream ? (int64_t)nbx * ((B + bt - 1) / bt) : 0);
     unsigned *d = nullptr;
     BNOS_HIP(hipMalloc((void **)&d, sizeof(unsigned) * blocks));
-    if (bt == 8) launch_count<8>(A, nbx, d);
+    unsigned *const d_all = d;
+    if (pairs) {
+        hipLaunchKernelGGL(k_count_kept, dim3((unsigned)((pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64))),
+                           dim3(kScoreThreads), 0, 0, A, bound ? 1 : 0, d);
+        d += pairs;
+    }
+    if (!stream) {
+    } else if (bt == 8) launch_count<8>(A, nbx, d);
     else if (bt == 4) launch_count<4>(A, nbx, d);
     else if (bt == 2) launch_count<2>(A, nbx, d);
     else launch_count<1>(A, nbx, d);
     std::vector<unsigned> hc((size_t)blocks);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpy(hc.data(), d, sizeof(unsigned) * blocks, hipMemcpyDeviceToHost);
-    hipFree(d);
+    if (e == hipSuccess) e = hipMemcpy(hc.data(), d_all, sizeof(unsigned) * blocks, hipMemcpyDeviceToHost);
+    hipFree(d_all);
     if (e != hipSuccess) { set_error(std::string("count tiles: ") + hipGetErrorString(e)); return BNOS_E_DEVICE; }
     int64_t tot = 0;
     for (unsigned v : hc) tot += v;
@@ -540,13 +735,25 @@ extern "C" bnos_status bnos_table_autotune(bnos_table h, const int32_t *orders, 
     double best_ms = 1e300;
     int best_cs = t->chunk_entries / kEntriesPerStep, best_bt = pick_bt(t, B);
     bnos_status s = BNOS_OK;
-    for (int cs = 1; cs <= t->pad_steps && e == hipSuccess && s == BNOS_OK; cs <<= 1) {
-        t->tuned_cs[bk] = cs;
-        if ((s = ensure_workspace(t, B)) != BNOS_OK) break;
-        for (int bt = 1; bt <= 8 && bt <= B && s == BNOS_OK; bt <<= 1) {
+    const bool kept = t->kept_rows();        // one launch whatever the shape: time it once, as it is set
+    if (kept && e == hipSuccess) s = ensure_kept_workspace(t, B);
+    if (kept) best_cs = t->chunk_entries_for(B) / kEntriesPerStep;
+    for (int cs = kept ? best_cs : 1; cs <= t->pad_steps && e == hipSuccess && s == BNOS_OK; cs <<= 1) {
+        if (!kept) {
+            t->tuned_cs[bk] = cs;
+            if ((s = ensure_workspace(t, B)) != BNOS_OK) break;
+        } else if (best_ms < 1e300) {
+            break;
+        }
+        for (int bt = kept ? best_bt : 1; bt <= 8 && bt <= B && s == BNOS_OK; bt <<= 1) {
+            if (kept && best_ms < 1e300) break;
             ScoreArgs A = score_args(t, orders, B, d_out, d_out + B, d_best, nullptr, nullptr);
             for (int r = 0; r <= reps && s == BNOS_OK; ++r) {
                 if (r == 1) e = hipEventRecord(e0, st);
+                if (kept) {
+                    s = launch_kept(t, A, st, false);
+                    continue;
+                }
                 if ((s = launch_stream(t, A, st, bt)) != BNOS_OK) break;
                 hipLaunchKernelGGL(k_merge, dim3(B), dim3(kMergeWaves * 64), 0, st, A);
             }
@@ -698,8 +905,21 @@ extern "C" bnos_status bnos_score_orders_noalloc(bnos_table h, const int32_t *or
     if (s != BNOS_OK) return s;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     ScoreArgs A = score_args(t, orders, B, lse, maxs, best, node_lse, node_second);
+    if (t->kept_rows() && !t->gather_for(B)) {
+        A.part = reinterpret_cast<Partial *>(part);      // one slot per (order, node), less than what was checked
+        return launch_kept(t, A, st, false);
+    }
+    // kept rows beside the streaming pass (bound off) take one slot more; where that passes the
+    // array, the pass streams the whole rows
+    int64_t extra = (A.kept && !t->gather_for(B)) ? (int64_t)B * t->n * (int64_t)sizeof(Partial) : 0;
+    if (need + extra > (int64_t)kNoAllocScratchBytes) {
+        extra = 0;
+        A.kept = nullptr;
+        A.slot0 = 0;
+        A.slots = A.chunks;
+    }
     A.part = reinterpret_cast<Partial *>(part);
-    A.cut_ws = reinterpret_cast<float *>(static_cast<char *>(part) + cuts_off);
+    A.cut_ws = reinterpret_cast<float *>(static_cast<char *>(part) + ((part_bytes + extra + 255) & ~(int64_t)255));
     if (t->gather_for(B)) s = launch_gather(t, A, st, false);
     else s = launch_stream(t, A, st, 0, false);
     if (s != BNOS_OK) return s;

@@ -374,7 +374,7 @@ struct ScoreArgs {
     int sum_steps;
     const int32_t *orders;
     int B, n;
-    Partial *part;          // [B][chunks][n]
+    Partial *part;          // [B][slots][n]
     double *lse, *maxs;
     uint64_t *best;
     double *node_lse;
@@ -392,6 +392,13 @@ struct ScoreArgs {
     const float *cuts;         // [B][n] each order's cut per node, computed before the launch, or null
     float *cut_ws;             // [B][n] workspace for those cuts (several-order launches)
     int K;
+    // kept entries (see kKeptCap), or null
+    const uint64_t *kmask;     // [n][kept_stride]
+    const float *kscore;
+    const int32_t *klen;       // [n] entries, [n] nodes by descending entries
+    int64_t kept_stride;
+    const uint8_t *kept;       // [n * S_pad / 4] the streaming pass leaves these entries out, or null
+    int slots, slot0;          // partials per (order, node); the streaming pass's chunk c writes slot0 + c
 };
 
 // What one streaming block needs to know about its table and its orders.
@@ -404,7 +411,7 @@ struct TabView {
     int sum_steps;
     int B;                      // orders (chains) of this table; row stride of wl_list
     const int32_t *orders;      // [B][n]
-    Partial *part;              // [B][chunks][n]
+    Partial *part;              // [B][slots][n]
     const int32_t *wl_count;    // [n] or null
     const int32_t *wl_list;     // [n][B]
     const uint64_t *tand;       // [n * S_pad / 256] AND of each 256-entry tile's masks, or null (no skipping)
@@ -416,6 +423,12 @@ struct TabView {
     const float *cuts;          // [orders][n] each order's (chain's) cut per node, computed by an
                                 // earlier launch, or null (the block computes it)
     int K;
+    const uint64_t *kmask;      // [n][kept_stride] kept entries (see kKeptCap), or null
+    const float *kscore;
+    const int32_t *klen;
+    int64_t kept_stride;
+    const uint8_t *kept;        // [n * S_pad / 4] entries the streaming pass leaves out, or null
+    int slots, slot0;           // part is [B][slots][n]; chunk c writes slot slot0 + c
 };
 
 // A row lists every mask over the node's n - 1 slots (slot s is node s below
@@ -599,7 +612,8 @@ __device__ __forceinline__ void bound_cuts(float cv, uint64_t cm, const uint64_t
 // The states and partials are bitwise those of reading the stored masks, for
 // 6 bytes per entry read instead of 12.  NOSAT steps without the saturation
 // test where next_mask_nosat allows it.
-template <int BT, bool CM = false, bool NOSAT = false, int RING = 0>
+// EXC: the kept entries, which another launch folded into slot 0, are left out.
+template <int BT, bool CM = false, bool NOSAT = false, int RING = 0, bool EXC = false>
 __device__ __forceinline__ void score_block(const TabView &V, int node, int chunk, int group, int chunks,
                                             int steps)
 {
@@ -764,7 +778,8 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
     constexpr int D = RING > 0 ? RING : ((BT == 1) ? 3 : 2);
     u64x2 r01[D], r23[D];
     f32x4 rsc[D];
-    uint32_t rneed[D];
+    uint32_t rneed[D], rkept[D];
+    const uint8_t *kp = EXC ? V.kept + (row >> 2) : nullptr;
 #define BNOS_ISSUE(d, kk)                                                                       \
     if ((kk) < nt) {                                                                            \
         const uint32_t q_ = ((uint32_t)s_tile[wave][(kk)] << 6) | (uint32_t)lane;              \
@@ -780,12 +795,14 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
                 r23[d] = __builtin_nontemporal_load(&mp[2 * q_ + 1]);                           \
             }                                                                                   \
             rsc[d] = __builtin_nontemporal_load(&sp[q_]);                                       \
+            if (EXC) rkept[d] = kp[q_];                                                         \
         }                                                                                       \
     }
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         rsc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
         rneed[d] = 0u;
+        rkept[d] = 0u;
         BNOS_ISSUE(d, d)
     }
     for (int k0 = 0; k0 < nt; k0 += D) {
@@ -801,6 +818,7 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
             }
             const float x[4] = {rsc[d].x, rsc[d].y, rsc[d].z, rsc[d].w};
             const uint32_t need_c = rneed[d];
+            const uint32_t kept_c = EXC ? rkept[d] : 0u;
 #pragma unroll
             for (int j = 0; j < BT; ++j) {
                 if (!((need_c >> j) & 1u)) continue;         // uniform
@@ -812,7 +830,7 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
                     // an entry below the order's cut is left out like the tiles below it (it is
                     // neither result and its term is below e^-60 of the largest); cut[j] = -inf
                     // without the bound
-                    const bool ok = (mk[e] & np) == 0ull && !(x[e] < cut[j]);
+                    const bool ok = (mk[e] & np) == 0ull && !(x[e] < cut[j]) && !(EXC && ((kept_c >> e) & 1u));
                     xs[e] = ok ? x[e] : -INFINITY;
                     any |= ok;
                 }
@@ -878,7 +896,7 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
             p.best = r.best;
             p.second = r.sec;
             p.bmask = (CM && r.m != -INFINITY) ? to_nodes(r.bm, node) : r.bm;
-            V.part[((int64_t)ob * V.chunks + chunk) * n + node] = p;
+            V.part[((int64_t)ob * V.slots + V.slot0 + chunk) * n + node] = p;
         }
     }
 }
@@ -907,6 +925,13 @@ __device__ __forceinline__ TabView view_of(const ScoreArgs &A)
     V.cscore = A.cscore;
     V.cuts = A.cuts;
     V.K = A.K;
+    V.kmask = A.kmask;
+    V.kscore = A.kscore;
+    V.klen = A.klen;
+    V.kept_stride = A.kept_stride;
+    V.kept = A.kept;
+    V.slots = A.slots;
+    V.slot0 = A.slot0;
     return V;
 }
 
@@ -1004,7 +1029,7 @@ __device__ __forceinline__ bool xcd_block(int64_t real_x, int &x, int &y)
 // to read, so the longest blocks are dispatched first and the shortest fill
 // the tail.  (An entry that is not a node id keeps the plain mapping; such an
 // order is invalid and scores NaN anyway.)
-template <int BT, bool CM = false, bool NOSAT = false, int RING = 0>
+template <int BT, bool CM = false, bool NOSAT = false, int RING = 0, bool EXC = false>
 __global__ __launch_bounds__(kScoreThreads) void k_score(ScoreArgs A)
 {
     int x, y;
@@ -1015,7 +1040,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(ScoreArgs A)
         const int v = A.orders[(int64_t)y * A.n + (A.n - 1 - node)];
         node = (v >= 0 && v < A.n) ? v : node;
     }
-    score_block<BT, CM, NOSAT, RING>(view_of(A), node, chunk, y, A.chunks, A.chunk_entries / kEntriesPerStep);
+    score_block<BT, CM, NOSAT, RING, EXC>(view_of(A), node, chunk, y, A.chunks, A.chunk_entries / kEntriesPerStep);
 }
 
 // Index of the segment holding x, for prefix bases base[0] = 0 < ... < base[T].
@@ -1032,7 +1057,7 @@ __device__ __forceinline__ int find_segment(const int64_t *__restrict__ base, in
 
 // Many tables in one grid: x runs over every table's (node, chunk) blocks
 // (table k owns x in [blk_base[k], blk_base[k+1])), y = group of BT orders.
-template <int BT>
+template <int BT, bool EXC = false>
 __global__ __launch_bounds__(kScoreThreads) void k_score_multi(const TabView *__restrict__ views,
                                                               const int64_t *__restrict__ blk_base, int T)
 {
@@ -1043,7 +1068,268 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_multi(const TabView *__
     const int local = (int)((int64_t)x - blk_base[k]);
     const int node = local / V.chunks;
     const int chunk = local - node * V.chunks;
-    score_block<BT>(V, node, chunk, y, V.chunks, V.chunk_entries / kEntriesPerStep);
+    score_block<BT, false, false, 0, EXC>(V, node, chunk, y, V.chunks, V.chunk_entries / kEntriesPerStep);
+}
+
+// ------------------------------------------------------------------ kept entries
+//
+// One wavefront reduces one node's kept row for one order, 64 entries a step
+// from the best score down.  The first usable entry is the best (equal scores
+// are listed in ascending mask order, so the tie rule holds), the next one the
+// second best, and once both are known the scan ends at the first step whose
+// first score lies kBoundGap nats below the best: a wavefront needs no per-lane
+// top-2 states, no tile summaries and no candidates, and reads only the part of
+// the row that matters.
+//
+// The sum of exp(x - best) does not depend on which lane, wavefront or launch
+// adds which entry: each FP32 term, at most 1, is rounded to a multiple of
+// 2^-47 and added as a 64-bit integer (a row lists at most 2^16 of them).  A term
+// below e^-kBoundGap rounds to zero, which is why the scan may stop there and
+// why the left-out entries of the row change no bit.  (The rounding moves a sum
+// by at most 2^-48 per term; FP32, in which the partials hold it, resolves 2^-24.)
+// The rounding is that of an FP64 addition to 48 = 1.5 * 2^5, whose ulp is 2^-47:
+// the integers are the bits of the results less those of 48.
+struct KeptAcc {
+    float best, sec;
+    uint64_t bm;
+    uint64_t s;      // sum of the rounded terms in units of 2^-47
+};
+
+__device__ __forceinline__ float kept_sum(const KeptAcc &a) { return (float)((double)a.s * 0x1p-47); }
+
+// A step takes kKeptTiles * 64 entries (rows are padded to whole steps), and the next
+// step's loads are issued, whether it will be needed or not, before the current one is
+// folded: a step folds in a few hundred cycles, about what a load from L2 takes.
+// (Loads inside conditions, one 64-entry tile at a time, made the compiler wait for every
+// load where the paths met: 0.7 us per tile.)
+struct KeptStep {
+    uint64_t m[kKeptTiles];
+    float x[kKeptTiles];
+};
+
+struct KeptScan {
+    KeptAcc a;
+    float stop;      // the gap's lower end once both results are known
+    int found;
+};
+
+__device__ __forceinline__ void kept_load(KeptStep &s, const uint64_t *__restrict__ km, const float *__restrict__ ks,
+                                          int step, int lane)
+{
+    // the step's uniform base stays in scalar registers (opaque, so that no vector address, whose
+    // registers would have to wait for earlier loads, is formed from it)
+    step = __builtin_amdgcn_readfirstlane(step);
+    uint64_t bm = reinterpret_cast<uint64_t>(km + step * (kKeptTiles * 64));
+    uint64_t bx = reinterpret_cast<uint64_t>(ks + step * (kKeptTiles * 64));
+    asm("" : "+s"(bm), "+s"(bx));
+    const auto *pm = reinterpret_cast<const __attribute__((address_space(1))) uint64_t *>(bm);
+    const auto *px = reinterpret_cast<const __attribute__((address_space(1))) float *>(bx);
+#pragma unroll
+    for (int d = 0; d < kKeptTiles; ++d) {
+        s.m[d] = pm[(uint32_t)(d * 64 + lane)];
+        s.x[d] = px[(uint32_t)(d * 64 + lane)];
+    }
+    __builtin_amdgcn_sched_barrier(0);       // the loads go out before the other step is waited for
+}
+
+// Takes the best and second best from a step while they are missing; false when the step holds no
+// usable entry.
+__device__ __forceinline__ bool kept_top(KeptScan &S, const KeptStep &s, uint64_t np)
+{
+    uint64_t bal[kKeptTiles], any = 0ull;
+#pragma unroll
+    for (int d = 0; d < kKeptTiles; ++d) {
+        bal[d] = __ballot((s.m[d] & np) == 0ull);
+        any |= bal[d];
+    }
+    if (any == 0ull) return false;                           // uniform
+    if (S.found < 2) {                                       // uniform
+#pragma unroll
+        for (int d = 0; d < kKeptTiles; ++d) {
+            uint64_t b = bal[d];
+            if (b != 0ull && S.found == 0) {
+                const int l = __builtin_ctzll(b);
+                S.a.best = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s.x[d]), l));
+                S.a.bm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(s.m[d] >> 32), l) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)s.m[d], l);
+                b &= b - 1;
+                S.found = 1;
+            }
+            if (b != 0ull && S.found == 1) {
+                const int l = __builtin_ctzll(b);
+                S.a.sec = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s.x[d]), l));
+                S.found = 2;
+                S.stop = fminf(gap_below(S.a.best), S.a.sec);
+            }
+        }
+    }
+    return true;
+}
+
+// Folds one step; false when STOP and the row's rest lies below the gap (nothing of this step is
+// folded then).
+template <bool STOP>
+__device__ __forceinline__ bool kept_fold(KeptScan &S, const KeptStep &s, uint64_t np)
+{
+    const float x0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, s.x[0])));
+    if (STOP && x0 < S.stop) return false;                   // uniform; never before both results are known
+    if (!kept_top(S, s, np)) return true;
+    uint64_t acc = 0ull - kKeptTiles * __builtin_bit_cast(uint64_t, 48.0);
+#pragma unroll
+    for (int d = 0; d < kKeptTiles; ++d) {
+#pragma clang fp contract(off)
+        const float e = ((s.m[d] & np) == 0ull) ? __builtin_amdgcn_exp2f((s.x[d] - S.a.best) * kLog2e) : 0.f;
+        acc += __builtin_bit_cast(uint64_t, (double)e + 48.0);
+    }
+    S.a.s += acc;
+    return true;
+}
+
+// np: complement of the predecessor set; STOP: end at the gap (else the whole row).
+// `steps` (may be null) receives the steps folded.
+template <bool STOP>
+__device__ __forceinline__ KeptAcc kept_scan(const uint64_t *__restrict__ km, const float *__restrict__ ks, int len,
+                                             uint64_t np, int lane, int *steps = nullptr)
+{
+    KeptScan S;
+    S.a.best = -INFINITY;
+    S.a.sec = -INFINITY;
+    S.a.bm = ~0ull;
+    S.a.s = 0ull;
+    S.stop = -INFINITY;
+    S.found = 0;
+    const int ns = (len + kKeptTiles * 64 - 1) / (kKeptTiles * 64);      // >= 1: the empty set is kept
+    KeptStep A, B;
+    kept_load(A, km, ks, 0, lane);
+    int t = 0;
+    for (;;) {
+        kept_load(B, km, ks, t + 1 < ns ? t + 1 : t, lane);
+        if (!kept_fold<STOP>(S, A, np)) break;               // uniform
+        if (++t >= ns) break;
+        kept_load(A, km, ks, t + 1 < ns ? t + 1 : t, lane);
+        if (!kept_fold<STOP>(S, B, np)) break;
+        if (++t >= ns) break;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) S.a.s += (uint64_t)__shfl_xor((unsigned long long)S.a.s, off, 64);
+    if (steps) *steps = t;
+    return S.a;
+}
+
+// The same scan shared by W wavefronts, wavefront w taking the steps w, w + W, ...: first each
+// finds its own top two usable entries (or learns that its next steps hold neither of the row's
+// top two), then, with the row's best known, each sums its steps down to the gap.  The result is
+// that of kept_scan, bit for bit: the top two come from the same entries and the sum is of
+// integers.  Every wavefront of the block calls it (it holds two barriers); the result is
+// valid in all of them.
+template <int W>
+struct KeptLds {
+    float best[W], sec[W];
+    uint64_t bm[W], s[W];
+    int second;                    // FP32 bits, ordered: the largest second best any wavefront holds
+};
+
+__device__ __forceinline__ int ordered_f32(float x)
+{
+    const int b = __builtin_bit_cast(int, x);
+    return b >= 0 ? b : b ^ 0x7fffffff;
+}
+
+// Must be called, and a barrier passed, before the block's first kept_scan_shared and between two.
+template <int W>
+__device__ __forceinline__ void kept_shared_reset(KeptLds<W> &L) { L.second = ordered_f32(-INFINITY); }
+
+template <int W, bool STOP>
+__device__ __forceinline__ KeptAcc kept_scan_shared(const uint64_t *__restrict__ km, const float *__restrict__ ks,
+                                                    int len, uint64_t np, int lane, int wave, KeptLds<W> &L)
+{
+    const int ns = (len + kKeptTiles * 64 - 1) / (kKeptTiles * 64);
+    KeptScan S;
+    S.a.best = -INFINITY;
+    S.a.sec = -INFINITY;
+    S.a.bm = ~0ull;
+    S.a.s = 0ull;
+    S.stop = -INFINITY;
+    S.found = 0;
+    bool early = false;            // the first usable entry sits alone in a step already passed
+    int t = wave;
+    KeptStep D;
+    kept_load(D, km, ks, t < ns ? t : ns - 1, lane);
+    while (t < ns) {                                         // uniform
+        const float x0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, D.x[0])));
+        if (ordered_f32(x0) < __builtin_amdgcn_readfirstlane(*(volatile int *)&L.second)) break;
+        KeptStep N;
+        kept_load(N, km, ks, t + W < ns ? t + W : t, lane);
+        const bool had = S.found != 0;
+        kept_top(S, D, np);
+        if (S.found == 2) {
+            early = had;
+            if (lane == 0) atomicMax(&L.second, ordered_f32(S.a.sec));
+            break;
+        }
+        D = N;
+        t += W;
+    }
+    if (S.found == 1) early = true;
+    if (lane == 0) {
+        L.best[wave] = S.a.best;
+        L.sec[wave] = S.a.sec;
+        L.bm[wave] = S.a.bm;
+    }
+    __syncthreads();
+    const float mine = S.a.best;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const float b = L.best[w], c = L.sec[w];
+        const uint64_t m = L.bm[w];
+        if (w == 0) {
+            S.a.best = b;
+            S.a.sec = c;
+            S.a.bm = m;
+            continue;
+        }
+        const bool take = b > S.a.best || (b == S.a.best && m < S.a.bm);
+        S.a.sec = take ? fmaxf(S.a.best, c) : fmaxf(S.a.sec, b);
+        S.a.best = take ? b : S.a.best;
+        S.a.bm = take ? m : S.a.bm;
+    }
+    S.found = 2;
+    S.stop = S.a.sec == -INFINITY ? -INFINITY : fminf(gap_below(S.a.best), S.a.sec);
+    if (early) {
+#pragma clang fp contract(off)
+        const float e = __builtin_amdgcn_exp2f((mine - S.a.best) * kLog2e);
+        const uint64_t u = __builtin_bit_cast(uint64_t, (double)e + 48.0) - __builtin_bit_cast(uint64_t, 48.0);
+        S.a.s = lane == 0 ? u : 0ull;
+    }
+    while (t < ns) {                                         // D holds step t
+        KeptStep N;
+        kept_load(N, km, ks, t + W < ns ? t + W : t, lane);
+        if (!kept_fold<STOP>(S, D, np)) break;
+        D = N;
+        t += W;
+    }
+    uint64_t s = S.a.s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) s += (uint64_t)__shfl_xor((unsigned long long)s, off, 64);
+    if (lane == 0) L.s[wave] = s;
+    __syncthreads();
+    s = 0ull;
+#pragma unroll
+    for (int w = 0; w < W; ++w) s += L.s[w];
+    S.a.s = s;
+    return S.a;
+}
+
+// The partial in `slot` of (order b, node).
+__device__ __forceinline__ void kept_store(const TabView &V, int b, int node, const KeptAcc &a)
+{
+    Partial p;
+    p.m = a.best;
+    p.s = kept_sum(a);
+    p.best = a.best;
+    p.second = a.sec;
+    p.bmask = a.bm;
+    V.part[(int64_t)b * V.slots * V.n + node] = p;
 }
 
 // ------------------------------------------------------------------ gather scoring
@@ -1161,7 +1447,7 @@ __device__ __forceinline__ void merge_block(const ScoreArgs &A, int b, MergeLds 
     // the order's entries are requested first and checked after the merge, so the
     // two loads overlap
     const int v = lane < n ? A.orders[(int64_t)b * n + lane] : -1;
-    const Acc r = merge_nodes(A.part + (int64_t)b * A.chunks * n, n, A.chunks, lane < n ? lane : -1, L);
+    const Acc r = merge_nodes(A.part + (int64_t)b * A.slots * n, n, A.slots, lane < n ? lane : -1, L);
     valid = order_valid(v, n, lane);
     lse_out = 0.0;
     max_out = 0.0;
@@ -1188,5 +1474,6 @@ ScoreArgs score_args(const TableT *t, const int32_t *orders, int B, double *lse,
 bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt, bool allow_timing = true);
 bnos_status launch_gather(TableT *t, ScoreArgs &A, hipStream_t st, bool allow_timing = true);
 bnos_status launch_merge(const ScoreArgs &A, hipStream_t st);
+bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timing = true);
 
 }  // namespace bnos

@@ -1,0 +1,81 @@
+"""Scoring and chains from the kept rows (the entries no subset of theirs rules out), at the sizes
+where their scan can go wrong: rows of one step, of many, of several sort runs, and rows too long
+to be kept; every number of wavefronts per row."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_1210_5128_amd import datagen
+
+from test_gpu_parity import check_orders_against_oracle, dev_score, same_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bnos():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1210_5128_amd import bnos as b
+    return b
+
+
+# (n, K, N, arities): a row of one entry; 64, 512 and 513 entries; one row per wavefront and more; kept
+# rows of several thousand entries; of 27,000 to 45,000 (several sort runs); above 65,536 (not kept); no data,
+# where every score ties
+SHAPES = [(1, 0, 20, (2,)), (7, 6, 100, (2,)), (10, 6, 60, (2,)), (12, 4, 200, (2, 3)), (20, 4, 1000, (2,)),
+          (33, 3, 80, (2,)), (26, 5, 300, (2,)), (36, 4, 2000, (2, 3, 4)), (64, 2, 129, (2,)), (48, 4, 60, (2,)),
+          (9, 4, 0, (2, 3))]
+
+
+@pytest.mark.parametrize("n,K,N,arities", SHAPES)
+def test_kept_rows_against_streaming_and_oracle(bnos, n, K, N, arities):
+    # with the bound off the streaming pass adds every entry that was not kept: bitwise equal, whatever
+    # the number of orders (8, 4, 2 or 1 wavefronts per row, or one block per order); and the oracle
+    net = datagen.random_network(n, N, arities, min(3, n - 1), seed=n + 10 * K)
+    t = bnos.build_score_table(net.data, net.arities, K)
+    orc = oracle.build_table(net.data, net.arities, K) if n <= 20 else None
+    try:
+        for B in (1, 6, 70, 700):
+            orders = datagen.random_orders(n, B, seed=n + B)
+            got = dev_score(t, orders)
+            t.score_bound(False)
+            plain = dev_score(t, orders)
+            t.score_bound(True)
+            same_bits(got, plain)
+            if orc is not None and B == 6:
+                assert check_orders_against_oracle(got, orc, K, orders) == 0
+            if t.kept_entries():          # an order's result does not depend on the batch it is in
+                one = dev_score(t, orders[B // 2:B // 2 + 1])
+                same_bits(one, {k: v[B // 2:B // 2 + 1] for k, v in got.items()})
+    finally:
+        t.free()
+
+
+def test_kept_rows_invalid_orders_and_memory_cap(bnos, monkeypatch):
+    # an order that is not a permutation gives NaN and leaves the others alone; a table built under a
+    # memory cap that has no room for kept rows scores the same (to the association of FP32 sums)
+    net = datagen.random_network(24, 1500, (2, 3, 4), 3, seed=8)
+    t = bnos.build_score_table(net.data, net.arities, 4)
+    orders = datagen.random_orders(24, 9, seed=2)
+    bad = orders.copy()
+    bad[3, 0], bad[5, 7], bad[7, 2] = bad[3, 1], -1, 24
+    got, ref = dev_score(t, bad), dev_score(t, orders)
+    for b in range(9):
+        if b in (3, 5, 7):
+            assert np.isnan(got["lse"][b]) and np.isnan(got["max"][b]) and np.all(got["best"][b] == 0)
+        else:
+            same_bits({k: v[b:b + 1] for k, v in got.items()}, {k: v[b:b + 1] for k, v in ref.items()})
+    held = t.info()["device_bytes"]
+    assert t.kept_entries() > 0
+    monkeypatch.setenv("BNOS_MAX_DEVICE_BYTES", str(held - 100000))
+    c = bnos.build_score_table(net.data, net.arities, 4)
+    assert c.kept_entries() == 0 and c.info()["device_bytes"] <= held - 100000
+    out = dev_score(c, orders)
+    assert np.array_equal(out["best"], ref["best"])
+    assert np.array_equal(out["node_second"].view(np.uint32), ref["node_second"].view(np.uint32))
+    np.testing.assert_allclose(out["node_lse"], ref["node_lse"], rtol=0, atol=2e-6)
+    t.free()
+    c.free()
