@@ -122,7 +122,8 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
  * one; the build lists every row's other entries apart, in descending score, and
  * scoring and chains with the score bound on (bnos_table_score_bound) read those
  * alone.  *entries = kept entries of all rows, 0 for a table that has none listed
- * (a row of more than 65,536, or no memory for them within BNOS_MAX_DEVICE_BYTES);
+ * (more than 16,384 per row on average, or no memory for them within
+ * BNOS_MAX_DEVICE_BYTES);
  * the streaming pass then serves it.
  */
 bnos_status bnos_table_kept(bnos_table t, int64_t *entries);

@@ -55,13 +55,14 @@ constexpr float kBoundGap = 60.0f;
 // largest one -- the score bound's own criterion, from subsets instead of
 // candidates, once for all orders.  A build therefore lists each row's other
 // entries, the kept ones, apart: at n = 60, K = 4, N = 5,000 they are 1,200 to
-// 6,200 of 489,406 per row, depending on the data.  Rows of more than kKeptCap
-// kept entries stay with the streaming pass, which shares each streamed tile
-// between orders (a scan of 65,536 entries takes about what the streaming pass
-// spends on a pair of order and node at that size).
-constexpr int kKeptCap = 65536;
+// 6,200 of 489,406 per row on average, depending on the data, with single rows
+// of 100,000.  A table that keeps more than kKeptMean per row on average (few
+// samples of binary variables: nearly all of them) stays with the streaming pass,
+// which shares each streamed tile between orders.
+constexpr int kKeptMean = 16384;
+constexpr int kKeptCap = 1 << 19;         // entries of one row
 constexpr int kKeptRun = 16384;           // sort keys of one block: 128 KB of LDS
-constexpr int kKeptTiles = 8;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
+constexpr int kKeptTiles = 4;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
 constexpr int64_t kKeptSubsetCap = (int64_t)1 << 26;   // (node, subset) records of the build's pass over subsets
 
 // Partial-reduction record written by each scoring block (one per order).
@@ -101,15 +102,15 @@ struct TableT {
     float *d_cscore = nullptr;      // [n][kBoundSlots]: their scores (-inf for none)
     bool score_bound = true;        // one-order blocks skip tiles by the score bound
 
-    // kept entries (null when the table has none listed): row i's sit at i * kept_stride, in
-    // descending score, equal scores in ascending mask order, padded with (~0, -inf) to a
-    // multiple of 64 * kKeptTiles
-    uint64_t *d_kmask = nullptr;    // [n][kept_stride]
-    float *d_kscore = nullptr;      // [n][kept_stride]
-    int32_t *d_klen = nullptr;      // [n] kept entries, then [n] the nodes in descending order of them
+    // kept entries (null when the table has none listed): row i's klen[i] sit from entry
+    // klen[2 n + i] on, in descending score, equal scores in ascending mask order, padded with
+    // (~0, -inf) to a multiple of 64 * kKeptTiles
+    uint64_t *d_kmask = nullptr;    // [kept_cap]
+    float *d_kscore = nullptr;      // [kept_cap]
+    int32_t *d_klen = nullptr;      // [4][n]: kept entries, the nodes in descending order of them, first entries, -
     float *d_kpm = nullptr;         // [n][n]: largest kept score of row i among the sets holding node m
     uint8_t *d_kept = nullptr;      // [n * S_pad / 4]: bit e of byte g set when entry 4 g + e is kept
-    int64_t kept_stride = 0;
+    int64_t kept_cap = 0;           // entries the arrays hold
     int64_t kept_total = 0;         // kept entries of all rows
     int64_t kept_steps = 0;         // scan steps of all kept rows
     int kept_steps_max = 0;         // and of the longest one
@@ -179,7 +180,7 @@ struct TableT {
     bool kept_rows() const { return d_kmask != nullptr && score_bound && tile_skip; }
     int64_t kept_bytes() const
     {
-        return (int64_t)n * kept_stride * 12 + (int64_t)n * 8 + (int64_t)n * n * 4 + (int64_t)n * (S_pad / 4);
+        return kept_cap * 12 + (int64_t)n * 16 + (int64_t)n * n * 4 + (int64_t)n * (S_pad / 4);
     }
 };
 

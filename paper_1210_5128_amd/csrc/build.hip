@@ -736,7 +736,7 @@ __global__ __launch_bounds__(256) void k_anchor(const uint64_t *__restrict__ mas
     anchor[g] = (m == ~0ull) ? (1ull << (n - 1)) : ((m & low) | ((m >> 1) & ~low));
 }
 
-// ---- kept entries (see kKeptCap)
+// ---- kept entries (see kKeptMean)
 //
 // Subset records: sub[node][r], r the rank of a set among those of at most K - 1
 // members, holds (the largest score among the set's subsets and itself, its own
@@ -845,33 +845,44 @@ __device__ __forceinline__ float keep_gap_below(float b)
     return (b - g >= kBoundGap) ? g : -INFINITY;
 }
 
+// Where a row's kept entries sit: rows follow one another, padded to whole steps of a scan.
+// By one wavefront; *fits tells whether all rows have room.
+__device__ __forceinline__ int kept_place_of(const int32_t *klen, int n, int node, int64_t cap, bool *fits)
+{
+    const int lane = threadIdx.x & 63;
+    constexpr int kStep = 64 * kKeptTiles;
+    const int len = lane < n ? klen[lane] : 0;
+    int64_t sum = (len + kStep - 1) / kStep * kStep;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t o = __shfl_up(sum, off, 64);
+        if (lane >= off) sum += o;
+    }
+    *fits = __shfl(sum, 63, 64) <= cap && __ballot(len > kKeptCap) == 0ull;
+    return node > 0 ? (int)__shfl(sum, node - 1, 64) : 0;
+}
+
 // One thread per 4-entry group of a row: which of its entries are kept (the byte of
-// `kept`), and a sort key for each, appended to the node's list (in any order: the sort
-// fixes it).  A key's high half falls as the score rises, its low half is the place in
-// the row, so ascending keys list descending scores and, among equal ones, ascending masks.
-// The counter goes on past the capacity; the host then lists no kept rows.
+// `kept`), and the rows' numbers of them.
 __global__ __launch_bounds__(256) void k_keep_entries(const uint64_t *__restrict__ masks,
                                                       const float *__restrict__ scores,
                                                       const int64_t *__restrict__ nsets, int n, int K, int64_t S,
                                                       int64_t S_pad, int64_t sub_row, const SubRec *__restrict__ sub,
-                                                      int64_t stride, uint8_t *__restrict__ kept,
-                                                      uint64_t *__restrict__ keys, int32_t *__restrict__ cnt)
+                                                      uint8_t *__restrict__ kept, int32_t *__restrict__ klen)
 {
     __shared__ int s_ns[512];
     load_nsets32(nsets, s_ns);
     const int node = blockIdx.y;
     const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;       // the row's 4-entry group (S_pad / 4 is a multiple of 256)
-    const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)node * S_pad;
     const SubRec *srow = sub + (int64_t)node * sub_row;
     const float empty = scores[row];
     uint32_t bits = 0u;
-    float x[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int64_t at = 4 * q + e;
-        x[e] = scores[row + at];
         if (at >= S) continue;
+        const float x = scores[row + at];
         const uint64_t nm = masks[row + at];
         const uint64_t low = (1ull << node) - 1ull;
         const uint64_t m = (nm & low) | ((nm >> 1) & ~low);          // slot space
@@ -879,112 +890,187 @@ __global__ __launch_bounds__(256) void k_keep_entries(const uint64_t *__restrict
         if (__popcll(m) >= 2) {
             float top, sec;
             subset_bounds(m, K - 1, s_ns, srow, empty, top, sec);
-            keep = !(x[e] < keep_gap_below(top) && x[e] < sec);
+            keep = !(x < keep_gap_below(top) && x < sec);
         }
         bits |= keep ? (1u << e) : 0u;
     }
     kept[row / 4 + q] = (uint8_t)bits;
-    // places of this wavefront's kept entries: one counter update per wavefront
-    int mine = __popc(bits), before = mine;
+    int mine = __popc(bits);
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(before, off, 64);
-        if (lane >= off) before += o;
-    }
-    const int total = __shfl(before, 63, 64);
-    if (total == 0) return;                                          // uniform per wavefront
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&cnt[node], total);
-    base = __shfl(base, 0, 64) + before - mine;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if ((bits >> e) & 1u) {
-            if (base < stride) {
-                const uint32_t u = __float_as_uint(x[e] + 0.0f);     // -0 sorts as +0
-                const uint32_t up = (u >> 31) ? ~u : (u | 0x80000000u);   // rises with the score
-                keys[(int64_t)node * stride + base] = ((uint64_t)~up << 32) | (uint32_t)(4 * q + e);
-            }
-            ++base;
-        }
+    for (int off = 1; off < 64; off <<= 1) mine += __shfl_xor(mine, off, 64);
+    if ((threadIdx.x & 63) == 0 && mine != 0) atomicAdd(&klen[node], mine);
 }
 
-// One node's kept row from its sorted runs of keys (one block): each key's place is its place
-// in its own run plus the smaller keys of the other runs (keys are distinct); the entries after
-// the last one, up to a whole step of a scan, are padding.  With it the largest kept score among
-// the sets holding each node (the first place that holds it), the row's score-bound candidates
-// (as k_bound_cands lists them, but the top kept entries), and the row's place among the rows
-// in descending length, after the lengths.
-struct KeepOut {
-    uint64_t *kmask;
-    float *kscore, *kpm;
-    int32_t *klen;
-    uint64_t *cmask;
-    float *cscore;
-    int64_t stride;
-};
+// A sort key for each kept entry, appended to its row's list (in any order: the sort fixes
+// it).  A key's high half falls as the score rises, its low half is the place in the row, so
+// ascending keys list descending scores and, among equal ones, ascending masks.  klen also
+// receives the rows' first entries, and holds the lists' cursors (zero at first).
+__global__ __launch_bounds__(256) void k_keep_keys(const float *__restrict__ scores, int n, int64_t S_pad,
+                                                   const uint8_t *__restrict__ kept, int64_t cap,
+                                                   uint64_t *__restrict__ keys, int32_t *klen)
+{
+    const int node = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    bool fits;
+    const int first = kept_place_of(klen, n, node, cap, &fits);
+    if (!fits) return;                                               // uniform over the grid
+    if (blockIdx.x == 0 && threadIdx.x == 0) klen[2 * n + node] = first;
+    const int64_t row = (int64_t)node * S_pad;
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < S_pad / 4; q += (int64_t)gridDim.x * 256) {
+        const uint32_t bits = kept[row / 4 + q];
+        const int mine = __popc(bits);
+        int before = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(before, off, 64);
+            if (lane >= off) before += o;
+        }
+        const int total = __shfl(before, 63, 64);
+        if (total == 0) continue;                                    // uniform per wavefront
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&klen[3 * n + node], total); // one update per wavefront
+        base = first + __shfl(base, 0, 64) + before - mine;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((bits >> e) & 1u) {
+                const uint32_t u = __float_as_uint(scores[row + 4 * q + e] + 0.0f);   // -0 sorts as +0
+                const uint32_t up = (u >> 31) ? ~u : (u | 0x80000000u);               // rises with the score
+                keys[base++] = ((uint64_t)~up << 32) | (uint32_t)(4 * q + e);
+            }
+    }
+}
 
-__device__ __forceinline__ void keep_finish(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
-                                            const uint64_t *keys, const KeepOut &O)
+// The kept row's entry `place` from its key.
+__device__ __forceinline__ void keep_entry(const uint64_t *masks, const float *scores, int64_t row, uint64_t key,
+                                           uint64_t *kmask, float *kscore, int64_t place)
+{
+    const int64_t at = row + (uint32_t)key;
+    kmask[place] = masks[at];
+    kscore[place] = scores[at];
+}
+
+// Sort of one run of a row's keys (bitonic, in LDS); a row of one run goes straight to its kept
+// entries.
+__global__ __launch_bounds__(1024) void k_keep_sort(const uint64_t *__restrict__ masks,
+                                                    const float *__restrict__ scores, int n, int64_t S_pad,
+                                                    int64_t cap, const int32_t *__restrict__ klen, uint64_t *keys,
+                                                    uint64_t *__restrict__ kmask, float *__restrict__ kscore)
+{
+    __shared__ uint64_t s_key[kKeptRun];
+    const int node = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int all = klen[node], begin = blockIdx.y * kKeptRun;
+    if (begin >= all) return;                                        // uniform
+    bool fits;
+    const int64_t first = kept_place_of(klen, n, node, cap, &fits);
+    if (!fits) return;                                               // uniform
+    const int len = all - begin < kKeptRun ? all - begin : kKeptRun;
+    int P = 64;
+    while (P < len) P <<= 1;                                         // P <= kKeptRun
+    uint64_t *run = keys + first + begin;
+    for (int i = tid; i < P; i += 1024) s_key[i] = i < len ? run[i] : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j >= 1; j >>= 1) {
+            for (int i = tid; i < P / 2; i += 1024) {
+                const int a = 2 * i - (i & (j - 1)), b = a + j;       // the i-th pair at distance j
+                const uint64_t x = s_key[a], y = s_key[b];
+                const bool up = (a & k) == 0;
+                if ((x > y) == up) {
+                    s_key[a] = y;
+                    s_key[b] = x;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < len; i += 1024) {
+        if (all <= kKeptRun) keep_entry(masks, scores, (int64_t)node * S_pad, s_key[i], kmask, kscore, first + i);
+        else run[i] = s_key[i];
+    }
+}
+
+// The kept entries of a row of several sorted runs: a key's place is its place in its own run
+// plus the smaller keys of the other runs (keys are distinct).  One thread per key.
+__global__ __launch_bounds__(1024) void k_keep_merge(const uint64_t *__restrict__ masks,
+                                                     const float *__restrict__ scores, int n, int64_t S_pad,
+                                                     int64_t cap, const int32_t *__restrict__ klen,
+                                                     const uint64_t *__restrict__ keys,
+                                                     uint64_t *__restrict__ kmask, float *__restrict__ kscore)
+{
+    const int node = blockIdx.x;
+    const int len = klen[node], i = blockIdx.y * 1024 + threadIdx.x;
+    if (len <= kKeptRun || blockIdx.y * 1024 >= (unsigned)len) return;   // uniform
+    bool fits;
+    const int64_t first = kept_place_of(klen, n, node, cap, &fits);
+    if (!fits || i >= len) return;
+    const uint64_t *k = keys + first;
+    const uint64_t key = k[i];
+    const int own = i / kKeptRun;
+    int place = i - own * kKeptRun;
+    for (int r = 0; r * kKeptRun < len; ++r) {
+        if (r == own) continue;
+        int lo = r * kKeptRun, hi = lo + kKeptRun < len ? lo + kKeptRun : len;
+        const int lo0 = lo;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (k[mid] < key) lo = mid + 1;
+            else hi = mid;
+        }
+        place += lo - lo0;
+    }
+    keep_entry(masks, scores, (int64_t)node * S_pad, key, kmask, kscore, first + place);
+}
+
+// One block per kept row: its padding, the largest kept score among the sets holding each node
+// (the first place that holds it), the row's score-bound candidates (as k_bound_cands lists
+// them, but the top kept entries), and its place among the rows in descending length.
+__global__ __launch_bounds__(1024) void k_keep_top(int n, int64_t cap, int32_t *klen, uint64_t *kmask, float *kscore,
+                                                   float *__restrict__ kpm, uint64_t *__restrict__ cmask,
+                                                   float *__restrict__ cscore)
 {
     __shared__ int s_first[64];
     const int node = blockIdx.x;
     const int tid = threadIdx.x;
-    const int len = O.klen[node];
-    uint64_t *cm = O.cmask + (int64_t)node * kBoundSlots, *krow = O.kmask + (int64_t)node * O.stride;
-    float *cs = O.cscore + (int64_t)node * kBoundSlots, *xrow = O.kscore + (int64_t)node * O.stride;
+    const int len = klen[node];
+    bool fits;
+    const int64_t first = kept_place_of(klen, n, node, cap, &fits);
+    if (!fits) return;                                               // uniform
+    uint64_t *krow = kmask + first, *cm = cmask + (int64_t)node * kBoundSlots;
+    float *xrow = kscore + first, *cs = cscore + (int64_t)node * kBoundSlots;
     if (tid < 64) {
         s_first[tid] = 0x7fffffff;
-        const int o = tid < n ? O.klen[tid] : -1;
+        const int o = tid < n ? klen[tid] : -1;
         const int before = __popcll(__ballot(o > len || (o == len && tid < node)));
-        if (tid == 0) O.klen[n + before] = node;
+        if (tid == 0) klen[n + before] = node;
     }
     if (tid < kBoundSlots) {
         cm[tid] = ~0ull;
         cs[tid] = -INFINITY;
     }
-    __syncthreads();
     constexpr int kStep = 64 * kKeptTiles;
-    const int padded = (len + kStep - 1) / kStep * kStep;            // at most stride
-    for (int i = tid; i < padded; i += 1024) {
-        int place = i;
-        uint64_t m = ~0ull;
-        float x = -INFINITY;
-        if (i < len) {
-            const uint64_t key = keys[i];
-            const int own = i / kKeptRun;
-            place = i - own * kKeptRun;
-            for (int r = 0; r * kKeptRun < len; ++r) {
-                if (r == own) continue;
-                int lo = r * kKeptRun, hi = lo + kKeptRun < len ? lo + kKeptRun : len;
-                const int lo0 = lo;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (keys[mid] < key) lo = mid + 1;
-                    else hi = mid;
-                }
-                place += lo - lo0;
-            }
-            const int64_t at = (int64_t)node * S_pad + (uint32_t)key;
-            m = masks[at];
-            x = scores[at];
-            for (uint64_t r = m; r; r &= r - 1) {
-                const int b = __builtin_ctzll(r);
-                if (place < s_first[b]) atomicMin(&s_first[b], place);
-            }
-            if (__popcll(m) < 2) {                                   // the empty set and the singletons
-                const int b = m ? __builtin_ctzll(m) : 64;
-                const int to = m == 0ull ? 63 : (b < node ? b : b - 1);
-                cm[to] = m;
-                cs[to] = x;
-            }
+    const int padded = (len + kStep - 1) / kStep * kStep;
+    for (int i = len + tid; i < padded; i += 1024) {
+        krow[i] = ~0ull;
+        xrow[i] = -INFINITY;
+    }
+    __syncthreads();
+    for (int i = tid; i < len; i += 1024) {
+        const uint64_t m = krow[i];
+        for (uint64_t r = m; r; r &= r - 1) {
+            const int b = __builtin_ctzll(r);
+            if (i < s_first[b]) atomicMin(&s_first[b], i);
         }
-        krow[place] = m;
-        xrow[place] = x;
+        if (__popcll(m) < 2) {                                       // the empty set and the singletons
+            const int b = m ? __builtin_ctzll(m) : 64;
+            const int to = m == 0ull ? 63 : (b < node ? b : b - 1);
+            cm[to] = m;
+            cs[to] = xrow[i];
+        }
     }
     __syncthreads();
     if (tid < n) {
         const int f = s_first[tid];
-        O.kpm[(int64_t)node * n + tid] = f < len ? xrow[f] : -INFINITY;
+        kpm[(int64_t)node * n + tid] = f < len ? xrow[f] : -INFINITY;
     }
     if (tid < 64) {                                                  // one wavefront
         int at = 64;
@@ -1002,49 +1088,6 @@ __device__ __forceinline__ void keep_finish(const uint64_t *masks, const float *
             at += __popcll(bal);
         }
     }
-}
-
-// Sort of one run of a node's keys (bitonic, in LDS); with a single run per node, the kept row
-// too.  Nothing is done where the list overflowed.
-__global__ __launch_bounds__(1024) void k_keep_sort(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
-                                                    uint64_t *keys, KeepOut O)
-{
-    __shared__ uint64_t s_key[kKeptRun];
-    const int node = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int all = O.klen[node], first = blockIdx.y * kKeptRun;
-    if (all > O.stride || first >= all) return;                      // uniform
-    const int len = all - first < kKeptRun ? all - first : kKeptRun;
-    int P = 64;
-    while (P < len) P <<= 1;                                         // P <= kKeptRun
-    uint64_t *run = keys + (int64_t)node * O.stride + first;
-    for (int i = tid; i < P; i += 1024) s_key[i] = i < len ? run[i] : ~0ull;
-    __syncthreads();
-    for (int k = 2; k <= P; k <<= 1)
-        for (int j = k >> 1; j >= 1; j >>= 1) {
-            for (int i = tid; i < P / 2; i += 1024) {
-                const int a = 2 * i - (i & (j - 1)), b = a + j;       // the i-th pair at distance j
-                const uint64_t x = s_key[a], y = s_key[b];
-                const bool up = (a & k) == 0;
-                if ((x > y) == up) {
-                    s_key[a] = y;
-                    s_key[b] = x;
-                }
-            }
-            __syncthreads();
-        }
-    if (gridDim.y == 1) {
-        keep_finish(masks, scores, n, S_pad, s_key, O);
-        return;
-    }
-    for (int i = tid; i < len; i += 1024) run[i] = s_key[i];
-}
-
-__global__ __launch_bounds__(1024) void k_keep_finish(const uint64_t *masks, const float *scores, int n, int64_t S_pad,
-                                                      const uint64_t *keys, KeepOut O)
-{
-    if (O.klen[blockIdx.x] > O.stride) return;                       // uniform
-    keep_finish(masks, scores, n, S_pad, keys + (int64_t)blockIdx.x * O.stride, O);
 }
 
 // Counts for explicit (node, parent mask) queries, with the build's counting code.
@@ -1169,7 +1212,7 @@ static void free_kept(TableT *t)
 }
 
 // Lists the table's kept rows after its rows are built (waits for the stream).  A table
-// without them (a row of more than kKeptCap kept entries, a memory cap they would pass, no
+// without them (more kept entries than kKeptMean per row, a memory cap they would pass, no
 // memory for them) is served by the streaming pass, so nothing here fails the build but a
 // device error.
 static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
@@ -1178,10 +1221,11 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
     const int64_t sub_row = K >= 1 ? sets_upto(n - 1, K - 1) : 1;
     if (sub_row * n > kKeptSubsetCap) return hipSuccess;
     constexpr int64_t kStep = 64 * kKeptTiles;
-    t->kept_stride = std::min<int64_t>((t->S + kStep - 1) / kStep * kStep, kKeptCap);
+    const int64_t row_cap = std::min<int64_t>((t->S + kStep - 1) / kStep * kStep, kKeptCap);
+    t->kept_cap = n * std::min<int64_t>(row_cap, kKeptMean);
     if (max_bytes > 0 && t->device_bytes() + t->kept_bytes() > max_bytes) return hipSuccess;
     // one allocation for the table (kept_bytes() of it) and one for the build's passes
-    const int64_t cells = (int64_t)n * t->kept_stride;
+    const int64_t cells = t->kept_cap;
     char *own = nullptr, *tmp = nullptr;
     if (hipMalloc((void **)&own, (size_t)t->kept_bytes()) != hipSuccess ||
         hipMalloc((void **)&tmp, (size_t)(cells * 8 + sub_row * n * (int64_t)sizeof(SubRec))) != hipSuccess) {
@@ -1193,23 +1237,26 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
     t->d_kscore = reinterpret_cast<float *>(own + cells * 8);
     t->d_kpm = reinterpret_cast<float *>(own + cells * 12);
     t->d_klen = reinterpret_cast<int32_t *>(own + cells * 12 + (int64_t)n * n * 4);
-    t->d_kept = reinterpret_cast<uint8_t *>(own + cells * 12 + (int64_t)n * n * 4 + (int64_t)n * 8);
+    t->d_kept = reinterpret_cast<uint8_t *>(own + cells * 12 + (int64_t)n * n * 4 + (int64_t)n * 16);
     uint64_t *keys = reinterpret_cast<uint64_t *>(tmp);
     SubRec *sub = reinterpret_cast<SubRec *>(tmp + cells * 8);
     std::vector<int32_t> len(n);
-    hipError_t e = hipMemsetAsync(t->d_klen, 0, sizeof(int32_t) * n, st);
+    hipError_t e = hipMemsetAsync(t->d_klen, 0, sizeof(int32_t) * 4 * n, st);
     if (e == hipSuccess) {
-        const KeepOut O = {t->d_kmask, t->d_kscore, t->d_kpm, t->d_klen, t->d_cmask, t->d_cscore, t->kept_stride};
-        const unsigned runs = (unsigned)((t->kept_stride + kKeptRun - 1) / kKeptRun);
+        const unsigned groups = (unsigned)(t->S_pad / 1024), longest = (unsigned)std::min<int64_t>(row_cap, cells);
         hipLaunchKernelGGL(k_keep_subsets, dim3(n), dim3(1024), 0, st, t->d_scores, t->d_nsets, n, K, t->S_pad,
                            sub_row, sub);
-        hipLaunchKernelGGL(k_keep_entries, dim3((unsigned)(t->S_pad / 1024), (unsigned)n), dim3(256), 0, st,
-                           t->d_masks, t->d_scores, t->d_nsets, n, K, t->S, t->S_pad, sub_row, sub, t->kept_stride,
-                           t->d_kept, keys, t->d_klen);
-        hipLaunchKernelGGL(k_keep_sort, dim3(n, runs), dim3(1024), 0, st, t->d_masks, t->d_scores, n, t->S_pad, keys, O);
-        if (runs > 1)
-            hipLaunchKernelGGL(k_keep_finish, dim3(n), dim3(1024), 0, st, t->d_masks, t->d_scores, n, t->S_pad, keys,
-                               O);
+        hipLaunchKernelGGL(k_keep_entries, dim3(groups, (unsigned)n), dim3(256), 0, st, t->d_masks, t->d_scores,
+                           t->d_nsets, n, K, t->S, t->S_pad, sub_row, sub, t->d_kept, t->d_klen);
+        hipLaunchKernelGGL(k_keep_keys, dim3(std::min(groups, 64u), (unsigned)n), dim3(256), 0, st, t->d_scores, n,
+                           t->S_pad, t->d_kept, cells, keys, t->d_klen);
+        hipLaunchKernelGGL(k_keep_sort, dim3(n, (longest + kKeptRun - 1) / kKeptRun), dim3(1024), 0, st, t->d_masks,
+                           t->d_scores, n, t->S_pad, cells, t->d_klen, keys, t->d_kmask, t->d_kscore);
+        if (longest > (unsigned)kKeptRun)
+            hipLaunchKernelGGL(k_keep_merge, dim3(n, (longest + 1023) / 1024), dim3(1024), 0, st, t->d_masks,
+                               t->d_scores, n, t->S_pad, cells, t->d_klen, keys, t->d_kmask, t->d_kscore);
+        hipLaunchKernelGGL(k_keep_top, dim3(n), dim3(1024), 0, st, n, cells, t->d_klen, t->d_kmask, t->d_kscore,
+                           t->d_kpm, t->d_cmask, t->d_cscore);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(len.data(), t->d_klen, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st);
@@ -1218,15 +1265,13 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
     if (e != hipSuccess) return e;
     bool fits = true;
     for (int i = 0; i < n; ++i) {
-        fits = fits && len[i] <= t->kept_stride;
-        const int steps = (int)((len[i] + kStep - 1) / kStep);
+        const int64_t steps = (len[i] + kStep - 1) / kStep;
+        fits = fits && len[i] <= kKeptCap;
         t->kept_total += len[i];
         t->kept_steps += steps;
-        t->kept_steps_max = std::max(t->kept_steps_max, steps);
+        t->kept_steps_max = std::max(t->kept_steps_max, (int)steps);
     }
-    if (!fits) {
-        free_kept(t);
-    }
+    if (!fits || t->kept_steps * kStep > cells) free_kept(t);
     return hipSuccess;
 }
 

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "bnos_internal.h"
@@ -410,8 +411,8 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
     const double li = lane < n ? (in ? s_l[lane] : l0) : 0.0;
     const double mi = lane < n ? (in ? s_b[lane] : m0) : 0.0;
     const double si = lane < n ? (in ? s_s[lane] : s0) : 0.0;
-    const double L = wave_sum_f64(li, lane);
-    const double M = wave_sum_f64(mi, lane);
+    const double L = wave_sum_f64(li);
+    const double M = wave_sum_f64(mi);
     const uint64_t chain = (uint64_t)(H.chain0 + c);
     const int64_t t = t0;
     const double nv = H.target ? M : L;
@@ -566,6 +567,468 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
     }
 }
 
+// ------------------------------------------------------------------ chains on kept rows
+//
+// A chain on a table with kept rows needs nothing from the other chains: one block runs
+// many of its iterations in one launch, with the order (each node's position), the nodes'
+// cached results and the counters in registers of its first wavefront.  Per iteration that
+// wavefront draws the swap and finds the nodes it can change; the block's wavefronts scan
+// those nodes' kept rows (kept_scan); the first wavefront decides, writes the traces and
+// goes on.  No work lists, no partials, no launch per iteration: at n = 60 with 256 chains
+// the three launches per iteration took 320 us, most of it in streaming tiles.
+//
+// A swap changes the predecessor set of the nodes from one swapped position to the other,
+// by the swapped nodes for those between, by the whole range for the two themselves.  A
+// node whose kept entries that hold a changed node all score below the node's second best
+// and kBoundGap below its best keeps its result, bit for bit: no such entry was or becomes
+// the best or the second best, and their terms round to zero in its sum.  `kpm` (the
+// largest kept score of a row among the sets holding each node) answers that without a
+// scan for most nodes of the window.
+//
+// Every proposal is drawn from (seed, chain, iteration) alone, so the block looks ahead: it
+// scores the proposals of the next KP iterations at once, each as if those before it were
+// rejected, and takes them in order up to the first accepted one; the later ones are drawn
+// again from the order that one gives.  The decisions are those of one iteration after the
+// other, and an iteration's chain of dependent steps (draw, rows, sum, test) is paid once per
+// round of (1 - r^KP) / (1 - r) iterations, r the share of rejected moves.
+//
+// Wavefront j < KP keeps a copy of the chain's state, one node per lane, and works proposal
+// j; all wavefronts share the scans.
+
+// log q({a, b}) from the lanes' e_i = exp(logit_i - max) and their sum.
+__device__ __forceinline__ double lanes_pair_logq(double e, double sum, int n, int a, int b, double eps)
+{
+    const double pa = readlane_f64(e, a) / sum, pb = readlane_f64(e, b) / sum;
+    const double Q = pa * pb * (1.0 / (1.0 - pa) + 1.0 / (1.0 - pb));
+    return log((1.0 - eps) * Q + eps * 2.0 / ((double)n * (n - 1)));
+}
+
+// Lanes' e_i = exp(logit_i - max) (0 from lane n on) and their sum.
+__device__ __forceinline__ void lanes_softmax(float logit, int n, int lane, double &e, double &sum)
+{
+    const float mx = wave_max_f32(lane < n ? logit : -INFINITY);
+    e = lane < n ? exp((double)logit - (double)mx) : 0.0;
+    sum = wave_sum_f64(e);
+}
+
+// First lane below n whose running sum of p over the lanes exceeds u, or `none`.
+__device__ __forceinline__ int lanes_pick(double p, double u, int n, int lane, int none)
+{
+    double c = p;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(c, off, 64);
+        if (lane >= off) c += o;
+    }
+    const uint64_t hit = __ballot(lane < n && p > 0.0 && u < c);
+    return hit ? __builtin_ctzll(hit) : none;
+}
+
+constexpr int64_t kRunIters = 4096;            // iterations per launch
+
+template <int KP>
+struct ChainLds {
+    uint8_t pos[KP][64];        // each proposal's positions
+    uint64_t aff[KP];           // and the nodes it can change
+    int hint[KP][64];
+    KeptAcc part[KP][64][kStripes];
+    double l[KP][64];           // the changed nodes' results
+    float m[KP][64], sec[KP][64];
+    uint64_t bm[KP][64];
+    double nv[KP], M[KP];       // each proposal's target and max score, and decision
+    int acc[KP], pair[KP][2];   // (and its swapped nodes)
+    float pm[64 * 65];
+    float ptop[64][kStripes];   // best score of each stripe
+    int len[64], off[64];       // the rows' entries and first entries
+};
+
+// Iterations t0 + 1 .. t1 of every chain; the chains' orders after iteration t0 (or, for
+// t0 == t_first, the starting orders in `prop`) are scored first, which rebuilds the caches.
+// What bounds it: latency, of the dependent scan steps (about 0.4 us per 256 entries from L2) and of
+// the draw, sums and barriers of a round (1.5 us).  Per iteration, 256 chains: 8 nodes 2.7 us, 40 nodes
+// (3,600 kept entries per row) 9.1 us, 60 nodes 8 to 18 us (1,500 to 5,100 per row), where the
+// three launches per iteration took 14, 70 and 320 us.
+template <int KP, bool LEARNED, int W>
+__global__ __launch_bounds__(W * 64) void k_chain_run(const TabView *__restrict__ tviews,
+                                                             const ChainView *__restrict__ views,
+                                                             const int64_t *__restrict__ chain_base, int T,
+                                                             int64_t t0, int64_t t1)
+{
+    static_assert(KP <= W && (W & (W - 1)) == 0 && (!LEARNED || KP == 1), "a wavefront per proposal; the network takes one");
+    __shared__ ChainLds<KP> S;
+    __shared__ float s_feat[LEARNED ? 64 * kF : 1];
+    __shared__ typename std::conditional<LEARNED, MlpLds, int>::type s_mlp;
+    const int k = find_segment(chain_base, T, (int64_t)blockIdx.x);
+    const ChainView &H = views[k];
+    const TabView &V = tviews[k];
+    const int c = (int)((int64_t)blockIdx.x - chain_base[k]);
+    const int n = H.n;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row = (int64_t)c * n;
+    const int pms = n | 1;                                   // odd pitch: a column's reads spread over the banks
+    const uint64_t *km = V.kmask;
+    const float *kx = V.kscore;
+    for (int i = tid; i < n * n; i += W * 64) S.pm[(i / n) * pms + i % n] = V.kpm[i];
+    for (int i = tid; i < n * kStripes; i += W * 64) {
+        const int node = i / kStripes, q = i % kStripes;
+        S.ptop[node][q] = q < kept_stripes_of(V.klen[node])
+                              ? kx[V.klen[2 * n + node] + q * (kPartSteps * kStepEntries)]
+                              : -INFINITY;
+    }
+    if (tid < 64) {
+        S.len[tid] = tid < n ? V.klen[tid] : 0;
+        S.off[tid] = tid < n ? V.klen[2 * n + tid] : 0;
+    }
+
+    const bool first = t0 == H.t_first;
+    const bool in = lane < n;
+    const bool ctl = wave < KP;            // this wavefront holds a copy of the chain's state
+    int pos = 64, posn = 64;               // position in the current order, and in this wavefront's proposal
+    double cl = 0.0;                       // cached log-sum-exp
+    float cm = 0.f, csec = 0.f;            // best and second-best score
+    uint64_t cbm = 0ull;                   // best parent set
+    double ce = 0.0, csum = 1.0;           // exp of its network score, and their sum
+    double score = 0.0, best = 0.0, lq_fwd = 0.0;
+    int64_t nacc = 0, hvc = 0;
+    int pa = 0, pb = 0;                    // nodes this wavefront's proposal swaps
+    const uint64_t chain = (uint64_t)(H.chain0 + c);
+    const int64_t every = H.trace_every;
+    int64_t since = 0, tslot = 0;          // iterations since the last traced one, and its place
+    // draws of 64 iterations at a time: lane i holds those of iteration tb + i
+    int64_t tb = t0 - 64;
+    int ra = 0, rb = 0;
+    double rlu = 0.0, rmix = 0.0, ru5 = 0.0, ru6 = 0.0;
+    if (wave == 0) {
+        S.pos[0][lane] = 64;
+        if (in) S.pos[0][(first ? H.prop : H.cur)[row + lane]] = (uint8_t)lane;
+        if (lane == 0) S.aff[0] = all_nodes(n);
+    }
+    __syncthreads();
+    if (ctl) {
+        posn = S.pos[0][lane];
+        pos = posn;
+        score = H.score[c];
+        best = H.best_score[c];
+        nacc = first && H.t_first == 0 ? 0 : H.accepted[c];
+        if (H.hv_feat) hvc = H.hv_count[c];
+        const int64_t kk = t0 - H.t_first;
+        tslot = kk / every;
+        since = kk - tslot * every;
+    }
+    int64_t t = t0;                        // iterations done (t0 is adopted by the first round)
+    bool adopt = true;
+    for (;;) {
+        // proposals of this round: iterations t + 1 .. t + np; the adoption is a round of its own
+        const int np = adopt ? 1 : (t1 - t < KP ? (int)(t1 - t) : KP);
+        // ---- scans: stripe by stripe over the proposals' changed nodes, dealt out to the wavefronts
+        if (tid < 64 * np) S.hint[tid >> 6][lane] = ordered_f32(-INFINITY);
+        __syncthreads();
+        {
+            int at = 0;
+            uint64_t left[KP];
+            int pv[KP];
+#pragma unroll
+            for (int j = 0; j < KP; ++j) {
+                left[j] = j < np ? uniform_u64(S.aff[j]) : 0ull;
+                pv[j] = j < np ? (int)S.pos[j][lane] : 64;
+            }
+            const int lens = in ? S.len[lane] : 0, offs = S.off[lane];
+            const int my_stripes = in ? kept_stripes_of(lens) : 0;
+            for (int q = 0; q < kStripes; ++q) {
+                const uint64_t has = __ballot(my_stripes > q);
+                uint64_t any = 0ull;
+#pragma unroll
+                for (int j = 0; j < KP; ++j) {
+                    left[j] &= has;
+                    any |= left[j];
+                    for (uint64_t rest = left[j]; rest != 0ull; rest &= rest - 1) {   // uniform
+                        if ((at++ & (W - 1)) != wave) continue;
+                        const int node = __builtin_ctzll(rest);
+                        KeptAcc a;
+                        a.best = -INFINITY;
+                        a.sec = -INFINITY;
+                        a.bm = ~0ull;
+                        a.s = 0ull;
+                        if (q == 0 || !(ordered_f32(S.ptop[node][q]) < *(volatile int *)&S.hint[j][node])) {
+                            const int mine = __builtin_amdgcn_readlane(pv[j], node);
+                            const uint64_t pred = __ballot(in && pv[j] < mine);
+                            const int off = __builtin_amdgcn_readlane(offs, node);
+                            a = kept_scan<true>(km + off, kx + off, __builtin_amdgcn_readlane(lens, node), q, ~pred,
+                                                lane, &S.hint[j][node]);
+                        }
+                        if (lane == 0) S.part[j][node][q] = a;
+                    }
+                }
+                if (any == 0ull) break;                      // uniform
+            }
+        }
+        __syncthreads();
+        // ---- each proposal's score and decision
+        double li = cl, M = 0.0;
+        float mi = cm, si = csec;
+        uint64_t bi = cbm;
+        double e = 0.0, esum = 1.0;
+        if (ctl && wave < np) {
+            const bool mine = in && ((S.aff[wave] >> lane) & 1ull);
+            if (mine) {
+                const Acc r = kept_combine(S.part[wave][lane], kept_stripes_of(S.len[lane]));
+                li = (double)r.m + log((double)r.s);
+                mi = r.m;
+                si = r.sec;
+                bi = r.bm;
+                if (KP > 1) {
+                    S.l[wave][lane] = li;
+                    S.m[wave][lane] = mi;
+                    S.sec[wave][lane] = si;
+                    S.bm[wave][lane] = bi;
+                }
+            }
+        }
+        if constexpr (LEARNED) {
+            if (wave == 0 && in) {
+                float *f = s_feat + lane * kF;
+                f[0] = (float)posn / (float)n;
+                f[1] = mi;
+                f[2] = isinf(si) ? 0.f : (float)((double)mi - (double)si);
+#pragma unroll
+                for (int i = 0; i < 5; ++i) f[3 + i] = (float)H.nstat[lane * 5 + i];
+            }
+            __syncthreads();
+            mlp_forward_block(H.mlp, s_feat, n, s_mlp, nullptr);
+        }
+        double nv = 0.0;
+        bool acc = adopt;
+        if (ctl && wave < np) {
+            const double L = wave_sum_f64(in ? li : 0.0);
+            M = wave_sum_f64(in ? (double)mi : 0.0);
+            nv = H.target ? M : L;
+            if constexpr (LEARNED) lanes_softmax(s_mlp.logit[lane], n, lane, e, esum);
+            if (!adopt) {
+                double ratio = nv - score;
+                if constexpr (LEARNED) ratio += lanes_pair_logq(e, esum, n, pa, pb, H.eps) - lq_fwd;
+                acc = readlane_f64(rlu, (int)(t + 1 + wave - tb)) < ratio;
+            }
+            if (KP > 1 && lane == 0) {
+                S.nv[wave] = nv;
+                S.M[wave] = M;
+                S.acc[wave] = acc ? 1 : 0;
+            }
+        }
+        int took = 0, done = np;           // proposal accepted (np: none), and iterations this round settles
+        if (KP > 1) {
+            __syncthreads();
+            if (ctl) {
+                while (took < np && S.acc[took] == 0) ++took;        // uniform
+                done = took < np ? took + 1 : np;
+                acc = took < np;
+            }
+        } else {
+            took = acc ? 0 : np;
+        }
+        if (!ctl) {
+            // (the scanning wavefronts only need to know how far the round went)
+            if (KP > 1) {
+                while (took < np && S.acc[took] == 0) ++took;
+                done = took < np ? took + 1 : np;
+            }
+        } else {
+            // ---- the state after the round; the first wavefront writes what the caller asked for
+            const bool wr = wave == 0;
+            if (!adopt && wr) {            // the rejected proposals
+                const int rej = took < np ? took : np;
+                if (H.flags && lane < rej) H.flags[(int64_t)c * H.iterations + (t - H.t_first) + lane] = 0;
+                for (int i = 0; i < rej; ++i)
+                    if (++since == every) {
+                        since = 0;
+                        ++tslot;
+                        if (lane == 0 && H.trace) H.trace[(int64_t)c * H.trace_len + tslot] = score;
+                        if (H.n_edges > 0) {
+                            const int ech = lane < H.n_edges ? H.edge_cp[2 * lane] : 0;
+                            const int epa = lane < H.n_edges ? H.edge_cp[2 * lane + 1] : 0;
+                            const uint64_t gch = (uint64_t)__shfl((unsigned long long)cbm, ech, 64);
+                            const uint64_t bits = __ballot(lane < H.n_edges && ((gch >> epa) & 1ull));
+                            if (lane == 0) H.edge_trace[(int64_t)c * H.trace_len + tslot] = (uint32_t)bits;
+                        }
+                    }
+            }
+            if (acc) {                     // uniform
+                if (KP > 1) {
+                    nv = S.nv[took];
+                    M = S.M[took];
+                    posn = S.pos[took][lane];
+                    if (took != wave) {
+                        const bool ch = in && ((S.aff[took] >> lane) & 1ull);
+                        li = ch ? S.l[took][lane] : cl;
+                        mi = ch ? S.m[took][lane] : cm;
+                        si = ch ? S.sec[took][lane] : csec;
+                        bi = ch ? S.bm[took][lane] : cbm;
+                    }
+                }
+                bool imp = false;
+                score = nv;
+                if (adopt) {
+                    if (first && H.t_first == 0) {
+                        imp = true;
+                        best = M;
+                        if (wr && lane == 0 && H.trace) H.trace[(int64_t)c * H.trace_len] = nv;
+                    }
+                } else {
+                    nacc += 1;
+                    imp = M > best;
+                    best = imp ? M : best;
+                    if (wr && H.hv_feat && hvc < H.hv_cap) {
+                        const int64_t at = (int64_t)c * H.hv_cap + hvc;
+                        if (lane == 0) {
+                            H.hv_pair[at * 2] = S.pair[took][0];
+                            H.hv_pair[at * 2 + 1] = S.pair[took][1];
+                        }
+                        if (in) {          // raw features of the order before the move
+                            float *f = H.hv_feat + (at * n + lane) * kF;
+                            f[0] = (float)pos / (float)n;
+                            f[1] = cm;
+                            f[2] = isinf(csec) ? 0.f : (float)((double)cm - (double)csec);
+#pragma unroll
+                            for (int i = 0; i < 5; ++i) f[3 + i] = (float)H.nstat[lane * 5 + i];
+                        }
+                    }
+                    if (hvc < H.hv_cap) hvc += 1;
+                }
+                pos = posn;
+                cl = li;
+                cm = mi;
+                csec = si;
+                cbm = bi;
+                ce = e;
+                csum = esum;
+                if (wr) {
+                    bool traced = adopt && first;
+                    if (!adopt) {
+                        if (lane == 0 && H.flags) H.flags[(int64_t)c * H.iterations + (t - H.t_first) + took] = 1;
+                        if (++since == every) {
+                            since = 0;
+                            ++tslot;
+                            traced = true;
+                            if (lane == 0 && H.trace) H.trace[(int64_t)c * H.trace_len + tslot] = score;
+                        }
+                    }
+                    if (H.n_edges > 0 && traced) {           // the current order's greedy graph
+                        const int ech = lane < H.n_edges ? H.edge_cp[2 * lane] : 0;
+                        const int epa = lane < H.n_edges ? H.edge_cp[2 * lane + 1] : 0;
+                        const uint64_t gch = (uint64_t)__shfl((unsigned long long)cbm, ech, 64);
+                        const uint64_t bits = __ballot(lane < H.n_edges && ((gch >> epa) & 1ull));
+                        if (lane == 0) H.edge_trace[(int64_t)c * H.trace_len + tslot] = (uint32_t)bits;
+                    }
+                    if (imp && in) H.best_graph[row + lane] = cbm;
+                    if (H.topk > 0 && (!adopt || (first && H.t_first == 0))) {
+                        topk_offer(H, c, n, lane, M, in ? cbm : 0ull);
+                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // the next offer reads other lanes' writes
+                    }
+                }
+            }
+        }
+        t += adopt ? 0 : done;
+        adopt = false;
+        if (t >= t1) break;                // uniform over the block
+        // ---- the next round's proposals
+        if (KP > 1) __syncthreads();       // every wavefront has read this round's results
+        const int64_t nt = t + 1 + wave;
+        if (ctl && nt <= t1) {
+            if (nt - tb >= 64) {
+                tb = t + 1;
+                const uint64_t st = (uint64_t)(tb + lane);
+                rng_pair(H.seed, chain, n, st, ra, rb);
+                rlu = log(rng_unit_open(rng_draw(H.seed, chain, 3, st)));
+                if constexpr (LEARNED) {
+                    rmix = rng_unit_open(rng_draw(H.seed, chain, 4, st));
+                    ru5 = rng_unit_open(rng_draw(H.seed, chain, 5, st));
+                    ru6 = rng_unit_open(rng_draw(H.seed, chain, 6, st));
+                }
+            }
+            const int i = (int)(nt - tb);
+            bool uniform = true;
+            if constexpr (LEARNED) uniform = readlane_f64(rmix, i) < H.eps;
+            if (uniform) {
+                const int a = __builtin_amdgcn_readlane(ra, i), b = __builtin_amdgcn_readlane(rb, i);
+                pa = __builtin_ctzll(__ballot(in && pos == a));
+                pb = __builtin_ctzll(__ballot(in && pos == b));
+            } else if constexpr (LEARNED) {
+                // node a ~ p, then node b ~ p without a (inverse CDF in node order, FP64)
+                const double p = ce / csum;
+                pa = lanes_pick(p, readlane_f64(ru5, i), n, lane, n - 1);
+                const double w2 = readlane_f64(ru6, i) * (1.0 - readlane_f64(p, pa));
+                pb = lanes_pick(lane == pa ? 0.0 : p, w2, n, lane, pa == n - 1 ? n - 2 : n - 1);
+            }
+            if constexpr (LEARNED) lq_fwd = lanes_pair_logq(ce, csum, n, pa, pb, H.eps);
+            // the nodes the swap can change
+            const int qa = __builtin_amdgcn_readlane(pos, pa), qb = __builtin_amdgcn_readlane(pos, pb);
+            const int lo = qa < qb ? qa : qb, hi = qa < qb ? qb : qa;
+            const int x = qa < qb ? pa : pb, y = qa < qb ? pb : pa;
+            const float cut = fminf(gap_below(cm), csec);
+            const bool between = in && pos > lo && pos < hi;
+            const int il = in ? lane : 0;
+            const float ix = S.pm[il * pms + x], iy = S.pm[il * pms + y], xi = S.pm[x * pms + il], yi = S.pm[y * pms + il];
+            const bool hit = between && (!(ix < cut) || !(iy < cut));
+            const float cutx = readlane_f32(cut, x), cuty = readlane_f32(cut, y);
+            const uint64_t gx = __ballot((between || lane == y) && !(xi < cutx));
+            const uint64_t gy = __ballot((between || lane == x) && !(yi < cuty));
+            uint64_t na = __ballot(hit);
+            na |= gx ? (1ull << x) : 0ull;
+            na |= gy ? (1ull << y) : 0ull;
+            posn = lane == pa ? qb : (lane == pb ? qa : pos);
+            S.pos[wave][lane] = (uint8_t)posn;
+            if (lane == 0) {
+                S.aff[wave] = na;
+                S.pair[wave][0] = pa;
+                S.pair[wave][1] = pb;
+            }
+        }
+        // (the barrier after the hints' reset publishes the proposals)
+    }
+    if (wave == 0) {
+        if (in) H.cur[row + pos] = lane;
+        if (lane == 0) {
+            H.score[c] = score;
+            H.best_score[c] = best;
+            H.accepted[c] = nacc;
+            if (H.hv_feat) H.hv_count[c] = hvc;
+        }
+    }
+}
+
+// The kept entries' partial (slot 0) of every (chain, window node) pair, whole rows, for sweeps
+// whose streaming pass adds the other entries (score bound off); one wavefront per pair.
+__global__ __launch_bounds__(kScoreThreads) void k_chain_kept(const TabView *__restrict__ tviews,
+                                                              const ChainView *__restrict__ views,
+                                                              const int64_t *__restrict__ node_base, int T, int C)
+{
+    const int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int64_t nodes = node_base[T];
+    if (g >= nodes * C) return;                              // uniform per wavefront
+    const int c = (int)(g / nodes);
+    const int64_t gn = g - (int64_t)c * nodes;
+    const int k = find_segment(node_base, T, gn);
+    const ChainView &H = views[k];
+    const TabView &V = tviews[k];
+    const int node = (int)(gn - node_base[k]);
+    if (!V.kept || !((H.wmask[c] >> node) & 1ull)) return;   // uniform
+    const int n = H.n;
+    const uint8_t *pp = H.ppos + (int64_t)c * n;
+    const int pv = pp[node], pu = pp[lane < n ? lane : n - 1];
+    const uint64_t pred = __ballot(lane < n && pu < pv);
+    const int64_t row = V.klen[2 * n + node];
+    __shared__ KeptAcc s_part[kScoreThreads / 64][kStripes];
+    KeptAcc *part = s_part[threadIdx.x >> 6];
+    const int len = V.klen[node], nq = kept_stripes_of(len);
+    for (int q = 0; q < nq; ++q) {
+        const KeptAcc a = kept_scan<false>(V.kmask + row, V.kscore + row, len, q, ~pred, lane, nullptr);
+        if (lane == 0) part[q] = a;
+    }
+    if (lane == 0) kept_store(V, c, node, kept_combine(part, nq));
+}
+
 }  // namespace bnos
 
 using namespace bnos;
@@ -645,18 +1108,26 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
     const int C = cfg->chains;
     hipStream_t us = reinterpret_cast<hipStream_t>(stream);
     BNOS_HIP(hipSetDevice(tabs[0]->device));
+    // tables with kept rows run their chains in k_chain_run; the others share the launches of an
+    // iteration: entries 0 .. Tk - 1 of the arrays below, and Tk .. T - 1
+    std::vector<int> order;
     for (int k = 0; k < T; ++k)
-        if ((s = ensure_workspace(tabs[k], C)) != BNOS_OK) return s;
+        if (tabs[k]->kept_rows()) order.push_back(k);
+    const int Tk = (int)order.size(), Ts = T - Tk;
+    for (int k = 0; k < T; ++k)
+        if (!tabs[k]->kept_rows()) order.push_back(k);
+    for (int q = Tk; q < T; ++q)
+        if ((s = ensure_workspace(tabs[order[q]], C)) != BNOS_OK) return s;
 
     // per-call workspace: descriptors + per table: per-node caches, proposals,
     // windows, work lists, iteration counters
-    size_t bytes = sizeof(TabView) * T + sizeof(ChainView) * T + 3 * sizeof(int64_t) * (T + 1) + 256;
+    size_t bytes = sizeof(TabView) * T + sizeof(ChainView) * T + 4 * sizeof(int64_t) * (T + 1) + 256;
     const size_t edges_off = bytes;
     bytes += 64 * sizeof(int32_t) + 256;                                        // traced edges
     std::vector<size_t> off(T);
-    for (int k = 0; k < T; ++k) {
-        const size_t n = tabs[k]->n, cn = (size_t)C * n;
-        off[k] = bytes;
+    for (int q = 0; q < T; ++q) {
+        const size_t n = tabs[order[q]]->n, cn = (size_t)C * n;
+        off[q] = bytes;
         bytes += cn * 24 + (size_t)C * 16 + cn * 4 + n * C * 4 + n * 4 + 256;   // caches, windows, lists
         bytes += cn * 8 + cn * 4 + (size_t)C * 8 + (size_t)C * 8 + 256;         // second best, logits, q, pair
         bytes += cn + 256;                                                       // node positions
@@ -671,14 +1142,15 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
     }
     std::vector<TabView> tv(T);
     std::vector<ChainView> cv(T);
-    std::vector<int64_t> blk_base(T + 1, 0), chain_base(T + 1, 0), node_base(T + 1, 0);
-    int64_t max_groups_c = C;
-    for (int k = 0; k < T; ++k) {
+    // prefix bases: the chains of the tables with kept rows; blocks, chains and nodes of the others
+    std::vector<int64_t> run_base(T + 1, 0), blk_base(T + 1, 0), chain_base(T + 1, 0), node_base(T + 1, 0);
+    for (int q = 0; q < T; ++q) {
+        const int k = order[q];
         TableT *t = tabs[k];
         const int n = t->n;
         const size_t cn = (size_t)C * n;
-        char *p = ws + off[k];
-        ChainView &H = cv[k];
+        char *p = ws + off[q];
+        ChainView &H = cv[q];
         H.n = n;
         H.C = C;
         H.target = cfg->target;
@@ -730,7 +1202,7 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         H.top_graph = st.top_graphs;
         H.top_score = st.top_scores;
         H.top_count = st.top_count;
-        TabView &V = tv[k];
+        TabView &V = tv[q];
         V.masks = t->d_masks;
         V.scores = t->d_scores;
         V.S_pad = t->S_pad;
@@ -752,22 +1224,30 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         V.cscore = bound ? t->d_cscore : nullptr;
         V.cuts = H.cuts;               // computed by k_worklist before each scoring launch
         V.K = t->K;
-        V.kmask = nullptr;             // the sweep's blocks stream the whole rows
-        V.kscore = nullptr;
-        V.klen = nullptr;
-        V.kept_stride = 0;
-        V.kept = nullptr;
-        V.slots = V.chunks;
-        V.slot0 = 0;
-        blk_base[k + 1] = blk_base[k] + (int64_t)n * V.chunks;
-        chain_base[k + 1] = chain_base[k] + C;
-        node_base[k + 1] = node_base[k] + n;
+        V.kmask = t->d_kmask;
+        V.kscore = t->d_kscore;
+        V.klen = t->d_klen;
+        V.kpm = t->d_kpm;
+        V.kept = t->d_kmask ? t->d_kept : nullptr;     // the streaming pass leaves out what slot 0 holds
+        V.slot0 = V.kept ? 1 : 0;
+        V.slots = V.chunks + V.slot0;
+        if (q < Tk) {
+            run_base[q + 1] = run_base[q] + C;
+        } else {
+            const int g = q - Tk;
+            blk_base[g + 1] = blk_base[g] + (int64_t)n * V.chunks;
+            chain_base[g + 1] = chain_base[g] + C;
+            node_base[g + 1] = node_base[g] + n;
+        }
     }
     TabView *d_tv = reinterpret_cast<TabView *>(ws);
     ChainView *d_cv = reinterpret_cast<ChainView *>(ws + sizeof(TabView) * T);
     int64_t *d_blk = reinterpret_cast<int64_t *>(ws + sizeof(TabView) * T + sizeof(ChainView) * T);
     int64_t *d_chain = d_blk + (T + 1);
     int64_t *d_node = d_chain + (T + 1);
+    int64_t *d_run = d_node + (T + 1);
+    const TabView *d_tvs = d_tv + Tk;            // the streamed tables
+    const ChainView *d_cvs = d_cv + Tk;
 
     hipStream_t cs = nullptr;
     hipGraph_t graph = nullptr;
@@ -789,36 +1269,59 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
     CK(hipMemcpy(d_blk, blk_base.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice));
     CK(hipMemcpy(d_chain, chain_base.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice));
     CK(hipMemcpy(d_node, node_base.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice));
+    CK(hipMemcpy(d_run, run_base.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice));
     // orders per scoring block: the chain-sweep shape of C's bucket if set (one per launch,
     // from the first table), else the scoring rule for a batch of C orders
     const int tb_bt = tabs[0]->chain_bt[TableT::bucket(C)];
     const int bt = (tb_bt > 0 && tb_bt <= C) ? tb_bt : pick_bt(tabs[0], C);
-    const unsigned groups = (unsigned)((max_groups_c + bt - 1) / bt);
-    const unsigned total_chains = (unsigned)chain_base[T];
-    bool any_bound = false;
-    for (int k = 0; k < T; ++k) any_bound = any_bound || cv[k].cuts != nullptr;
-    // blocks of k_worklist that compute the score-bound cuts after the list blocks
-    const int64_t cut_blocks = any_bound ? (node_base[T] * (int64_t)C + kListThreads / 64 - 1) / (kListThreads / 64) : 0;
-    if ((node_base[T] + cut_blocks) * kListThreads > (int64_t)UINT32_MAX) {
-        set_error("too many (chain, node) pairs for one launch: lower the chains or the tables per call");
-        cleanup();
-        return BNOS_E_RANGE;
+    const unsigned groups = (unsigned)((C + bt - 1) / bt);
+    const unsigned run_chains = (unsigned)run_base[Tk], total_chains = (unsigned)chain_base[Ts];
+    // the size limit holds over all tables, however they are served
+    {
+        int64_t nodes = 0;
+        bool bound = false;
+        for (int q = 0; q < T; ++q) {
+            nodes += cv[q].n;
+            bound = bound || cv[q].cuts != nullptr;
+        }
+        const int64_t cut = bound ? (nodes * C + kListThreads / 64 - 1) / (kListThreads / 64) : 0;
+        if ((nodes + cut) * kListThreads > (int64_t)UINT32_MAX) {
+            set_error("too many (chain, node) pairs for one launch: lower the chains or the tables per call");
+            cleanup();
+            return BNOS_E_RANGE;
+        }
     }
-    hipLaunchKernelGGL(k_chain_init, dim3(total_chains), dim3(64), 0, us, d_cv, d_chain, T);
+    bool any_bound = false, any_kept = false;    // of the streamed tables
+    for (int q = Tk; q < T; ++q) {
+        any_bound = any_bound || cv[q].cuts != nullptr;
+        any_kept = any_kept || tv[q].kept != nullptr;
+    }
+    const int64_t pairs = node_base[Ts] * (int64_t)C;
+    // blocks of k_worklist that compute the score-bound cuts after the list blocks
+    const int64_t cut_blocks = any_bound ? (pairs + kListThreads / 64 - 1) / (kListThreads / 64) : 0;
+    if (Tk > 0) hipLaunchKernelGGL(k_chain_init, dim3(run_chains), dim3(64), 0, us, d_cv, d_run, Tk);
+    if (Ts > 0) hipLaunchKernelGGL(k_chain_init, dim3(total_chains), dim3(64), 0, us, d_cvs, d_chain, Ts);
     CK(hipGetLastError());
     auto one_step = [&](hipStream_t q) -> hipError_t {
-        hipLaunchKernelGGL(k_worklist, dim3((unsigned)(node_base[T] + cut_blocks)), dim3(kListThreads), 0, q, d_tv, d_cv,
-                           d_node, T, C);
-        dim3 grid((unsigned)((blk_base[T] + kXcds - 1) / kXcds * kXcds), groups);   // padded for xcd_block
-        if (bt == 8) hipLaunchKernelGGL(k_score_multi<8>, grid, dim3(kScoreThreads), 0, q, d_tv, d_blk, T);
-        else if (bt == 4) hipLaunchKernelGGL(k_score_multi<4>, grid, dim3(kScoreThreads), 0, q, d_tv, d_blk, T);
-        else if (bt == 2) hipLaunchKernelGGL(k_score_multi<2>, grid, dim3(kScoreThreads), 0, q, d_tv, d_blk, T);
-        else hipLaunchKernelGGL(k_score_multi<1>, grid, dim3(kScoreThreads), 0, q, d_tv, d_blk, T);
-        hipLaunchKernelGGL(k_chain_step, dim3(total_chains), dim3(kStepWaves * 64), 0, q, d_tv, d_cv, d_chain, T);
+        hipLaunchKernelGGL(k_worklist, dim3((unsigned)(node_base[Ts] + cut_blocks)), dim3(kListThreads), 0, q, d_tvs,
+                           d_cvs, d_node, Ts, C);
+        dim3 grid((unsigned)((blk_base[Ts] + kXcds - 1) / kXcds * kXcds), groups);   // padded for xcd_block
+        if (any_kept) {                          // score bound off: slot 0, then every entry not in it
+            hipLaunchKernelGGL(k_chain_kept, dim3((unsigned)((pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64))),
+                               dim3(kScoreThreads), 0, q, d_tvs, d_cvs, d_node, Ts, C);
+            if (bt == 8) hipLaunchKernelGGL((k_score_multi<8, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+            else if (bt == 4) hipLaunchKernelGGL((k_score_multi<4, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+            else if (bt == 2) hipLaunchKernelGGL((k_score_multi<2, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+            else hipLaunchKernelGGL((k_score_multi<1, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+        } else if (bt == 8) hipLaunchKernelGGL(k_score_multi<8>, grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+        else if (bt == 4) hipLaunchKernelGGL(k_score_multi<4>, grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+        else if (bt == 2) hipLaunchKernelGGL(k_score_multi<2>, grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+        else hipLaunchKernelGGL(k_score_multi<1>, grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
+        hipLaunchKernelGGL(k_chain_step, dim3(total_chains), dim3(kStepWaves * 64), 0, q, d_tvs, d_cvs, d_chain, Ts);
         return hipGetLastError();
     };
     const int64_t sweep = cfg->sweep_len > 0 ? cfg->sweep_len : 32;
-    const int64_t graphs = steps / sweep;
+    const int64_t graphs = Ts > 0 ? steps / sweep : 0;
     const int64_t rest = steps - graphs * sweep;
     if (graphs > 0) {
         CK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
@@ -841,8 +1344,24 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         CK(hipEventCreate(&ev1));
         CK(hipEventRecord(ev0, us));
     }
+    for (int64_t t0 = cfg->first_iteration, last = t0 + cfg->iterations; Tk > 0;) {
+        const int64_t t1 = last - t0 < kRunIters ? last : t0 + kRunIters;
+        // 16 wavefronts per chain while every compute unit has one chain or two; with more chains 8,
+        // so that more of them are resident (1,024 chains of 60 nodes: 20.6 us per iteration against 31)
+        const dim3 grid(run_chains), block((run_chains <= 512 ? 16 : 8) * 64);
+        if (cfg->proposal == 1 && run_chains <= 512)
+            hipLaunchKernelGGL((k_chain_run<1, true, 16>), grid, block, 0, us, d_tv, d_cv, d_run, Tk, t0, t1);
+        else if (cfg->proposal == 1)
+            hipLaunchKernelGGL((k_chain_run<1, true, 8>), grid, block, 0, us, d_tv, d_cv, d_run, Tk, t0, t1);
+        else if (run_chains <= 512)
+            hipLaunchKernelGGL((k_chain_run<2, false, 16>), grid, block, 0, us, d_tv, d_cv, d_run, Tk, t0, t1);
+        else
+            hipLaunchKernelGGL((k_chain_run<2, false, 8>), grid, block, 0, us, d_tv, d_cv, d_run, Tk, t0, t1);
+        CK(hipGetLastError());
+        if ((t0 = t1) >= last) break;
+    }
     for (int64_t g = 0; g < graphs; ++g) CK(hipGraphLaunch(exec, us));
-    for (int64_t q = 0; q < rest; ++q) CK(one_step(us));
+    for (int64_t q = 0; Ts > 0 && q < rest; ++q) CK(one_step(us));
     if (replay_ms) CK(hipEventRecord(ev1, us));
     CK(hipStreamSynchronize(us));
     if (replay_ms) CK(hipEventElapsedTime(replay_ms, ev0, ev1));
@@ -939,11 +1458,15 @@ extern "C" bnos_status bnos_chains_autotune(bnos_table h, const bnos_chain_cfg *
     const int old_cs = t->chain_cs[bk], old_bt = t->chain_bt[bk];
     double best_ms = 1e300;
     int best_cs = 0, best_bt = 0;
-    for (int cs = 1; cs <= t->pad_steps && s == BNOS_OK; cs <<= 1) {
-        for (int bt = 1; bt <= 8 && bt <= C && s == BNOS_OK; bt <<= 1) {
+    // chains on kept rows have one launch whatever the shape: time it once, as it is set
+    const bool kept = t->kept_rows();
+    const int cs0 = kept ? t->chain_chunk_entries_for(C) / kEntriesPerStep : 1;
+    const int bt0 = !kept ? 1 : ((old_bt > 0 && old_bt <= C) ? old_bt : pick_bt(t, C));
+    for (int cs = cs0; cs <= (kept ? cs0 : t->pad_steps) && s == BNOS_OK; cs <<= 1) {
+        for (int bt = bt0; bt <= (kept ? bt0 : 8) && bt <= C && s == BNOS_OK; bt <<= 1) {
             t->chain_cs[bk] = cs;
             t->chain_bt[bk] = bt;
-            if ((s = ensure_workspace(t, C)) != BNOS_OK) break;
+            if (!kept && (s = ensure_workspace(t, C)) != BNOS_OK) break;
             double tot = 0.0;
             for (int r = 0; r <= reps && s == BNOS_OK; ++r) {
                 if (resume) {
@@ -979,7 +1502,7 @@ extern "C" bnos_status bnos_chains_autotune(bnos_table h, const bnos_chain_cfg *
     }
     t->chain_cs[bk] = best_cs;
     t->chain_bt[bk] = best_bt;
-    if ((s = ensure_workspace(t, C)) != BNOS_OK) return s;
+    if (!kept && (s = ensure_workspace(t, C)) != BNOS_OK) return s;
     if (chunk_steps) *chunk_steps = best_cs;
     if (orders_per_block) *orders_per_block = best_bt;
     if (ms_per_iteration) *ms_per_iteration = best_ms;

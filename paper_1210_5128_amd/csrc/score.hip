@@ -71,11 +71,14 @@ __global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
     __shared__ int s_valid;
     __shared__ float s_m[64], s_s[64], s_sec[64];
     __shared__ uint64_t s_bm[64];
+    __shared__ KeptAcc s_part[kKeptWaves][kStripes];
+    __shared__ int s_hint[kKeptWaves];
     const int b = blockIdx.x;
     const int n = A.n;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int by_len = lane < n ? A.klen[n + lane] : 0, lens = lane < n ? A.klen[lane] : 0;
+    const int offs = lane < n ? A.klen[2 * n + lane] : 0;
     if (wave == 0) order_positions(A.orders + (int64_t)b * n, n, lane, s_pos, &s_valid);
     __syncthreads();
     const int pos = s_pos[lane];
@@ -83,13 +86,19 @@ __global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
         const int node = __builtin_amdgcn_readlane(by_len, k), len = __builtin_amdgcn_readlane(lens, node);
         const int mine = __builtin_amdgcn_readlane(pos, node);
         const uint64_t pred = __ballot(lane < n && pos < mine);
-        const int64_t row = (int64_t)node * A.kept_stride;
-        const KeptAcc a = kept_scan<true>(A.kmask + row, A.kscore + row, len, ~pred, lane);
+        const int64_t row = __builtin_amdgcn_readlane(offs, node);
+        const int nq = kept_stripes_of(len);
+        if (lane == 0) s_hint[wave] = ordered_f32(-INFINITY);
+        for (int q = 0; q < nq; ++q) {
+            const KeptAcc a = kept_scan<true>(A.kmask + row, A.kscore + row, len, q, ~pred, lane, &s_hint[wave]);
+            if (lane == 0) s_part[wave][q] = a;
+        }
         if (lane == 0) {
-            s_m[node] = a.best;
-            s_s[node] = kept_sum(a);
-            s_sec[node] = a.sec;
-            s_bm[node] = a.bm;
+            const Acc r = kept_combine(s_part[wave], nq);
+            s_m[node] = r.m;
+            s_s[node] = r.s;
+            s_sec[node] = r.sec;
+            s_bm[node] = r.bm;
         }
     }
     __syncthreads();
@@ -104,7 +113,7 @@ __global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
         if (A.node_lse) A.node_lse[o] = valid ? li : NAN;
         if (A.node_second) A.node_second[o] = valid ? s_sec[lane] : NAN;
     }
-    const double l = wave_sum_f64(li, lane), m = wave_sum_f64(mi, lane);
+    const double l = wave_sum_f64(li), m = wave_sum_f64(mi);
     if (lane == 0) {
         A.lse[b] = valid ? l : NAN;
         A.maxs[b] = valid ? m : NAN;
@@ -120,25 +129,27 @@ __global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
 template <int W, bool STOP>
 __global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
 {
-    __shared__ KeptLds<W> L;
+    __shared__ KeptAcc s_part[kStripes];
+    __shared__ int s_hint;
     const int64_t g = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = A.n;
     const int k = (int)(g / A.B), b = (int)(g - (int64_t)k * A.B);
     const int node = A.klen[n + k];
-    if (threadIdx.x == 0) kept_shared_reset(L);
+    const int len = A.klen[node];
+    if (threadIdx.x == 0) s_hint = ordered_f32(-INFINITY);
     bool valid;
     const uint64_t np = ~wave_pred(A.orders + (int64_t)b * n, n, node, lane, valid);
-    const int64_t row = (int64_t)node * A.kept_stride;
-    KeptAcc a;
-    if (W == 1) {
-        a = kept_scan<STOP>(A.kmask + row, A.kscore + row, A.klen[node], np, lane);
-    } else {
-        __syncthreads();
-        a = kept_scan_shared<W, STOP>(A.kmask + row, A.kscore + row, A.klen[node], np, lane, wave, L);
+    if (W > 1) __syncthreads();
+    const int64_t row = A.klen[2 * n + node];
+    const int nq = kept_stripes_of(len);
+    for (int q = wave; q < nq; q += W) {
+        const KeptAcc a = kept_scan<STOP>(A.kmask + row, A.kscore + row, len, q, np, lane, &s_hint);
+        if (lane == 0) s_part[q] = a;
     }
-    if (threadIdx.x == 0) kept_store(view_of(A), b, node, a);
+    if (W > 1) __syncthreads();
+    if (threadIdx.x == 0) kept_store(view_of(A), b, node, kept_combine(s_part, nq));
 }
 
 // Measurement only: the 64-entry tiles of the kept rows k_score_kept (stop) or
@@ -152,9 +163,13 @@ __global__ __launch_bounds__(kScoreThreads) void k_count_kept(ScoreArgs A, int s
     const int b = (int)(g / n), node = (int)(g - (int64_t)b * n);
     bool valid;
     const uint64_t np = ~wave_pred(A.orders + (int64_t)b * n, n, node, lane, valid);
-    const int64_t row = (int64_t)node * A.kept_stride;
-    int steps = (A.klen[node] + 64 * kKeptTiles - 1) / (64 * kKeptTiles);
-    if (stop) kept_scan<true>(A.kmask + row, A.kscore + row, A.klen[node], np, lane, &steps);
+    const int64_t row = A.klen[2 * n + node];
+    __shared__ int s_hint[kScoreThreads / 64];
+    int *hint = &s_hint[threadIdx.x >> 6];
+    if (lane == 0) *hint = ordered_f32(-INFINITY);
+    int steps = stop ? 0 : kept_steps_of(A.klen[node]);
+    for (int q = 0; stop && q < kept_stripes_of(A.klen[node]); ++q)
+        kept_scan<true>(A.kmask + row, A.kscore + row, A.klen[node], q, np, lane, hint, &steps);
     if (lane == 0) counts[g] = (unsigned)(steps * kKeptTiles);
 }
 
@@ -387,7 +402,7 @@ ScoreArgs score_args(const TableT *t, const int32_t *orders, int B, double *lse,
     A.kmask = t->d_kmask;
     A.kscore = t->d_kscore;
     A.klen = t->d_klen;
-    A.kept_stride = t->kept_stride;
+    A.kpm = t->d_kpm;
     A.kept = t->d_kmask ? t->d_kept : nullptr;
     A.slot0 = A.kept ? 1 : 0;
     A.slots = A.chunks + A.slot0;
@@ -506,9 +521,9 @@ bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timin
     if (allow_timing && t->timing && t->timing_seen++ % t->timing_every == 0) {
         if ((s = next_events(t, e0, e1, A.B)) != BNOS_OK) return s;
     }
-    if (t->kept_steps <= kKeptWaves * 4) {
-        // short rows: four steps per wavefront of one block take less than a second launch would
-        // (8-20 nodes, one step per row: 7.4 us per call against 9.8 at up to 256 orders)
+    if (t->kept_steps <= kKeptWaves * 8 && t->kept_steps_max <= 4) {
+        // short rows: a few steps per wavefront of one block take less than a second launch would
+        // (8-20 nodes, up to 214 entries per row: 7.4 us per call against 9.8 at up to 256 orders)
         const dim3 grid((unsigned)A.B), block(64 * (unsigned)(t->n < kKeptWaves ? t->n : kKeptWaves));
         if (e0) hipExtLaunchKernelGGL(k_score_kept, grid, block, 0, st, e0, e1, 0, A);
         else hipLaunchKernelGGL(k_score_kept, grid, block, 0, st, A);
@@ -516,10 +531,10 @@ bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timin
         return BNOS_OK;
     }
     // W wavefronts per (order, node): a longest row of M steps takes M / W of them one after the
-    // other (0.33 us each), and every wavefront of a pair costs the chip 0.7 ns, so with P pairs
-    // W^2 = 470 M / P is the least of the sum; the power of two nearest.  (60 nodes, M = 25: one
+    // other (0.17 us each), and every wavefront of a pair costs the chip 0.7 ns, so with P pairs
+    // W^2 = 235 M / P is the least of the sum; the power of two nearest.  (60 nodes, M = 50: one
     // order 12.6 / 11.6 / 10.4 / 10.7 us for W = 1 / 2 / 4 / 8, 64 orders 19.7 / 20.7 / 24.8 / 36.8.)
-    const double w2 = 470.0 * t->kept_steps_max / ((double)A.B * t->n);
+    const double w2 = 235.0 * t->kept_steps_max / ((double)A.B * t->n);
     A.slots = 1;
     if (w2 < 2.0) launch_partials<1>(A, st, e0, e1);
     else if (w2 < 8.0) launch_partials<2>(A, st, e0, e1);

@@ -316,15 +316,29 @@ __device__ __forceinline__ Acc acc_wave_reduce_scatter(Acc (&a)[BT], int lane)
     return r;
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v, int lane)
+// Sum over the wavefront, the same for every lane, associated as a butterfly over lanes
+// 1, 2, 4, ... 32 apart: within rows of 16 by DPP (once 4 or 8 neighbours hold the same value,
+// mirroring the half row or row pairs the lanes as the butterfly does), then the rows' sums.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
 {
-    // fixed butterfly: the lower lane's value is the left operand
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        double o = __shfl_xor(v, off, 64);
-        v = (lane & off) ? (o + v) : (v + o);
-    }
-    return v;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, ((uint64_t)dpp_u32<CTRL>((uint32_t)(u >> 32), 0u) << 32) |
+                                          dpp_u32<CTRL>((uint32_t)u, 0u));
+}
+__device__ __forceinline__ double readlane_f64(double v, int l)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l));
+}
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    v = v + dpp_f64<0xb1>(v);       // quad_perm: lane ^ 1
+    v = v + dpp_f64<0x4e>(v);       // lane ^ 2
+    v = v + dpp_f64<0x141>(v);      // row_half_mirror
+    v = v + dpp_f64<0x140>(v);      // row_mirror
+    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
 // Predecessor mask of `node` in an order, computed by one wavefront (lane p
@@ -392,11 +406,11 @@ struct ScoreArgs {
     const float *cuts;         // [B][n] each order's cut per node, computed before the launch, or null
     float *cut_ws;             // [B][n] workspace for those cuts (several-order launches)
     int K;
-    // kept entries (see kKeptCap), or null
-    const uint64_t *kmask;     // [n][kept_stride]
+    // kept entries (see kKeptMean), or null
+    const uint64_t *kmask;
     const float *kscore;
-    const int32_t *klen;       // [n] entries, [n] nodes by descending entries
-    int64_t kept_stride;
+    const int32_t *klen;       // [n] entries, [n] nodes by descending entries, [n] first entries
+    const float *kpm;          // [n][n]
     const uint8_t *kept;       // [n * S_pad / 4] the streaming pass leaves these entries out, or null
     int slots, slot0;          // partials per (order, node); the streaming pass's chunk c writes slot0 + c
 };
@@ -423,10 +437,10 @@ struct TabView {
     const float *cuts;          // [orders][n] each order's (chain's) cut per node, computed by an
                                 // earlier launch, or null (the block computes it)
     int K;
-    const uint64_t *kmask;      // [n][kept_stride] kept entries (see kKeptCap), or null
+    const uint64_t *kmask;      // kept entries (see kKeptMean), or null
     const float *kscore;
-    const int32_t *klen;
-    int64_t kept_stride;
+    const int32_t *klen;        // [n] entries, [n] nodes by descending entries, [n] first entries
+    const float *kpm;           // [n][n] largest kept score of row i among the sets holding node m
     const uint8_t *kept;        // [n * S_pad / 4] entries the streaming pass leaves out, or null
     int slots, slot0;           // part is [B][slots][n]; chunk c writes slot slot0 + c
 };
@@ -779,7 +793,8 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
     u64x2 r01[D], r23[D];
     f32x4 rsc[D];
     uint32_t rneed[D], rkept[D];
-    const uint8_t *kp = EXC ? V.kept + (row >> 2) : nullptr;
+    const bool exc = EXC && V.kept != nullptr;           // uniform (one table of the launch may have none)
+    const uint8_t *kp = exc ? V.kept + (row >> 2) : nullptr;
 #define BNOS_ISSUE(d, kk)                                                                       \
     if ((kk) < nt) {                                                                            \
         const uint32_t q_ = ((uint32_t)s_tile[wave][(kk)] << 6) | (uint32_t)lane;              \
@@ -795,7 +810,7 @@ __device__ __forceinline__ void score_block(const TabView &V, int node, int chun
                 r23[d] = __builtin_nontemporal_load(&mp[2 * q_ + 1]);                           \
             }                                                                                   \
             rsc[d] = __builtin_nontemporal_load(&sp[q_]);                                       \
-            if (EXC) rkept[d] = kp[q_];                                                         \
+            if (exc) rkept[d] = kp[q_];                                                         \
         }                                                                                       \
     }
 #pragma unroll
@@ -928,7 +943,7 @@ __device__ __forceinline__ TabView view_of(const ScoreArgs &A)
     V.kmask = A.kmask;
     V.kscore = A.kscore;
     V.klen = A.klen;
-    V.kept_stride = A.kept_stride;
+    V.kpm = A.kpm;
     V.kept = A.kept;
     V.slots = A.slots;
     V.slot0 = A.slot0;
@@ -1073,33 +1088,57 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_multi(const TabView *__
 
 // ------------------------------------------------------------------ kept entries
 //
-// One wavefront reduces one node's kept row for one order, 64 entries a step
-// from the best score down.  The first usable entry is the best (equal scores
-// are listed in ascending mask order, so the tie rule holds), the next one the
-// second best, and once both are known the scan ends at the first step whose
-// first score lies kBoundGap nats below the best: a wavefront needs no per-lane
-// top-2 states, no tile summaries and no candidates, and reads only the part of
-// the row that matters.
+// A kept row is scanned from the best score down.  The first usable entry is the
+// best (equal scores are listed in ascending mask order, so the tie rule holds),
+// the next one the second best, and once both are known the scan ends at the
+// first step whose first score lies kBoundGap nats below the best: a wavefront
+// needs no per-lane top-2 states, no tile summaries and no candidates, and
+// reads only the part of the row that matters.
 //
-// The sum of exp(x - best) does not depend on which lane, wavefront or launch
-// adds which entry: each FP32 term, at most 1, is rounded to a multiple of
-// 2^-47 and added as a 64-bit integer (a row lists at most 2^16 of them).  A term
-// below e^-kBoundGap rounds to zero, which is why the scan may stop there and
-// why the left-out entries of the row change no bit.  (The rounding moves a sum
-// by at most 2^-48 per term; FP32, in which the partials hold it, resolves 2^-24.)
-// The rounding is that of an FP64 addition to 48 = 1.5 * 2^5, whose ulp is 2^-47:
-// the integers are the bits of the results less those of 48.
+// So that several wavefronts can share a long row, it is dealt out in parts of
+// kPartSteps steps to kStripes stripes (part p to stripe p mod kStripes), each
+// scanned like a row of its own; a row of one part has one stripe.  A stripe's
+// result does not depend on which lane or wavefront adds which entry: each term
+// exp(x - stripe's best), in FP32 and at most 1, is rounded to a multiple of
+// 2^-47 and added as a 64-bit integer (a row of at most kKeptCap entries deals a
+// stripe 2^16 of them).
+// kept_combine adds the stripes in order in FP64.  Every launch shape and every
+// path so gives the same bits.  A term below e^-kBoundGap of the row's best is
+// lost in the rounding of that sum, which is why a scan may stop there and why
+// the left-out entries of the row change no bit.  (The integers move a stripe's
+// sum by at most 2^-48 per term; FP32, in which the partials hold it, resolves
+// 2^-24.)  The rounding is that of an FP64 addition to 48 = 1.5 * 2^5, whose ulp is
+// 2^-47: the integers are the bits of the results less those of 48.
+constexpr int kStepEntries = kKeptTiles * 64;
+constexpr int kPartSteps = 8;
+constexpr int kStripes = 8;
+
 struct KeptAcc {
     float best, sec;
     uint64_t bm;
     uint64_t s;      // sum of the rounded terms in units of 2^-47
 };
 
-__device__ __forceinline__ float kept_sum(const KeptAcc &a) { return (float)((double)a.s * 0x1p-47); }
+// Sum of a 64-bit integer over the wavefront, uniform.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v)
+{
+    return ((uint64_t)dpp_u32<CTRL>((uint32_t)(v >> 32), 0u) << 32) | dpp_u32<CTRL>((uint32_t)v, 0u);
+}
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
+{
+    v += dpp_u64<0xb1>(v);
+    v += dpp_u64<0x4e>(v);
+    v += dpp_u64<0x114>(v);
+    v += dpp_u64<0x118>(v);
+    v += dpp_u64<0x142>(v);
+    v += dpp_u64<0x143>(v);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+}
 
-// A step takes kKeptTiles * 64 entries (rows are padded to whole steps), and the next
-// step's loads are issued, whether it will be needed or not, before the current one is
-// folded: a step folds in a few hundred cycles, about what a load from L2 takes.
+// A step's loads are issued, whether it will be needed or not, before the step in front of
+// it is folded: a step folds in a few hundred cycles, about what a load from L2 takes.
 // (Loads inside conditions, one 64-entry tile at a time, made the compiler wait for every
 // load where the paths met: 0.7 us per tile.)
 struct KeptStep {
@@ -1107,20 +1146,13 @@ struct KeptStep {
     float x[kKeptTiles];
 };
 
-struct KeptScan {
-    KeptAcc a;
-    float stop;      // the gap's lower end once both results are known
-    int found;
-};
-
 __device__ __forceinline__ void kept_load(KeptStep &s, const uint64_t *__restrict__ km, const float *__restrict__ ks,
                                           int step, int lane)
 {
     // the step's uniform base stays in scalar registers (opaque, so that no vector address, whose
     // registers would have to wait for earlier loads, is formed from it)
-    step = __builtin_amdgcn_readfirstlane(step);
-    uint64_t bm = reinterpret_cast<uint64_t>(km + step * (kKeptTiles * 64));
-    uint64_t bx = reinterpret_cast<uint64_t>(ks + step * (kKeptTiles * 64));
+    uint64_t bm = uniform_u64(reinterpret_cast<uint64_t>(km + step * kStepEntries));
+    uint64_t bx = uniform_u64(reinterpret_cast<uint64_t>(ks + step * kStepEntries));
     asm("" : "+s"(bm), "+s"(bx));
     const auto *pm = reinterpret_cast<const __attribute__((address_space(1))) uint64_t *>(bm);
     const auto *px = reinterpret_cast<const __attribute__((address_space(1))) float *>(bx);
@@ -1132,9 +1164,36 @@ __device__ __forceinline__ void kept_load(KeptStep &s, const uint64_t *__restric
     __builtin_amdgcn_sched_barrier(0);       // the loads go out before the other step is waited for
 }
 
-// Takes the best and second best from a step while they are missing; false when the step holds no
-// usable entry.
-__device__ __forceinline__ bool kept_top(KeptScan &S, const KeptStep &s, uint64_t np)
+// Steps of a row, its stripes, and the steps of stripe q and where they sit.
+__device__ __forceinline__ int kept_steps_of(int len) { return (len + kStepEntries - 1) / kStepEntries; }
+__device__ __forceinline__ int kept_stripes_of(int len)
+{
+    const int parts = (len + kPartSteps * kStepEntries - 1) / (kPartSteps * kStepEntries);
+    return parts < kStripes ? parts : kStripes;
+}
+__device__ __forceinline__ int stripe_steps(int ns, int q)
+{
+    const int whole = ns / (kPartSteps * kStripes), rest = ns - whole * (kPartSteps * kStripes) - q * kPartSteps;
+    return whole * kPartSteps + (rest < 0 ? 0 : (rest > kPartSteps ? kPartSteps : rest));
+}
+__device__ __forceinline__ int stripe_step(int i, int q)
+{
+    return ((i / kPartSteps) * kStripes + q) * kPartSteps + i % kPartSteps;
+}
+
+struct KeptScan {
+    KeptAcc a;
+    float stop;      // the gap's lower end once both results are known
+    int found;
+};
+
+__device__ __forceinline__ float readlane_f32(float x, int l)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+}
+
+// Folds one step.
+__device__ __forceinline__ void kept_fold(KeptScan &S, const KeptStep &s, uint64_t np)
 {
     uint64_t bal[kKeptTiles], any = 0ull;
 #pragma unroll
@@ -1142,92 +1201,47 @@ __device__ __forceinline__ bool kept_top(KeptScan &S, const KeptStep &s, uint64_
         bal[d] = __ballot((s.m[d] & np) == 0ull);
         any |= bal[d];
     }
-    if (any == 0ull) return false;                           // uniform
+    if (any == 0ull) return;                                 // uniform
     if (S.found < 2) {                                       // uniform
+        // the first tile that holds a usable entry (its ballot, scores and masks, selected without
+        // branches: every condition is scalar), and the first one after it
+        uint64_t b = bal[kKeptTiles - 1], later = 0ull, m = s.m[kKeptTiles - 1];
+        float x = s.x[kKeptTiles - 1], xl = 0.f;
 #pragma unroll
-        for (int d = 0; d < kKeptTiles; ++d) {
-            uint64_t b = bal[d];
-            if (b != 0ull && S.found == 0) {
-                const int l = __builtin_ctzll(b);
-                S.a.best = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s.x[d]), l));
-                S.a.bm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(s.m[d] >> 32), l) << 32) |
-                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)s.m[d], l);
-                b &= b - 1;
-                S.found = 1;
-            }
-            if (b != 0ull && S.found == 1) {
-                const int l = __builtin_ctzll(b);
-                S.a.sec = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s.x[d]), l));
-                S.found = 2;
-                S.stop = fminf(gap_below(S.a.best), S.a.sec);
-            }
+        for (int d = kKeptTiles - 2; d >= 0; --d) {
+            const bool has = bal[d] != 0ull;
+            later = has ? (b != 0ull ? b : later) : later;
+            xl = has ? x : xl;
+            b = has ? bal[d] : b;
+            m = has ? s.m[d] : m;
+            x = has ? s.x[d] : x;
         }
+        const int l = __builtin_ctzll(b);
+        const float v = readlane_f32(x, l);
+        const uint64_t b2 = b & (b - 1);
+        const float next = readlane_f32(b2 != 0ull ? x : xl, __builtin_ctzll((b2 != 0ull ? b2 : later) | (1ull << 63)));
+        const bool more = (b2 | later) != 0ull;              // the step holds a second usable entry
+        if (S.found == 0) {
+            S.a.best = v;
+            S.a.bm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), l) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, l);
+            S.a.sec = more ? next : -INFINITY;
+            S.found = more ? 2 : 1;
+        } else {
+            S.a.sec = v;
+            S.found = 2;
+        }
+        if (S.found == 2) S.stop = fminf(gap_below(S.a.best), S.a.sec);
     }
-    return true;
-}
-
-// Folds one step; false when STOP and the row's rest lies below the gap (nothing of this step is
-// folded then).
-template <bool STOP>
-__device__ __forceinline__ bool kept_fold(KeptScan &S, const KeptStep &s, uint64_t np)
-{
-    const float x0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, s.x[0])));
-    if (STOP && x0 < S.stop) return false;                   // uniform; never before both results are known
-    if (!kept_top(S, s, np)) return true;
-    uint64_t acc = 0ull - kKeptTiles * __builtin_bit_cast(uint64_t, 48.0);
 #pragma unroll
     for (int d = 0; d < kKeptTiles; ++d) {
+        if (bal[d] != 0ull) {                                // uniform
 #pragma clang fp contract(off)
-        const float e = ((s.m[d] & np) == 0ull) ? __builtin_amdgcn_exp2f((s.x[d] - S.a.best) * kLog2e) : 0.f;
-        acc += __builtin_bit_cast(uint64_t, (double)e + 48.0);
+            const float e = ((s.m[d] & np) == 0ull) ? __builtin_amdgcn_exp2f((s.x[d] - S.a.best) * kLog2e) : 0.f;
+            S.a.s += __builtin_bit_cast(uint64_t, (double)e + 48.0) - __builtin_bit_cast(uint64_t, 48.0);
+        }
     }
-    S.a.s += acc;
-    return true;
 }
-
-// np: complement of the predecessor set; STOP: end at the gap (else the whole row).
-// `steps` (may be null) receives the steps folded.
-template <bool STOP>
-__device__ __forceinline__ KeptAcc kept_scan(const uint64_t *__restrict__ km, const float *__restrict__ ks, int len,
-                                             uint64_t np, int lane, int *steps = nullptr)
-{
-    KeptScan S;
-    S.a.best = -INFINITY;
-    S.a.sec = -INFINITY;
-    S.a.bm = ~0ull;
-    S.a.s = 0ull;
-    S.stop = -INFINITY;
-    S.found = 0;
-    const int ns = (len + kKeptTiles * 64 - 1) / (kKeptTiles * 64);      // >= 1: the empty set is kept
-    KeptStep A, B;
-    kept_load(A, km, ks, 0, lane);
-    int t = 0;
-    for (;;) {
-        kept_load(B, km, ks, t + 1 < ns ? t + 1 : t, lane);
-        if (!kept_fold<STOP>(S, A, np)) break;               // uniform
-        if (++t >= ns) break;
-        kept_load(A, km, ks, t + 1 < ns ? t + 1 : t, lane);
-        if (!kept_fold<STOP>(S, B, np)) break;
-        if (++t >= ns) break;
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) S.a.s += (uint64_t)__shfl_xor((unsigned long long)S.a.s, off, 64);
-    if (steps) *steps = t;
-    return S.a;
-}
-
-// The same scan shared by W wavefronts, wavefront w taking the steps w, w + W, ...: first each
-// finds its own top two usable entries (or learns that its next steps hold neither of the row's
-// top two), then, with the row's best known, each sums its steps down to the gap.  The result is
-// that of kept_scan, bit for bit: the top two come from the same entries and the sum is of
-// integers.  Every wavefront of the block calls it (it holds two barriers); the result is
-// valid in all of them.
-template <int W>
-struct KeptLds {
-    float best[W], sec[W];
-    uint64_t bm[W], s[W];
-    int second;                    // FP32 bits, ordered: the largest second best any wavefront holds
-};
 
 __device__ __forceinline__ int ordered_f32(float x)
 {
@@ -1235,15 +1249,14 @@ __device__ __forceinline__ int ordered_f32(float x)
     return b >= 0 ? b : b ^ 0x7fffffff;
 }
 
-// Must be called, and a barrier passed, before the block's first kept_scan_shared and between two.
-template <int W>
-__device__ __forceinline__ void kept_shared_reset(KeptLds<W> &L) { L.second = ordered_f32(-INFINITY); }
-
-template <int W, bool STOP>
-__device__ __forceinline__ KeptAcc kept_scan_shared(const uint64_t *__restrict__ km, const float *__restrict__ ks,
-                                                    int len, uint64_t np, int lane, int wave, KeptLds<W> &L)
+// Scan of stripe q of a row of `len` entries for the predecessor complement np.  STOP: end at the
+// gap (else the whole stripe); then *hint (LDS, ordered_f32 of -inf at first) holds the highest
+// gap end that any stripe of the row has found, and no entry below it is scanned for.  `steps`
+// (may be null) is raised by the steps folded.
+template <bool STOP>
+__device__ __forceinline__ KeptAcc kept_scan(const uint64_t *__restrict__ km, const float *__restrict__ ks, int len,
+                                             int q, uint64_t np, int lane, int *hint, int *steps = nullptr)
 {
-    const int ns = (len + kKeptTiles * 64 - 1) / (kKeptTiles * 64);
     KeptScan S;
     S.a.best = -INFINITY;
     S.a.sec = -INFINITY;
@@ -1251,81 +1264,68 @@ __device__ __forceinline__ KeptAcc kept_scan_shared(const uint64_t *__restrict__
     S.a.s = 0ull;
     S.stop = -INFINITY;
     S.found = 0;
-    bool early = false;            // the first usable entry sits alone in a step already passed
-    int t = wave;
-    KeptStep D;
-    kept_load(D, km, ks, t < ns ? t : ns - 1, lane);
-    while (t < ns) {                                         // uniform
-        const float x0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, D.x[0])));
-        if (ordered_f32(x0) < __builtin_amdgcn_readfirstlane(*(volatile int *)&L.second)) break;
-        KeptStep N;
-        kept_load(N, km, ks, t + W < ns ? t + W : t, lane);
-        const bool had = S.found != 0;
-        kept_top(S, D, np);
-        if (S.found == 2) {
-            early = had;
-            if (lane == 0) atomicMax(&L.second, ordered_f32(S.a.sec));
-            break;
-        }
-        D = N;
-        t += W;
+    const int ns = stripe_steps(kept_steps_of(len), q);      // >= 1
+    const bool shared = STOP && len > kPartSteps * kStepEntries;          // more stripes than this one
+    auto over = [&](const KeptStep &s) -> bool {             // uniform
+        if (!STOP) return false;
+        const float x0 = readlane_f32(s.x[0], 0);
+        return x0 < S.stop || (shared && ordered_f32(x0) < __builtin_amdgcn_readfirstlane(*(volatile int *)hint));
+    };
+    KeptStep A, B;
+    kept_load(A, km, ks, stripe_step(0, q), lane);
+    int t = 0;
+    for (;;) {
+        kept_load(B, km, ks, stripe_step(t + 1 < ns ? t + 1 : t, q), lane);
+        if (over(A)) break;
+        kept_fold(S, A, np);
+        if (++t >= ns) break;
+        kept_load(A, km, ks, stripe_step(t + 1 < ns ? t + 1 : t, q), lane);
+        if (over(B)) break;
+        kept_fold(S, B, np);
+        if (++t >= ns) break;
     }
-    if (S.found == 1) early = true;
-    if (lane == 0) {
-        L.best[wave] = S.a.best;
-        L.sec[wave] = S.a.sec;
-        L.bm[wave] = S.a.bm;
-    }
-    __syncthreads();
-    const float mine = S.a.best;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const float b = L.best[w], c = L.sec[w];
-        const uint64_t m = L.bm[w];
-        if (w == 0) {
-            S.a.best = b;
-            S.a.sec = c;
-            S.a.bm = m;
-            continue;
-        }
-        const bool take = b > S.a.best || (b == S.a.best && m < S.a.bm);
-        S.a.sec = take ? fmaxf(S.a.best, c) : fmaxf(S.a.sec, b);
-        S.a.best = take ? b : S.a.best;
-        S.a.bm = take ? m : S.a.bm;
-    }
-    S.found = 2;
-    S.stop = S.a.sec == -INFINITY ? -INFINITY : fminf(gap_below(S.a.best), S.a.sec);
-    if (early) {
-#pragma clang fp contract(off)
-        const float e = __builtin_amdgcn_exp2f((mine - S.a.best) * kLog2e);
-        const uint64_t u = __builtin_bit_cast(uint64_t, (double)e + 48.0) - __builtin_bit_cast(uint64_t, 48.0);
-        S.a.s = lane == 0 ? u : 0ull;
-    }
-    while (t < ns) {                                         // D holds step t
-        KeptStep N;
-        kept_load(N, km, ks, t + W < ns ? t + W : t, lane);
-        if (!kept_fold<STOP>(S, D, np)) break;
-        D = N;
-        t += W;
-    }
-    uint64_t s = S.a.s;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) s += (uint64_t)__shfl_xor((unsigned long long)s, off, 64);
-    if (lane == 0) L.s[wave] = s;
-    __syncthreads();
-    s = 0ull;
-#pragma unroll
-    for (int w = 0; w < W; ++w) s += L.s[w];
-    S.a.s = s;
+    if (shared && S.found == 2 && lane == 0) atomicMax(hint, ordered_f32(S.stop));
+    S.a.s = wave_sum_u64(S.a.s);
+    if (steps) *steps += t;
     return S.a;
 }
 
-// The partial in `slot` of (order b, node).
-__device__ __forceinline__ void kept_store(const TabView &V, int b, int node, const KeptAcc &a)
+// A node's result from its stripes' (P[0 .. nq - 1]).
+__device__ __forceinline__ Acc kept_combine(const KeptAcc *P, int nq)
+{
+    Acc r;
+    r.best = P[0].best;
+    r.sec = P[0].sec;
+    r.bm = P[0].bm;
+    double s = (double)P[0].s * 0x1p-47;
+    if (nq > 1) {
+        for (int q = 1; q < nq; ++q) {
+            const float b = P[q].best, c = P[q].sec;
+            const uint64_t m = P[q].bm;
+            const bool take = b > r.best || (b == r.best && m < r.bm);
+            r.sec = take ? fmaxf(r.best, c) : fmaxf(r.sec, b);
+            r.best = take ? b : r.best;
+            r.bm = take ? m : r.bm;
+        }
+        s = 0.0;
+        for (int q = 0; q < nq; ++q) {
+            const float b = P[q].best;
+            if (b == -INFINITY) continue;
+            const double e = b == r.best ? 1.0 : exp((double)b - (double)r.best);
+            s += ((double)P[q].s * 0x1p-47) * e;
+        }
+    }
+    r.m = r.best;
+    r.s = (float)s;
+    return r;
+}
+
+// Slot 0 of (order b, node).
+__device__ __forceinline__ void kept_store(const TabView &V, int b, int node, const Acc &a)
 {
     Partial p;
-    p.m = a.best;
-    p.s = kept_sum(a);
+    p.m = a.m;
+    p.s = a.s;
     p.best = a.best;
     p.second = a.sec;
     p.bmask = a.bm;
@@ -1461,8 +1461,8 @@ __device__ __forceinline__ void merge_block(const ScoreArgs &A, int b, MergeLds 
             if (A.node_lse) A.node_lse[o] = valid ? li : NAN;
             if (A.node_second) A.node_second[o] = valid ? r.sec : NAN;
         }
-        lse_out = wave_sum_f64(li, lane);
-        max_out = wave_sum_f64(mi, lane);
+        lse_out = wave_sum_f64(li);
+        max_out = wave_sum_f64(mi);
     }
 }
 

@@ -79,3 +79,63 @@ def test_kept_rows_invalid_orders_and_memory_cap(bnos, monkeypatch):
     np.testing.assert_allclose(out["node_lse"], ref["node_lse"], rtol=0, atol=2e-6)
     t.free()
     c.free()
+
+
+@pytest.mark.parametrize("n,K,N,arities,chains", [(2, 1, 50, (2,), 3), (9, 4, 0, (2, 3), 5), (20, 4, 1000, (2,), 4),
+                                                  (24, 4, 1500, (2, 3, 4), 600), (64, 2, 129, (2,), 7)])
+@pytest.mark.parametrize("target", [0, 1])
+def test_kept_chains_take_the_streamed_decisions(bnos, n, K, N, arities, chains, target):
+    # the one-launch chains against the launch-per-iteration sweep (score bound off): the same moves and, bit
+    # for bit, the same traces, records and traced edges, whole and resumed at an odd place
+    net = datagen.random_network(n, N, arities, min(3, n - 1), seed=3 * n + K)
+    t = bnos.build_score_table(net.data, net.arities, K)
+    assert t.kept_entries() > 0
+    iters, cut, every = 150, 67, 1
+    edges = [(0, 1), (1, 0)]
+    out = []
+    try:
+        for on in (True, False):
+            t.score_bound(on)
+            st = t.new_chain_state(chains, iters, flags=True, topk=3, edges=edges, harvest_cap=20)
+            t.run_chains(st, iters, seed=77, target=target, chain_offset=5)
+            torch.cuda.synchronize()
+            out.append({k: v.cpu().numpy() for k, v in st.items() if torch.is_tensor(v)})
+        a, b = out
+        for k in a:
+            assert np.array_equal(a[k].view(np.uint8), b[k].view(np.uint8)), k
+        t.score_bound(True)
+        st = t.new_chain_state(chains, cut, flags=True, topk=3)
+        t.run_chains(st, cut, seed=77, target=target, chain_offset=5)
+        st2 = t.new_chain_state(chains, iters - cut, flags=True, topk=3)
+        for k in ("orders", "scores", "best_graphs", "best_scores", "accepted", "top_graphs", "top_scores", "top_count"):
+            st2[k] = st[k]
+        t.run_chains(st2, iters - cut, seed=77, target=target, chain_offset=5, first_iteration=cut)
+        torch.cuda.synchronize()
+        for k in ("orders", "scores", "best_graphs", "best_scores", "accepted", "top_graphs", "top_scores", "top_count"):
+            assert np.array_equal(st2[k].cpu().numpy(), a[k]), k
+        assert np.array_equal(st2["accept_flags"].cpu().numpy(), a["accept_flags"][:, cut:])
+        assert np.array_equal(st2["trace"].cpu().numpy(), a["trace"][:, cut:])
+    finally:
+        t.free()
+
+
+def test_kept_and_streamed_tables_in_one_call(bnos):
+    # tables with and without kept rows, and one with the bound off, advanced together: each as by itself
+    shapes = [(12, 3, 300, (2, 3)), (48, 4, 60, (2,)), (20, 4, 1000, (3,))]
+    tabs = []
+    for n, K, N, ar in shapes:
+        net = datagen.random_network(n, N, ar, 3, seed=n)
+        tabs.append(bnos.build_score_table(net.data, net.arities, K))
+    assert [t.kept_entries() > 0 for t in tabs] == [True, False, True]
+    tabs[2].score_bound(False)
+    states = [t.new_chain_state(5, 40, flags=True) for t in tabs]
+    bnos.run_chains_multi(tabs, states, 40, 9, chain_offset=2)
+    torch.cuda.synchronize()
+    for k, t in enumerate(tabs):
+        ref = t.new_chain_state(5, 40, flags=True)
+        t.run_chains(ref, 40, 9, chain_offset=2 + 5 * k)
+        torch.cuda.synchronize()
+        for key in ("orders", "scores", "best_graphs", "best_scores", "accepted", "trace", "accept_flags"):
+            assert torch.equal(states[k][key], ref[key]), (k, key)
+    for t in tabs:
+        t.free()
