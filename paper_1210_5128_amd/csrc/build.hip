@@ -212,16 +212,39 @@ __global__ void k_prior(const float *__restrict__ src, int n, int mode, double *
     dst[g] = v;
 }
 
-// lut[row][c] = lnG(c + a) - lnG(a), a = ess / den[row], c = 0..N (FP64 ocml lgamma).
-__global__ void k_lut(const int32_t *__restrict__ den, int rows, int64_t N, double ess, double *__restrict__ lut)
+// lut[row][c] = lnG(c + a) - lnG(a), a = ess / den[row], c = 0..N (FP64 ocml lgamma); with
+// scale > 0 as 64-bit integers, the nearest to scale times that (see lut_scale).
+__global__ void k_lut(const int32_t *__restrict__ den, int rows, int64_t N, double ess, double scale,
+                      double *__restrict__ lut)
 {
     const int64_t total = (int64_t)rows * (N + 1);
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
         const int row = (int)(g / (N + 1));
         const int64_t c = g - (int64_t)row * (N + 1);
         const double a = ess / (double)den[row];
-        lut[g] = lgamma((double)c + a) - lgamma(a);
+        const double v = lgamma((double)c + a) - lgamma(a);
+        lut[g] = scale > 0.0 ? __builtin_bit_cast(double, (int64_t)rint(v * scale)) : v;
     }
+}
+
+// Sum of a 64-bit integer over the wavefront (uniform), on the DPP lane network.
+template <int CTRL>
+__device__ __forceinline__ uint64_t lane_moved_u64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uint64_t wave_total_u64(uint64_t v)
+{
+    v += lane_moved_u64<0xb1>(v);       // lane ^ 1, lane ^ 2, rows shifted by 4 and 8, row broadcasts
+    v += lane_moved_u64<0x4e>(v);
+    v += lane_moved_u64<0x114>(v);
+    v += lane_moved_u64<0x118>(v);
+    v += lane_moved_u64<0x142>(v);
+    v += lane_moved_u64<0x143>(v);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
 }
 
 // Rank of a mask among the masks over `bits` bits with at most K set bits, in
@@ -257,7 +280,8 @@ __device__ __forceinline__ void divmod_small(int x, int r, uint32_t magic, int &
     rem = x - (int)__umul24((uint32_t)q, (uint32_t)r);
 }
 
-__device__ __forceinline__ Subset decode_subset(uint64_t U, const int32_t *__restrict__ ar)
+// (ar: the n arities, then their magic numbers.)
+__device__ __forceinline__ Subset decode_subset(uint64_t U, const int32_t *__restrict__ ar, int n)
 {
     Subset S;
     S.j = 0;
@@ -266,13 +290,14 @@ __device__ __forceinline__ Subset decode_subset(uint64_t U, const int32_t *__res
     for (int t = 0; t <= kMaxK; ++t) {
         S.u[t] = 0;
         S.r[t] = 1;
+        S.magic[t] = 0u;
         if (m) {
             S.u[t] = __builtin_ctzll(m);
             m &= m - 1;
             S.r[t] = ar[S.u[t]];
+            S.magic[t] = (uint32_t)ar[n + S.u[t]];
             S.j = t + 1;
         }
-        S.magic[t] = S.r[t] > 1 ? (uint32_t)(0x100000000ull / (uint64_t)S.r[t]) + 1u : 0u;
     }
     int cells = 1;
 #pragma unroll
@@ -392,12 +417,124 @@ __device__ __forceinline__ int family_base(const Subset &S, int c, int k)
 // of the family (i, U \ {i}) from it -- that family's N_ijk are the joint
 // counts with i's state as the child state -- stored at U \ {i}'s entry of i's
 // row.  Counting once per U instead of once per family cuts the sample visits
-// by the mean family size (about 5x at K = 4).  The BDeu terms are summed in
-// the same order as in k_build (parent configurations k by lane, the lowest id
-// most significant; child states in order; the same butterfly), so the stored
-// scores are the same, bit for bit.
+// by the mean family size (about 5x at K = 4).
+
+// The lookup's terms as integers: the families of U share the sum of the N_ijk terms, which
+// depend only on U's cells (alpha_ijk = ess / cells for every child), and each subtracts the
+// terms of its own N_ik.  64-bit integers add up to the same total in any order, so the shared
+// sum, k_build's order over one family's cells and any lane assignment store the same score,
+// bit for bit.  lut_scale picks the unit: a family's sum stays below 2^62 of them, and a term,
+// rounded to the nearest, is closer to its FP64 value than FP64 additions of the family's
+// terms keep it (n = 60, N = 5,000: units of 2^-43).
+
+// Adds this lane's cells (c, c + 64, ...) of the joint histogram: the N_ijk terms to `all`,
+// and to of[t] the N_ik terms of the family whose child is member t, each taken at the cell
+// with that member's state 0.  (J = the number of members, a constant of the instance.)
+template <int J>
+__device__ __forceinline__ void subset_terms_j(const Subset &S, const uint32_t *hist, int lane,
+                                               const int32_t *__restrict__ lut_row,
+                                               const int64_t *__restrict__ lut, int64_t stride, uint64_t &all,
+                                               uint64_t (&of)[kMaxK + 1])
+{
+    const int64_t *Lijk = lut + lut_row[S.cells] * stride;
+    const int64_t *Lik[J];
+#pragma unroll
+    for (int t = 0; t < J; ++t) {
+        int q, rem;
+        divmod_small(S.cells, S.r[t], S.magic[t], q, rem);
+        Lik[t] = lut + lut_row[q] * stride;
+    }
+    for (int c = lane; c < S.cells; c += 64) {
+        const uint32_t cnt = hist[c];
+        all += (uint64_t)Lijk[cnt];
+        int rest = c;
+#pragma unroll
+        for (int t = J - 1; t >= 0; --t) {
+            int d = rest;
+            if (t > 0) {
+                int q;
+                divmod_small(rest, S.r[t], S.magic[t], q, d);
+                rest = q;
+            }
+            if (d == 0) {
+                uint32_t nik = cnt;
+                for (int x = 1, at = c + S.stride[t]; x < S.r[t]; ++x, at += S.stride[t]) nik += hist[at];
+                of[t] += (uint64_t)Lik[t][nik];
+            }
+        }
+    }
+}
+
+// What bounded it: scalar instructions.  The families' ranks were looked up bit by bit over 59
+// slots, U unranked over 60 nodes, seven 64-bit divisions formed the magic numbers, for every
+// subset, and every family summed the N_ijk terms again: 56 ms at n = 60 for 200 samples and for
+// 5,000 alike.  A wavefront now takes `run` consecutive subsets, each the successor of the one
+// before, lane t finishes the family of member t, and what is left is the histogram.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_build_joint(
+    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
+    const double *__restrict__ prior, const int64_t *__restrict__ nsets, int n, int K, double unit,
+    double log_gamma, int64_t n_subsets, int run, int64_t S_pad, int cells_cap, const int32_t *__restrict__ lut_row,
+    const int64_t *__restrict__ lut, uint64_t *__restrict__ masks, float *__restrict__ scores)
+{
+    extern __shared__ uint32_t lds_hist[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the subset's decode stays scalar
+    const int lane = threadIdx.x & 63;
+    uint32_t *hist = lds_hist + wave * cells_cap;
+    const int64_t g0 = ((int64_t)blockIdx.x * WAVES + wave) * run;
+    if (g0 >= n_subsets) return;
+    uint64_t U = unrank_ascending(g0 + 1, n, K + 1, nsets);
+    for (int64_t g = g0; g < g0 + run && g < n_subsets; ++g) {
+        const Subset Sb = decode_subset(U, ar, n);
+        joint_histogram(data, N, N_pad, Sb, hist, lane);
+        uint64_t all = 0ull, of[kMaxK + 1];
+#pragma unroll
+        for (int t = 0; t <= kMaxK; ++t) of[t] = 0ull;
+        switch (Sb.j) {                // uniform
+        case 1: subset_terms_j<1>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        case 2: subset_terms_j<2>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        case 3: subset_terms_j<3>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        case 4: subset_terms_j<4>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        case 5: subset_terms_j<5>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        case 6: subset_terms_j<6>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        default: subset_terms_j<kMaxK + 1>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
+        }
+        all = wave_total_u64(all);
+        uint64_t sum = 0ull;           // lane t: the family of member t
+        int node = 0;
+#pragma unroll
+        for (int t = 0; t <= kMaxK; ++t)
+            if (t < Sb.j) {            // uniform
+                const uint64_t o = wave_total_u64(of[t]);
+                sum = lane == t ? all - o : sum;
+                node = lane == t ? Sb.u[t] : node;
+            }
+        if (lane < Sb.j) {
+            double sc = fma((double)(Sb.j - 1), log_gamma, (double)(int64_t)sum * unit);   // unit: a power of two
+            // the rank of U without the node: its members from the highest down, at places
+            // K, K - 1, ..., those above the node one slot lower
+            int64_t e = (int64_t)node * S_pad;
+#pragma unroll
+            for (int t = 0; t <= kMaxK; ++t)
+                if (t < Sb.j && t != lane) {
+                    sc += prior[(int64_t)node * n + Sb.u[t]];
+                    const int above = Sb.j - 1 - t - (lane > t ? 1 : 0), slot = Sb.u[t] - (lane < t ? 1 : 0);
+                    e += nsets[slot * 8 + (K - above)];
+                }
+            masks[e] = U & ~(1ull << node);
+            scores[e] = (float)sc;     // round to nearest even
+        }
+        wave_lds_sync();   // every lane has read hist before the next subset clears it
+        U += (__popcll(U) <= K) ? 1ull : (U & (0ull - U));   // the next mask of at most K + 1 members
+    }
+}
+
+// The same with FP64 terms, a family after the other (where no integer unit serves: see
+// lut_scale): the BDeu terms are summed in the same order as in k_build (parent configurations k
+// by lane, the lowest id most significant; child states in order; the same butterfly), so the
+// stored scores are the same, bit for bit.
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_build_joint_fp(
     const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
     const double *__restrict__ prior, const int64_t *__restrict__ nsets, int n, int K, double ess,
     double log_gamma, int64_t n_subsets, int64_t S_pad, int cells_cap, const int32_t *__restrict__ lut_row,
@@ -409,7 +546,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_build_joint(
     uint32_t *hist = lds_hist + wave * cells_cap;
     for (int64_t g = (int64_t)blockIdx.x * WAVES + wave; g < n_subsets; g += (int64_t)gridDim.x * WAVES) {
         const uint64_t U = unrank_ascending(g + 1, n, K + 1, nsets);
-        const Subset Sb = decode_subset(U, ar);
+        const Subset Sb = decode_subset(U, ar, n);
         const int j = Sb.j, cells = Sb.cells;
         joint_histogram(data, N, N_pad, Sb, hist, lane);
         // one family per member
@@ -470,7 +607,7 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_build(
     const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
     const double *__restrict__ prior, const int64_t *__restrict__ nsets, int n, int K, double ess,
-    double log_gamma, int64_t S, int64_t S_pad, int cells_cap, const int32_t *__restrict__ lut_row,
+    double unit, double log_gamma, int64_t S, int64_t S_pad, int cells_cap, const int32_t *__restrict__ lut_row,
     const double *__restrict__ lut, uint64_t *__restrict__ masks, float *__restrict__ scores)
 {
     extern __shared__ uint32_t lds_hist[];
@@ -497,7 +634,21 @@ __global__ __launch_bounds__(WAVES * 64) void k_build(
         const double a_ijk = ess / (double)cells;
         const double a_ik = ess / (double)M.q;
         double acc = 0.0;
-        if (lut) {
+        if (lut && unit > 0.0) {      // integer terms
+            const int64_t *L_ijk = reinterpret_cast<const int64_t *>(lut) + (int64_t)lut_row[cells] * (N + 1);
+            const int64_t *L_ik = reinterpret_cast<const int64_t *>(lut) + (int64_t)lut_row[M.q] * (N + 1);
+            uint64_t sum = 0ull;
+            for (int k = lane; k < M.q; k += 64) {
+                uint32_t nik = 0;
+                for (int j = 0; j < r; ++j) {
+                    const uint32_t c = hist[k * r + j];
+                    nik += c;
+                    sum += (uint64_t)L_ijk[c];
+                }
+                sum -= (uint64_t)L_ik[nik];
+            }
+            acc = (double)(int64_t)wave_total_u64(sum) * unit;
+        } else if (lut) {
             // lnG(c + a) - lnG(a) looked up per count (same FP64 values as computed below)
             const double *L_ijk = lut + (int64_t)lut_row[cells] * (N + 1);
             const double *L_ik = lut + (int64_t)lut_row[M.q] * (N + 1);
@@ -527,10 +678,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_build(
                 acc += part;
             }
         }
-        acc = wave_sum_f64(acc);
+        if (!(lut && unit > 0.0)) acc = wave_sum_f64(acc);
         wave_lds_sync();   // every lane has read hist before the next entry clears it
         if (lane == 0) {
-            double s = acc + (double)M.cnt * log_gamma;
+            double s = fma((double)M.cnt, log_gamma, acc);
 #pragma unroll
             for (int t = 0; t < kMaxK; ++t)
                 if (t < M.cnt) s += prior[(int64_t)node * n + M.id[t]];
@@ -1093,7 +1244,7 @@ __global__ __launch_bounds__(1024) void k_keep_top(int n, int64_t cap, int32_t *
 // Counts for explicit (node, parent mask) queries, with the build's counting code.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_counts(
-    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
+    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar, int n,
     int Q, const int32_t *__restrict__ qnode, const uint64_t *__restrict__ qmask,
     const int64_t *__restrict__ qoff, int cells_cap, uint32_t *__restrict__ out)
 {
@@ -1118,7 +1269,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_counts(
 // the child state).
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_counts_joint(
-    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
+    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar, int n,
     int Q, const int32_t *__restrict__ qnode, const uint64_t *__restrict__ qmask,
     const int64_t *__restrict__ qoff, int cells_cap, uint32_t *__restrict__ out)
 {
@@ -1129,7 +1280,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_counts_joint(
     for (int qi = blockIdx.x * WAVES + wave; qi < Q; qi += gridDim.x * WAVES) {
         const int child = qnode[qi];
         const uint64_t U = qmask[qi] | (1ull << child);
-        const Subset Sb = decode_subset(U, ar);
+        const Subset Sb = decode_subset(U, ar, n);
         joint_histogram(data, N, N_pad, Sb, hist, lane);
         const int c = __popcll(U & ((1ull << child) - 1ull));       // the child's place among U's members
         int node, ri, sci, q;
@@ -1162,30 +1313,59 @@ static int64_t sets_upto(int m, int K)
 
 static int waves_for_cells(int cells_cap) { return cells_cap <= 4096 ? 4 : 1; }
 
+// Units per nat of an integer lookup (a power of two), or 0 where FP64 terms serve: alpha = ess / d
+// runs from ess / max_cells to ess, so with N samples no term's magnitude passes N (ln(N + ess + 1) + 1)
+// + |ln alpha| + 1, a family has at most min(N, cells) terms that start at ln alpha, and its sums
+// stay below the bound formed here; outside these ess the differences of lgamma lose their digits.
+static double lut_scale(double ess, int64_t N, int max_cells)
+{
+    if (!(ess >= 1e-6 && ess <= 1e6)) return 0.0;
+    const double starts = (double)std::min<int64_t>(N + 1, max_cells);
+    const double bound = 2.0 * ((double)(N + 1) * (std::log((double)N + ess + 2.0) + 1.0) +
+                                starts * (std::fabs(std::log(ess / (double)max_cells)) + std::fabs(std::log(ess)) + 2.0));
+    int s = 62;
+    for (double b = bound; b >= 1.0; b *= 0.5) --s;
+    return s < 1 ? 0.0 : std::ldexp(1.0, s < 50 ? s : 50);
+}
+
 template <int W>
-static hipError_t launch_build(TableT *t, hipStream_t st, int cells_cap, const int32_t *lut_row, const double *lut)
+static hipError_t launch_build(TableT *t, hipStream_t st, int cells_cap, const int32_t *lut_row, const double *lut,
+                               double scale)
 {
     int64_t total = (int64_t)t->n * t->S_pad;
     int64_t blocks = (total + W - 1) / W;
     if (blocks > (1 << 22)) blocks = 1 << 22;
     size_t lds = (size_t)W * cells_cap * sizeof(uint32_t);
     hipLaunchKernelGGL(k_build<W>, dim3((unsigned)blocks), dim3(W * 64), lds, st, t->d_data, t->N,
-                       t->N_pad, t->d_ar, t->d_prior, t->d_nsets, t->n, t->K, t->ess, t->log_gamma,
+                       t->N_pad, t->d_ar, t->d_prior, t->d_nsets, t->n, t->K, t->ess,
+                       scale > 0.0 ? 1.0 / scale : 0.0, t->log_gamma,
                        t->S, t->S_pad, cells_cap, lut_row, lut, t->d_masks, t->d_scores);
     return hipGetLastError();
 }
 
 template <int W>
 static hipError_t launch_build_joint(TableT *t, hipStream_t st, int cells_cap, const int32_t *lut_row,
-                                     const double *lut)
+                                     const double *lut, double scale)
 {
     const int64_t subsets = sets_upto(t->n, t->K + 1) - 1;
-    int64_t blocks = (subsets + W - 1) / W;
-    if (blocks > (1 << 22)) blocks = 1 << 22;
     size_t lds = (size_t)W * cells_cap * sizeof(uint32_t);
-    hipLaunchKernelGGL(k_build_joint<W>, dim3((unsigned)blocks), dim3(W * 64), lds, st, t->d_data, t->N,
-                       t->N_pad, t->d_ar, t->d_prior, t->d_nsets, t->n, t->K, t->ess, t->log_gamma, subsets,
-                       t->S_pad, cells_cap, lut_row, lut, t->d_masks, t->d_scores);
+    if (scale > 0.0) {
+        // runs long enough to spread the first subset's unranking, short enough to leave 16 wavefronts
+        // to each SIMD of the card
+        const int run = (int)std::max<int64_t>(1, std::min<int64_t>(32, subsets / 16384));
+        const int64_t waves = (subsets + run - 1) / run, blocks = (waves + W - 1) / W;
+        if (blocks > INT32_MAX) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_build_joint<W>, dim3((unsigned)blocks), dim3(W * 64), lds, st, t->d_data, t->N,
+                           t->N_pad, t->d_ar, t->d_prior, t->d_nsets, t->n, t->K, 1.0 / scale, t->log_gamma, subsets,
+                           run, t->S_pad, cells_cap, lut_row, reinterpret_cast<const int64_t *>(lut), t->d_masks,
+                           t->d_scores);
+    } else {
+        int64_t blocks = (subsets + W - 1) / W;
+        if (blocks > (1 << 22)) blocks = 1 << 22;
+        hipLaunchKernelGGL(k_build_joint_fp<W>, dim3((unsigned)blocks), dim3(W * 64), lds, st, t->d_data, t->N,
+                           t->N_pad, t->d_ar, t->d_prior, t->d_nsets, t->n, t->K, t->ess, t->log_gamma, subsets,
+                           t->S_pad, cells_cap, lut_row, lut, t->d_masks, t->d_scores);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t->S_pad == t->S) return e;
     const int64_t pad = (int64_t)t->n * (t->S_pad - t->S);
@@ -1439,7 +1619,7 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
         return fail(e == hipErrorOutOfMemory ? BNOS_E_NOMEM : BNOS_E_DEVICE);           \
     }
     ALLOC(t->d_data, (size_t)n * t->N_pad);
-    ALLOC(t->d_ar, sizeof(int32_t) * n);
+    ALLOC(t->d_ar, sizeof(int32_t) * 2 * n);
     ALLOC(t->d_prior, sizeof(double) * n * n);
     ALLOC(t->d_nsets, sizeof(int64_t) * 64 * 8);
     ALLOC(t->d_masks, sizeof(uint64_t) * (size_t)n * t->S_pad);
@@ -1471,7 +1651,9 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     CK(hipMemsetAsync(t->d_data, 0, (size_t)n * t->N_pad, st));
     if (N > 0 && !dev_data) CK(hipMemcpyAsync(d_rows, data, (size_t)N * n, hipMemcpyHostToDevice, st));
     if (prior) CK(hipMemcpyAsync(d_prior_in, prior, sizeof(float) * n * n, hipMemcpyHostToDevice, st));
-    CK(hipMemcpyAsync(t->d_ar, arities, sizeof(int32_t) * n, hipMemcpyHostToDevice, st));
+    std::vector<int32_t> ar_magic(arities, arities + n);     // the arities, then their magic numbers (divmod_small)
+    for (int v = 0; v < n; ++v) ar_magic.push_back(arities[v] > 1 ? (int32_t)(uint32_t)(0x100000000ull / arities[v] + 1) : 0);
+    CK(hipMemcpyAsync(t->d_ar, ar_magic.data(), sizeof(int32_t) * 2 * n, hipMemcpyHostToDevice, st));
     CK(hipMemcpyAsync(t->d_nsets, nsets.data(), sizeof(int64_t) * 64 * 8, hipMemcpyHostToDevice, st));
     if (N > 0) {
         int64_t tot = N * n;
@@ -1508,6 +1690,7 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     // product of at most K parent arities) and d = q * r_i; every such d up to
     // the largest q * r_i gets a row of lnG(c + alpha) - lnG(alpha), c = 0..N,
     // unless that would take more than kLutBytes (then lgamma is called inline).
+    const double scale = lut_scale(ess, N, max_cells);
     {
         std::vector<char> isq(max_cells + 1, 0), isd(max_cells + 1, 0);
         std::vector<int> ar_set;
@@ -1540,18 +1723,18 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
             CK(hipMemcpyAsync(d_lut_row, row.data(), sizeof(int32_t) * row.size(), hipMemcpyHostToDevice, st));
             const int64_t tot = (int64_t)den.size() * (N + 1);
             hipLaunchKernelGGL(k_lut, dim3((unsigned)std::min<int64_t>((tot + 255) / 256, 1 << 16)), dim3(256), 0, st,
-                               d_den, (int)den.size(), N, ess, d_lut);
+                               d_den, (int)den.size(), N, ess, scale, d_lut);
             CK(hipGetLastError());
         }
     }
     int cap = cells_cap_for(max_cells);
     t->count_mode = (d_lut && o.count_mode == 0) ? 0 : 1;
     if (t->count_mode == 0) {                    // one joint histogram per node subset
-        if (waves_for_cells(cap) == 4) { CK(launch_build_joint<4>(t, st, cap, d_lut_row, d_lut)); }
-        else { CK(launch_build_joint<1>(t, st, cap, d_lut_row, d_lut)); }
+        if (waves_for_cells(cap) == 4) { CK(launch_build_joint<4>(t, st, cap, d_lut_row, d_lut, scale)); }
+        else { CK(launch_build_joint<1>(t, st, cap, d_lut_row, d_lut, scale)); }
     } else {                                     // one histogram per family
-        if (waves_for_cells(cap) == 4) { CK(launch_build<4>(t, st, cap, d_lut_row, d_lut)); }
-        else { CK(launch_build<1>(t, st, cap, d_lut_row, d_lut)); }
+        if (waves_for_cells(cap) == 4) { CK(launch_build<4>(t, st, cap, d_lut_row, d_lut, scale)); }
+        else { CK(launch_build<1>(t, st, cap, d_lut_row, d_lut, scale)); }
     }
     hipLaunchKernelGGL(k_node_stats, dim3(n), dim3(1024), 0, st, t->d_scores, t->S, t->S_pad, t->d_prior, n,
                        t->d_nstat);
@@ -1681,14 +1864,14 @@ extern "C" bnos_status bnos_counts(bnos_table h, int32_t Q, const int32_t *nodes
     const dim3 grid((unsigned)(four ? blocks : blocks * 4)), block(four ? 256 : 64);
     const size_t lds = (four ? 4 : 1) * cap_cells * sizeof(uint32_t);
     if (t->count_mode == 0) {
-        if (four) hipLaunchKernelGGL(k_counts_joint<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q,
+        if (four) hipLaunchKernelGGL(k_counts_joint<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q,
                                      d_nodes, d_masks, d_off, cap_cells, d_out);
-        else hipLaunchKernelGGL(k_counts_joint<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q,
+        else hipLaunchKernelGGL(k_counts_joint<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q,
                                 d_nodes, d_masks, d_off, cap_cells, d_out);
     } else {
-        if (four) hipLaunchKernelGGL(k_counts<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q,
+        if (four) hipLaunchKernelGGL(k_counts<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q,
                                      d_nodes, d_masks, d_off, cap_cells, d_out);
-        else hipLaunchKernelGGL(k_counts<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q, d_nodes,
+        else hipLaunchKernelGGL(k_counts<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q, d_nodes,
                                 d_masks, d_off, cap_cells, d_out);
     }
     CK(hipGetLastError());
