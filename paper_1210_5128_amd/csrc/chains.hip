@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
             for (int j = 0; j < 5; ++j) f[3 + j] = (float)H.nstat[i * 5 + j];
         }
         __syncthreads();
-        mlp_forward_block(H.mlp, s_feat, n, s_mlp, nullptr);
+        mlp_forward_block(H.mlp, mlp_load(H.mlp, wave, lane), s_feat, n, s_mlp);
     }
     if (wave != 0) return;
 
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(W * 64) void k_chain_run(const TabView *__restrict_
                 for (int i = 0; i < 5; ++i) f[3 + i] = (float)H.nstat[lane * 5 + i];
             }
             __syncthreads();
-            mlp_forward_block(H.mlp, s_feat, n, s_mlp, nullptr);
+            mlp_forward_block(H.mlp, mlp_load(H.mlp, wave, lane), s_feat, n, s_mlp);
         }
         double nv = 0.0;
         bool acc = adopt;

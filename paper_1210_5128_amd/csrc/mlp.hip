@@ -78,14 +78,17 @@ __global__ void k_mlp_refresh(const float *__restrict__ master, uint16_t *__rest
     }
 }
 
-// Block per sample: logits of its n nodes from raw features [R][n][8].
-__global__ __launch_bounds__(1024) void k_mlp_forward(MlpView P, const float *__restrict__ feats, int n,
+// Logits of R samples of n nodes from raw features [R][n][8]: block b takes the samples b,
+// b + blocks, ... with the weights in registers.
+__global__ __launch_bounds__(1024) void k_mlp_forward(MlpView P, const float *__restrict__ feats, int R, int n,
                                                       float *__restrict__ logits)
 {
     __shared__ MlpLds L;
-    const int s = blockIdx.x;
-    mlp_forward_block(P, feats + (int64_t)s * n * kF, n, L, nullptr);
-    if (threadIdx.x < n) logits[(int64_t)s * n + threadIdx.x] = L.logit[threadIdx.x];
+    const MlpRegs W = mlp_load(P, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
+    for (int s = blockIdx.x; s < R; s += gridDim.x) {
+        mlp_forward_block(P, W, feats + (int64_t)s * n * kF, n, L);
+        if (threadIdx.x < n) logits[(int64_t)s * n + threadIdx.x] = L.logit[threadIdx.x];
+    }
 }
 
 // Per-feature mean and population standard deviation over `rows` rows (FP64,
@@ -152,16 +155,29 @@ __global__ void k_feat_norm_final(const double *__restrict__ part, int blocks, i
     norm[kF + k] = (float)(1.0 / sd);
 }
 
+constexpr int kRP = kRows + 8;       // LDS row pitch of arrays with the nodes along a row (bf16)
+constexpr int kFP = kRows + 4;       // and of such a float array
 struct alignas(16) GradLds {
-    MlpLds f;
-    float zraw[kRows * kF];
-    float h2[kRows][kH];            // relu(layer 2); later reused for dpre1
-    uint16_t d2[2][kRows][kHP];     // dL/dpre2 as hi / lo bf16 operands
+    uint16_t z[kRows][16];          // normalised features: hi in columns 0..7, lo in 8..15
+    uint16_t zt[16][kRP];           // the same, transposed
+    uint16_t h1[2][kRows][kHP];     // relu(layer 1) as hi / lo operands; then dL/dpre2
+    uint16_t h1t[2][kH][kRP];       // relu(layer 1), transposed
+    uint16_t d2t[2][kH][kRP];       // dL/dpre2, transposed
+    float ft[kH][kFP];              // relu(layer 2), transposed; then dL/dpre1
+    float part[kRows][8];
     float dl[kRows];
-    float gw3[kH], gb2[kH], gb1[kH];
-    double loss;
-    float gb3;
 };
+static_assert(sizeof(GradLds) <= 160 * 1024, "one block per compute unit");
+
+// Four values of consecutive nodes as hi / lo operands of a transposed array.
+__device__ __forceinline__ void store4_bf(uint16_t *hi, uint16_t *lo, const float (&v)[4])
+{
+    uint16_t h[4], l[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) split_bf(v[r], h[r], l[r]);
+    *reinterpret_cast<uint2 *>(hi) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+    *reinterpret_cast<uint2 *>(lo) = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+}
 
 // Sample index of position j of the epoch's visiting order (affine bijection).
 __device__ __forceinline__ int64_t visit(int64_t j, int64_t count, int64_t stride, int64_t offset)
@@ -176,8 +192,14 @@ __device__ __forceinline__ int64_t visit(int64_t j, int64_t count, int64_t strid
 // one partial gradient (+ loss sum at index kNParam) per block.  Every
 // activation operand is a hi/lo BF16 pair (see mlp_device.h); products of two
 // activations take hi*hi + hi*lo + lo*hi.
+//
+// Wavefront w reads the weights of column tile w (both layers and W2^T) ahead of the phase
+// that uses them and takes that tile's columns for all rows.  Activations that the
+// gradients contract over the nodes are kept transposed too, so that every operand is one
+// 16-byte LDS read, and layer 2's outputs stay in registers until their gradient is
+// formed.  The bias and w3 sums run over the nodes in order, one column per thread, beside
+// the phases that need no result of theirs.
 constexpr int kGradWaves = 8;
-constexpr int kW2TilesPerWave = 64 / kGradWaves;
 
 __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const float *__restrict__ feats,
                                                    const int32_t *__restrict__ pairs, int64_t count, int64_t first,
@@ -187,33 +209,74 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const f
     __shared__ GradLds G;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int li = lane & 15, g = lane >> 4;
-    v4f accW2[kW2TilesPerWave];     // gW2 tiles (ut, kt) = (wave*T+q) / 8, % 8
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4, u = wave * 16 + li;
+    v4f accW2[8];                   // gW2 tiles (row tile wave, column tile q)
     v4f accW1 = {0.f, 0.f, 0.f, 0.f};
+    float gw3 = 0.f, gb2 = 0.f, gb1 = 0.f;      // column tid, tid - 128, tid - 256
+    float gb3 = 0.f;
+    double loss = 0.0;
 #pragma unroll
-    for (int q = 0; q < kW2TilesPerWave; ++q) accW2[q] = (v4f){0.f, 0.f, 0.f, 0.f};
-    if (tid < kH) {
-        G.gw3[tid] = 0.f;
-        G.gb2[tid] = 0.f;
-        G.gb1[tid] = 0.f;
-    }
-    if (tid == 0) {
-        G.loss = 0.0;
-        G.gb3 = 0.f;
-    }
+    for (int q = 0; q < 8; ++q) accW2[q] = (v4f){0.f, 0.f, 0.f, 0.f};
     const int64_t j0 = (int64_t)blockIdx.x * spb;
     for (int si = 0; si < spb; ++si) {
         const int64_t j = j0 + si;
         if (j >= nsamples) break;                        // uniform
         const int64_t smp = visit(first + j, count, stride, offset);
-        for (int e = tid; e < n * kF; e += blockDim.x) G.zraw[e] = feats[smp * n * kF + e];
+        const MlpRegs R = mlp_load(P, wave, lane);       // requested here, used two barriers on
+        {                                                // one feature of one node per thread
+            const int r = tid / kF, k = tid % kF;
+            float v = 0.f;
+            if (r < n) v = (feats[(smp * n + r) * kF + k] - P.norm[k]) * P.norm[kF + k];
+            uint16_t hi, lo;
+            split_bf(v, hi, lo);
+            G.z[r][k] = hi;
+            G.z[r][kF + k] = lo;
+            G.zt[k][r] = hi;
+            G.zt[kF + k][r] = lo;
+        }
         __syncthreads();
-        mlp_forward_block(P, G.zraw, n, G.f, &G.h2[0][0]);
+        // layer 1 (as mlp_forward_block)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+            v4u a = {0u, 0u, 0u, 0u};
+            if (g < 2) a = ld8(&G.z[rt * 16 + li][8 * g]);
+            const v4f d = mfma32(a, R.w1, (v4f){0.f, 0.f, 0.f, 0.f});
+            float h[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float x = d[r] + R.b1;
+                h[r] = x > 0.f ? x : 0.f;
+                split_bf(h[r], G.h1[0][rt * 16 + 4 * g + r][u], G.h1[1][rt * 16 + 4 * g + r][u]);
+            }
+            store4_bf(&G.h1t[0][u][rt * 16 + 4 * g], &G.h1t[1][u][rt * 16 + 4 * g], h);
+        }
+        __syncthreads();
+        // layer 2, its outputs kept in registers too, and the layer-3 dot products
+        v4f h2[4];
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+            v4f d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                d = mfma32(ld8(&G.h1[s >> 2][rt * 16 + li][(s & 3) * 32 + 8 * g]), R.w2[s & 3], d);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float x = d[r] + R.b2;
+                h2[rt][r] = x > 0.f ? x : 0.f;
+                const float q = row_dot_f32(h2[rt][r], R.w3);
+                if (li == 0) G.part[rt * 16 + 4 * g + r][wave] = q;
+            }
+            *reinterpret_cast<v4f *>(&G.ft[u][rt * 16 + 4 * g]) = h2[rt];
+        }
+        __syncthreads();
         // dL/dlogit for L = -ln q({a,b})
         if (wave == 0) {
+            float s = P.b3[0];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s += G.part[lane][c];
             const int a = pairs[smp * 2], b = pairs[smp * 2 + 1];
-            const double l = lane < n ? (double)G.f.logit[lane] : -1e300;
+            const double l = lane < n ? (double)s : -1e300;
             double mx = l;
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
@@ -232,100 +295,113 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const f
             const double gb = pb * pa * (1.0 / ((1.0 - pb) * (1.0 - pb)) + 1.0 / (1.0 - pa));
             double dQ = -p * (ga + gb) + (lane == a ? ga : 0.0) + (lane == b ? gb : 0.0);
             G.dl[lane] = lane < n ? (float)(-(1.0 - eps) * dQ / q) : 0.f;
-            if (lane == 0) G.loss += -log(q);
+            loss += -log(q);
         }
         __syncthreads();
-        // dL/dpre2 = relu'(pre2) * dl * w3 (hi/lo operands); bias / w3 / b3 gradients (rows in order)
-        for (int e = tid; e < kRows * kH; e += blockDim.x) {
-            const int r = e / kH, u = e % kH;
-            const float d = G.h2[r][u] > 0.f ? G.dl[r] * P.w3r[u] : 0.f;
-            split_bf(d, G.d2[0][r][u], G.d2[1][r][u]);
-        }
-        if (tid < kH) {
-            float s3 = 0.f, s2 = 0.f;
-            for (int r = 0; r < n; ++r) {
-                const float h = G.h2[r][tid];
-                s3 += G.dl[r] * h;
-                s2 += h > 0.f ? G.dl[r] * P.w3r[tid] : 0.f;
+        v4u w2t[4];                     // W2^T rows of this column tile, used after the next barrier
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w2t[q] = ld8(P.W2tb + u * kH + q * 32 + 8 * g);
+        // dL/dpre2 = relu'(pre2) * dl * w3 (hi/lo operands, both ways; h1's rows are done with)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+            const int row = rt * 16 + 4 * g;
+            float d[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d[r] = h2[rt][r] > 0.f ? G.dl[row + r] * R.w3 : 0.f;
+                split_bf(d[r], G.h1[0][row + r][u], G.h1[1][row + r][u]);
             }
-            G.gw3[tid] += s3;
-            G.gb2[tid] += s2;
+            store4_bf(&G.d2t[0][u][row], &G.d2t[1][u][row], d);
         }
-        if (tid == 0) {
+        // w3 / layer-2 bias / b3 gradients (rows in order)
+        if (tid < kH) {
+            float s3 = 0.f;
+            for (int r = 0; r < n; ++r) s3 += G.dl[r] * G.ft[tid][r];
+            gw3 += s3;
+        } else if (tid < 2 * kH) {
+            const float w3 = P.w3r[tid - kH];
+            float s2 = 0.f;
+            for (int r = 0; r < n; ++r) s2 += G.ft[tid - kH][r] > 0.f ? G.dl[r] * w3 : 0.f;
+            gb2 += s2;
+        } else if (tid == 2 * kH) {
             float s = 0.f;
             for (int r = 0; r < n; ++r) s += G.dl[r];
-            G.gb3 += s;
+            gb3 += s;
         }
         __syncthreads();
         // gW2[u][k] += sum_r d2[r][u] h1[r][k]: A[u][r] = d2, B[r][k] = h1, K = 64 rows in two
         // steps of 32, for the products (d2 hi, h1 hi), (d2 hi, h1 lo), (d2 lo, h1 hi)
+        {
+            v4u a[2][2];
 #pragma unroll
-        for (int q = 0; q < kW2TilesPerWave; ++q) {
-            const int tile = wave * kW2TilesPerWave + q, ut = tile >> 3, kt = tile & 7;
+            for (int pd = 0; pd < 2; ++pd)
 #pragma unroll
-            for (int pr = 0; pr < 3; ++pr) {
-                const int pd = pr == 2 ? 1 : 0, ph = pr == 1 ? 1 : 0;
+                for (int ks = 0; ks < 2; ++ks) a[pd][ks] = ld8(&G.d2t[pd][u][ks * 32 + 8 * g]);
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const int r0 = ks * 32 + 8 * g;
-                    accW2[q] = mfma32(ld8_strided(&G.d2[pd][r0][ut * 16 + li], kHP),
-                                      ld8_strided(&G.f.h1[ph][r0][kt * 16 + li], kHP), accW2[q]);
-                }
+            for (int q = 0; q < 8; ++q) {
+                v4u b[2][2];
+#pragma unroll
+                for (int ph = 0; ph < 2; ++ph)
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) b[ph][ks] = ld8(&G.h1t[ph][q * 16 + li][ks * 32 + 8 * g]);
+#pragma unroll
+                for (int pr = 0; pr < 3; ++pr)
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) accW2[q] = mfma32(a[pr == 2][ks], b[pr == 1][ks], accW2[q]);
             }
         }
-        __syncthreads();
-        // dh1[r][k] = sum_u d2[r][u] W2[u][k] (K = 128, hi then lo); dpre1 = relu'(pre1) dh1 -> G.h2
-        for (int tile = wave; tile < 32; tile += kGradWaves) {
-            const int rt = tile >> 3, kt = tile & 7;
+        // dh1[r][k] = sum_u d2[r][u] W2[u][k] (K = 128, hi then lo); dpre1 = relu'(pre1) dh1
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
             v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const int pd = s >> 2, ub = (s & 3) * 32 + 8 * g;
-                d = mfma32(ld8(&G.d2[pd][rt * 16 + li][ub]), ld8(P.W2tb + (kt * 16 + li) * kH + ub), d);
-            }
-            const int k = kt * 16 + li;
+            for (int s = 0; s < 8; ++s)
+                d = mfma32(ld8(&G.h1[s >> 2][rt * 16 + li][(s & 3) * 32 + 8 * g]), w2t[s & 3], d);
+            v4f v;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = rt * 16 + 4 * g + r;
-                G.h2[row][k] = (row < n && G.f.h1[0][row][k] != 0) ? d[r] : 0.f;
+                v[r] = (row < n && G.h1t[0][u][row] != 0) ? d[r] : 0.f;
             }
+            *reinterpret_cast<v4f *>(&G.ft[u][rt * 16 + 4 * g]) = v;
         }
         __syncthreads();
-        if (tid < kH) {
-            float s1 = 0.f;
-            for (int r = 0; r < n; ++r) s1 += G.h2[r][tid];
-            G.gb1[tid] += s1;
-        }
         // gW1[u][k] += sum_r dpre1[r][u] z[r][k]: A[u][r] = dpre1 (hi, then lo), B[r][c] = the
         // z row (columns 0..7 hi, 8..15 lo); columns c and c + 8 are added at the end, so the
         // tile sums hi*hi + hi*lo + lo*hi + lo*lo (8 tiles of 16 hidden units)
-        if (wave < 8) {
-            const int ut = wave;
+        {
+            v4u a[2][2];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int part = s >> 1, r0 = (s & 1) * 32 + 8 * g;
-                v4u a;
+            for (int ks = 0; ks < 2; ++ks) {
+                float x[8];
+                *reinterpret_cast<v4f *>(&x[0]) = *reinterpret_cast<const v4f *>(&G.ft[u][ks * 32 + 8 * g]);
+                *reinterpret_cast<v4f *>(&x[4]) = *reinterpret_cast<const v4f *>(&G.ft[u][ks * 32 + 8 * g + 4]);
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
+                for (int i = 0; i < 4; ++i) {
                     uint16_t h0, l0, h1v, l1;
-                    split_bf(G.h2[r0 + 2 * jj][ut * 16 + li], h0, l0);
-                    split_bf(G.h2[r0 + 2 * jj + 1][ut * 16 + li], h1v, l1);
-                    a[jj] = part ? ((uint32_t)l0 | ((uint32_t)l1 << 16)) : ((uint32_t)h0 | ((uint32_t)h1v << 16));
+                    split_bf(x[2 * i], h0, l0);
+                    split_bf(x[2 * i + 1], h1v, l1);
+                    a[0][ks][i] = (uint32_t)h0 | ((uint32_t)h1v << 16);
+                    a[1][ks][i] = (uint32_t)l0 | ((uint32_t)l1 << 16);
                 }
-                accW1 = mfma32(a, ld8_strided(&G.f.z[r0][li], 16), accW1);
             }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) accW1 = mfma32(a[s >> 1][s & 1], ld8(&G.zt[li][(s & 1) * 32 + 8 * g]), accW1);
+        }
+        if (tid >= 2 * kH && tid < 3 * kH) {
+            float s1 = 0.f;
+            for (int r = 0; r < n; ++r) s1 += G.ft[tid - 2 * kH][r];
+            gb1 += s1;
         }
         __syncthreads();
     }
     // partial gradient of this block
     float *out = part + (int64_t)blockIdx.x * (kNParam + 1);
 #pragma unroll
-    for (int q = 0; q < kW2TilesPerWave; ++q) {
-        const int tile = wave * kW2TilesPerWave + q, ut = tile >> 3, kt = tile & 7;
+    for (int q = 0; q < 8; ++q)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[kOffW2 + (ut * 16 + 4 * g + r) * kH + kt * 16 + li] = accW2[q][r];
-    }
-    if (wave < 8) {
+        for (int r = 0; r < 4; ++r) out[kOffW2 + (wave * 16 + 4 * g + r) * kH + q * 16 + li] = accW2[q][r];
+    {
         // column li + 8 holds the products with z_lo of column li
         float hi8[4];
 #pragma unroll
@@ -334,45 +410,71 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const f
 #pragma unroll
             for (int r = 0; r < 4; ++r) out[kOffW1 + (wave * 16 + 4 * g + r) * kF + li] = accW1[r] + hi8[r];
     }
-    if (tid < kH) {
-        out[kOffB1 + tid] = G.gb1[tid];
-        out[kOffB2 + tid] = G.gb2[tid];
-        out[kOffW3 + tid] = G.gw3[tid];
+    if (tid < kH) out[kOffW3 + tid] = gw3;
+    else if (tid < 2 * kH) out[kOffB2 + tid - kH] = gb2;
+    else if (tid < 3 * kH) out[kOffB1 + tid - 2 * kH] = gb1;
+    if (tid == 2 * kH) out[kOffB3] = gb3;
+    if (tid == 0) out[kNParam] = (float)loss;
+}
+
+// Sum of one parameter's partials over the blocks, in block order (FP64), 16 loads in flight.
+__device__ __forceinline__ double partial_sum(const float *__restrict__ part, int blocks, int p)
+{
+    double s = 0.0;
+    int b = 0;
+    for (; b + 16 <= blocks; b += 16) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = part[(int64_t)(b + i) * (kNParam + 1) + p];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += v[i];
     }
-    if (tid == 0) {
-        out[kOffB3] = G.gb3;
-        out[kNParam] = (float)G.loss;
-    }
+    for (; b < blocks; ++b) s += part[(int64_t)b * (kNParam + 1) + p];
+    return s;
 }
 
 // grad[p] = (sum over blocks, in block order) / count; loss likewise.
 __global__ void k_grad_reduce(const float *__restrict__ part, int blocks, double inv, float *__restrict__ grad,
-                              double *__restrict__ loss, float *__restrict__ loss_slot)
+                              double *__restrict__ loss)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p > kNParam) return;
-    double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += part[(int64_t)b * (kNParam + 1) + p];
-    if (p < kNParam) {
-        grad[p] = (float)(s * inv);
-    } else {
-        if (loss) *loss = s * inv;
-        if (loss_slot) *loss_slot = (float)(s * inv);
-    }
+    const double s = partial_sum(part, blocks, p);
+    if (p < kNParam) grad[p] = (float)(s * inv);
+    else if (loss) *loss = s * inv;
 }
 
-// Adam (Kingma & Ba 2015) on the FP32 master weights.
-__global__ void k_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ g, float lr, float b1, float b2, float eps, float c1, float c2)
+// One training step after the partials: the gradient as k_grad_reduce forms it, Adam (Kingma & Ba
+// 2015) on the FP32 master weights, and the BF16 copies as k_mlp_refresh makes them.
+__global__ void k_train_step(const float *__restrict__ part, int blocks, double inv, float *__restrict__ loss_slot,
+                             float *__restrict__ w, float *__restrict__ m, float *__restrict__ v, float lr, float b1,
+                             float b2, float eps, float c1, float c2, uint16_t *__restrict__ W1b,
+                             uint16_t *__restrict__ W2b, uint16_t *__restrict__ W2tb, float *__restrict__ w3r)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kNParam) return;
-    const float gp = g[p];
+    if (p > kNParam) return;
+    const double s = partial_sum(part, blocks, p);
+    if (p == kNParam) {
+        if (loss_slot) *loss_slot = (float)(s * inv);
+        return;
+    }
+    const float gp = (float)(s * inv);
     const float mp = b1 * m[p] + (1.f - b1) * gp;
     const float vp = b2 * v[p] + (1.f - b2) * gp * gp;
     m[p] = mp;
     v[p] = vp;
-    w[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
+    const float x = w[p] - lr * (mp / c1) / (sqrtf(vp / c2) + eps);
+    w[p] = x;
+    if (p < kOffB1) {
+        W1b[p] = f2bf(x);
+    } else if (p >= kOffW2 && p < kOffB2) {
+        const int e = p - kOffW2;
+        const uint16_t b = f2bf(x);
+        W2b[e] = b;
+        W2tb[(e % kH) * kH + e / kH] = b;
+    } else if (p >= kOffW3 && p < kOffB3) {
+        w3r[p - kOffW3] = bf2f(f2bf(x));
+    }
 }
 
 static void refresh(MlpT *m, hipStream_t st)
@@ -396,17 +498,15 @@ static void free_mlp(MlpT *m)
 }
 
 constexpr int kSamplesPerBlock = 8;
+static int grad_blocks(int64_t nsamples) { return (int)((nsamples + kSamplesPerBlock - 1) / kSamplesPerBlock); }
 
-static bnos_status grad_impl(MlpT *m, const float *feats, const int32_t *pairs, int64_t count, int64_t first,
-                             int64_t nsamples, int64_t stride, int64_t offset, int n, double eps, float *grad,
-                             double *loss, float *loss_slot, float *part, hipStream_t st)
+// The blocks' partial gradients of samples first .. first + nsamples of an epoch's order.
+static bnos_status launch_grad(MlpT *m, const float *feats, const int32_t *pairs, int64_t count, int64_t first,
+                               int64_t nsamples, int64_t stride, int64_t offset, int n, double eps, float *part,
+                               hipStream_t st)
 {
-    const int blocks = (int)((nsamples + kSamplesPerBlock - 1) / kSamplesPerBlock);
-    hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(kGradWaves * 64), 0, st, mlp_view(m), feats, pairs, count, first, nsamples,
-                       stride, offset, n, kSamplesPerBlock, eps, part);
-    BNOS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_grad_reduce, dim3((kNParam + 1 + 255) / 256), dim3(256), 0, st, part, blocks,
-                       1.0 / (double)nsamples, grad, loss, loss_slot);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(grad_blocks(nsamples)), dim3(kGradWaves * 64), 0, st, mlp_view(m), feats, pairs,
+                       count, first, nsamples, stride, offset, n, kSamplesPerBlock, eps, part);
     BNOS_HIP(hipGetLastError());
     return BNOS_OK;
 }
@@ -549,8 +649,8 @@ extern "C" bnos_status bnos_mlp_forward(bnos_mlp h, const float *feats, int32_t 
     if (!feats || !logits) { set_error("NULL argument"); return BNOS_E_INVALID; }
     if (R < 1 || n < 2 || n > 64) { set_error("need R >= 1 and 2 <= n <= 64"); return BNOS_E_RANGE; }
     BNOS_HIP(hipSetDevice(m->device));
-    hipLaunchKernelGGL(k_mlp_forward, dim3(R), dim3(1024), 0, reinterpret_cast<hipStream_t>(stream), mlp_view(m),
-                       feats, n, logits);
+    hipLaunchKernelGGL(k_mlp_forward, dim3(R < 512 ? R : 512), dim3(1024), 0, reinterpret_cast<hipStream_t>(stream),
+                       mlp_view(m), feats, R, n, logits);
     BNOS_HIP(hipGetLastError());
     return BNOS_OK;
 }
@@ -565,10 +665,15 @@ extern "C" bnos_status bnos_mlp_grad(bnos_mlp h, const float *feats, const int32
     if (!(eps >= 0.f && eps <= 1.f)) { set_error("eps outside [0, 1]"); return BNOS_E_RANGE; }
     BNOS_HIP(hipSetDevice(m->device));
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int blocks = (R + kSamplesPerBlock - 1) / kSamplesPerBlock;
+    const int blocks = grad_blocks(R);
     float *part = nullptr;
     BNOS_HIP(hipMalloc((void **)&part, sizeof(float) * (size_t)blocks * (kNParam + 1)));
-    bnos_status s = grad_impl(m, feats, pairs, R, 0, R, 1, 0, n, eps, grad, loss, nullptr, part, st);
+    bnos_status s = launch_grad(m, feats, pairs, R, 0, R, 1, 0, n, eps, part, st);
+    if (s == BNOS_OK) {
+        hipLaunchKernelGGL(k_grad_reduce, dim3((kNParam + 1 + 255) / 256), dim3(256), 0, st, part, blocks,
+                           1.0 / (double)R, grad, loss);
+        if (hipGetLastError() != hipSuccess) { s = BNOS_E_DEVICE; set_error("gradient launch failed"); }
+    }
     hipError_t e = hipStreamSynchronize(st);
     hipFree(part);
     if (s != BNOS_OK) return s;
@@ -605,10 +710,8 @@ extern "C" bnos_status bnos_mlp_train(bnos_mlp h, const float *feats, const int3
     BNOS_HIP(hipSetDevice(m->device));
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const int64_t bsz = batch < count ? batch : count;
-    const int blocks = (int)((bsz + kSamplesPerBlock - 1) / kSamplesPerBlock);
-    float *part = nullptr, *grad = nullptr;
-    BNOS_HIP(hipMalloc((void **)&part, sizeof(float) * (size_t)blocks * (kNParam + 1) + sizeof(float) * kNParam + 64));
-    grad = part + (size_t)blocks * (kNParam + 1);
+    float *part = nullptr;
+    BNOS_HIP(hipMalloc((void **)&part, sizeof(float) * (size_t)grad_blocks(bsz) * (kNParam + 1)));
     const int64_t steps_per_epoch = (count + bsz - 1) / bsz;
     int64_t step = 0;
     bnos_status s = BNOS_OK;
@@ -621,15 +724,14 @@ extern "C" bnos_status bnos_mlp_train(bnos_mlp h, const float *feats, const int3
         for (int64_t b = 0; b < steps_per_epoch && s == BNOS_OK; ++b) {
             const int64_t first = b * bsz;
             const int64_t ns = (first + bsz <= count) ? bsz : count - first;
-            s = grad_impl(m, feats, pairs, count, first, ns, stride, offset, n, eps, grad, nullptr,
-                          loss_trace ? loss_trace + step : nullptr, part, st);
+            s = launch_grad(m, feats, pairs, count, first, ns, stride, offset, n, eps, part, st);
             if (s != BNOS_OK) break;
             ++m->adam_t;
             const float b1 = 0.9f, b2 = 0.999f;
             const float c1 = 1.f - powf(b1, (float)m->adam_t), c2 = 1.f - powf(b2, (float)m->adam_t);
-            hipLaunchKernelGGL(k_adam, dim3((kNParam + 255) / 256), dim3(256), 0, st, m->d_master, m->d_m, m->d_v,
-                               grad, lr, b1, b2, 1e-8f, c1, c2);
-            refresh(m, st);
+            hipLaunchKernelGGL(k_train_step, dim3((kNParam + 1 + 127) / 128), dim3(128), 0, st, part, grad_blocks(ns),
+                               1.0 / (double)ns, loss_trace ? loss_trace + step : nullptr, m->d_master, m->d_m, m->d_v,
+                               lr, b1, b2, 1e-8f, c1, c2, m->d_W1b, m->d_W2b, m->d_W2tb, m->d_w3r);
             if (hipGetLastError() != hipSuccess) { s = BNOS_E_DEVICE; set_error("training launch failed"); }
             ++step;
         }

@@ -86,15 +86,6 @@ __device__ __forceinline__ v4f mfma32(v4u a, v4u b, v4f c)
 // Eight consecutive bf16 values (16-byte aligned) as one operand register set.
 __device__ __forceinline__ v4u ld8(const uint16_t *p) { return *reinterpret_cast<const v4u *>(p); }
 
-// Eight bf16 values p[0], p[s], ..., p[7 s] (a column of a row-major array).
-__device__ __forceinline__ v4u ld8_strided(const uint16_t *p, int s)
-{
-    v4u v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = (uint32_t)p[(2 * j) * s] | ((uint32_t)p[(2 * j + 1) * s] << 16);
-    return v;
-}
-
 // LDS of one forward pass (16-byte aligned: operands are read with 16-byte LDS loads).
 struct alignas(16) MlpLds {
     uint16_t z[kRows][16];          // normalised features: hi in columns 0..7, lo in 8..15
@@ -103,80 +94,96 @@ struct alignas(16) MlpLds {
     float logit[kRows];
 };
 
-// Forward pass of one sample (rows <= 64 nodes) by a block of 1-32 wavefronts.
-// zraw: raw features [rows][8] (LDS or global).  If h2 != null, relu(layer 2)
-// is also stored there ([64][128] floats, for the backward pass).  The
-// logits land in L.logit[0..rows).  Fixed reduction orders: deterministic.
-__device__ __forceinline__ void mlp_forward_block(const MlpView &P, const float *zraw, int rows, MlpLds &L,
-                                                  float *h2)
+// x[0] w[0] + ... + x[15] w[15] over the lanes of a row of 16, in the row's lane 0 (other lanes: not
+// the sum): neighbours first, the even lane's product taken unrounded, then by twos, fours and eights.
+template <int CTRL>
+__device__ __forceinline__ float row_moved_f32(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_dot_f32(float x, float w)
+{
+    float v = fmaf(x, w, row_moved_f32<0xb1>(x * w));    // quad_perm: lane ^ 1
+    v = v + row_moved_f32<0x4e>(v);                      // lane ^ 2
+    v = v + row_moved_f32<0x104>(v);                     // row_shl: lane + 4
+    return v + row_moved_f32<0x108>(v);                  // lane + 8
+}
+
+// A wavefront's share of the weights: the 16 hidden units of column tile wave % 8 in both layers, as
+// the operands the matrix cores take.  Loaded once for as many samples as the caller has (a
+// tile's operands requested where they were used made every tile wait for L2).
+struct MlpRegs {
+    v4u w1, w2[4];
+    float b1, b2, w3;
+};
+
+__device__ __forceinline__ MlpRegs mlp_load(const MlpView &P, int wave, int lane)
+{
+    const int li = lane & 15, g = lane >> 4, u = (wave & 7) * 16 + li;
+    MlpRegs R;
+    R.w1 = (v4u){0u, 0u, 0u, 0u};
+    if (g < 2) R.w1 = ld8(P.W1b + u * kF);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) R.w2[q] = ld8(P.W2b + u * kH + q * 32 + 8 * g);
+    R.b1 = P.b1[u];
+    R.b2 = P.b2[u];
+    R.w3 = P.w3r[u];
+    return R;
+}
+
+// Forward pass of one sample (rows <= 64 nodes) by a block of 8, 16, 24 or 32 wavefronts: wavefront w
+// takes the columns of tile w % 8 for the row tiles w / 8, w / 8 + waves / 8, ... that hold rows.
+// zraw: raw features [rows][8] (LDS or global).  The logits land in L.logit[0..rows).  Fixed
+// reduction orders: deterministic.
+__device__ __forceinline__ void mlp_forward_block(const MlpView &P, const MlpRegs &R, const float *zraw, int rows,
+                                                  MlpLds &L)
 {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int nw = blockDim.x >> 6;
-    for (int e = tid; e < kRows * kF; e += blockDim.x) {
+    const int tiles = (rows + 15) >> 4;
+    for (int e = tid; e < tiles * 16 * kF; e += blockDim.x) {
         const int r = e / kF, k = e % kF;
         float v = 0.f;
         if (r < rows) v = (zraw[r * kF + k] - P.norm[k]) * P.norm[kF + k];
         split_bf(v, L.z[r][k], L.z[r][kF + k]);
     }
     __syncthreads();
-    const int li = lane & 15, g = lane >> 4;
-    // layer 1: 4 row tiles x 8 column tiles, one K = 32 step: A = [z_hi | z_lo | 0 | 0],
-    // B = [W1^T; W1^T; 0; 0], so the product is (z_hi + z_lo) W1^T
-    for (int tile = wave; tile < 32; tile += nw) {
-        const int rt = tile >> 3, ct = tile & 7;
-        v4u a = {0u, 0u, 0u, 0u}, b = {0u, 0u, 0u, 0u};
-        if (g < 2) {
-            a = ld8(&L.z[rt * 16 + li][8 * g]);
-            b = ld8(P.W1b + (ct * 16 + li) * kF);
-        }
-        const v4f d = mfma32(a, b, (v4f){0.f, 0.f, 0.f, 0.f});
-        const int u = ct * 16 + li;
+    const int li = lane & 15, g = lane >> 4, ct = wave & 7, u = ct * 16 + li;
+    // layer 1: one K = 32 step per tile: A = [z_hi | z_lo | 0 | 0], B = [W1^T; W1^T; 0; 0], so
+    // the product is (z_hi + z_lo) W1^T
+    for (int rt = wave >> 3; rt < tiles; rt += nw >> 3) {
+        v4u a = {0u, 0u, 0u, 0u};
+        if (g < 2) a = ld8(&L.z[rt * 16 + li][8 * g]);
+        const v4f d = mfma32(a, R.w1, (v4f){0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float x = d[r] + P.b1[u];
+            const float x = d[r] + R.b1;
             split_bf(x > 0.f ? x : 0.f, L.h1[0][rt * 16 + 4 * g + r][u], L.h1[1][rt * 16 + 4 * g + r][u]);
         }
     }
     __syncthreads();
     // layer 2: K = 128 inputs, taken twice (hi, then lo), each against W2; then
     // the layer-3 dot products per column tile
-    for (int tile = wave; tile < 32; tile += nw) {
-        const int rt = tile >> 3, ct = tile & 7;
+    for (int rt = wave >> 3; rt < tiles; rt += nw >> 3) {
         v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int part = s >> 2, kb = (s & 3) * 32 + 8 * g;
-            d = mfma32(ld8(&L.h1[part][rt * 16 + li][kb]), ld8(P.W2b + (ct * 16 + li) * kH + kb), d);
-        }
-        const int u = ct * 16 + li;
-        float q[4];
+        for (int s = 0; s < 8; ++s)
+            d = mfma32(ld8(&L.h1[s >> 2][rt * 16 + li][(s & 3) * 32 + 8 * g]), R.w2[s & 3], d);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float x = d[r] + P.b2[u];
-            x = x > 0.f ? x : 0.f;
-            if (h2) h2[(rt * 16 + 4 * g + r) * kH + u] = x;
-            q[r] = x * P.w3r[u];
+            const float x = d[r] + R.b2;
+            const float q = row_dot_f32(x > 0.f ? x : 0.f, R.w3);
+            if (li == 0) L.part[rt * 16 + 4 * g + r][ct] = q;
         }
-        // sum over the 16 columns of the tile (lanes with equal l/16), fixed butterfly
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float o = __shfl_xor(q[r], off, 64);
-                q[r] = (li & off) ? (o + q[r]) : (q[r] + o);
-            }
-        if (li == 0)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) L.part[rt * 16 + 4 * g + r][ct] = q[r];
     }
     __syncthreads();
     if (tid < kRows) {
         float s = P.b3[0];
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) s += L.part[tid][ct];
-        L.logit[tid] = s;
+        for (int c = 0; c < 8; ++c) s += L.part[tid][c];
+        L.logit[tid] = s;                    // (past the row tiles: unused)
     }
     __syncthreads();
 }
