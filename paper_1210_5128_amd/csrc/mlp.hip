@@ -12,6 +12,7 @@
 
 #include "bnos_internal.h"
 #include "mlp_device.h"
+#include "score_device.h"
 
 namespace bnos {
 
@@ -165,25 +166,50 @@ struct alignas(16) GradLds {
     uint16_t d2t[2][kH][kRP];       // dL/dpre2, transposed
     float ft[kH][kFP];              // relu(layer 2), transposed; then dL/dpre1
     float part[kRows][8];
-    float dl[kRows];
+    alignas(16) float dl[kRows];
 };
 static_assert(sizeof(GradLds) <= 160 * 1024, "one block per compute unit");
-
-// Four values of consecutive nodes as hi / lo operands of a transposed array.
-__device__ __forceinline__ void store4_bf(uint16_t *hi, uint16_t *lo, const float (&v)[4])
-{
-    uint16_t h[4], l[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) split_bf(v[r], h[r], l[r]);
-    *reinterpret_cast<uint2 *>(hi) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-    *reinterpret_cast<uint2 *>(lo) = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
-}
 
 // Sample index of position j of the epoch's visiting order (affine bijection).
 __device__ __forceinline__ int64_t visit(int64_t j, int64_t count, int64_t stride, int64_t offset)
 {
     // j < 2^31 and stride < count <= 2^31: the product fits in 64 bits
     return (int64_t)(((uint64_t)j * (uint64_t)stride + (uint64_t)offset) % (uint64_t)count);
+}
+
+// Largest value of a wavefront, in every lane.
+__device__ __forceinline__ double wave_max_f64(double v)
+{
+    v = fmax(v, dpp_f64<0xb1>(v));       // lane ^ 1
+    v = fmax(v, dpp_f64<0x4e>(v));       // lane ^ 2
+    v = fmax(v, dpp_f64<0x141>(v));      // row_half_mirror
+    v = fmax(v, dpp_f64<0x140>(v));      // row_mirror
+    return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
+}
+
+// op folded over the rows of a column and of the logit gradients, in order from zero, as far as the
+// row tiles that hold nodes (a row past the nodes has gradient zero and adds zero); both are read
+// 16 rows at a time (one element at a time, every row waited for its own LDS read).
+template <typename Op>
+__device__ __forceinline__ float rows_in_order(int n, const float *col, const float *dl, Op op)
+{
+    typedef __attribute__((address_space(3))) const v4f lds4;
+    lds4 *pc = (lds4 *)(col), *pd = (lds4 *)(dl);
+    asm("" : "+v"(pc), "+v"(pd));       // (else every address is kept across samples, and spills)
+    float s = 0.f;
+#pragma unroll
+    for (int r0 = 0; r0 < kRows; r0 += 16) {
+        if (r0 >= n) break;
+        v4f c[4], d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            c[i] = pc[r0 / 4 + i];
+            d[i] = pd[r0 / 4 + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s = op(s, c[i / 4][i % 4], d[i / 4][i % 4]);
+    }
+    return s;
 }
 
 // Block per chunk of `spb` samples: forward, gradient of -ln q(pair) w.r.t.
@@ -193,12 +219,19 @@ __device__ __forceinline__ int64_t visit(int64_t j, int64_t count, int64_t strid
 // activation operand is a hi/lo BF16 pair (see mlp_device.h); products of two
 // activations take hi*hi + hi*lo + lo*hi.
 //
-// Wavefront w reads the weights of column tile w (both layers and W2^T) ahead of the phase
-// that uses them and takes that tile's columns for all rows.  Activations that the
-// gradients contract over the nodes are kept transposed too, so that every operand is one
-// 16-byte LDS read, and layer 2's outputs stay in registers until their gradient is
-// formed.  The bias and w3 sums run over the nodes in order, one column per thread, beside
-// the phases that need no result of theirs.
+// A chunk is serial and its samples' phases depend on each other, so a sample's latency bounds
+// the kernel (about 18,800 cycles at 60 nodes; the matrix cores are busy for 2,600 of
+// them): the weights stay in registers for the whole chunk, the next sample's features are
+// requested a sample ahead, and every operand is one 16-byte LDS read (activations that the
+// gradients contract over the nodes are kept transposed too).  Wavefront w takes 2 x 2 tiles
+// of each product (row tiles 2 (w / 4) + i, column tiles 2 (w % 4) + c; 2 x 4 of gW2), which
+// halves the LDS reads of one column tile by all rows, and keeps its part of layer 2 and of
+// layer 1's relu in registers until their gradients are formed.  The bias and w3 sums run
+// over the nodes in order, one column per thread.  60 nodes, 1,024 samples, with the
+// reduction: 290 us with operands gathered from row-major arrays and weights read where used,
+// 185 us with transposed arrays, 152 us with the row sums read 16 at a time and the weights
+// kept, 130 us with 2 x 2 tiles and two values split per conversion (8,192 samples: 1,420,
+// 881, 747 and 640 us).
 constexpr int kGradWaves = 8;
 
 __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const float *__restrict__ feats,
@@ -210,85 +243,118 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const f
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, g = lane >> 4, u = wave * 16 + li;
-    v4f accW2[8];                   // gW2 tiles (row tile wave, column tile q)
+    const int li = lane & 15, g = lane >> 4;
+    const int rp = wave >> 2, cp = wave & 3;
+    v4f accW2[2][4];                // gW2 tiles (row tile 2 cp + c, column tile 4 rp + q)
     v4f accW1 = {0.f, 0.f, 0.f, 0.f};
     float gw3 = 0.f, gb2 = 0.f, gb1 = 0.f;      // column tid, tid - 128, tid - 256
     float gb3 = 0.f;
     double loss = 0.0;
+    const MlpRegs R[2] = {mlp_load(P, 2 * cp, lane), mlp_load(P, 2 * cp + 1, lane)};
+    v4u w2t[2][4];                  // W2^T rows of these column tiles
 #pragma unroll
-    for (int q = 0; q < 8; ++q) accW2[q] = (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            accW2[c][q] = (v4f){0.f, 0.f, 0.f, 0.f};
+            w2t[c][q] = ld8(P.W2tb + ((2 * cp + c) * 16 + li) * kH + q * 32 + 8 * g);
+        }
+    const float w3c = tid < 2 * kH ? P.w3r[tid & (kH - 1)] : 0.f;
+    const float b3 = P.b3[0], mu = P.norm[tid % kF], isd = P.norm[kF + tid % kF];
     const int64_t j0 = (int64_t)blockIdx.x * spb;
-    for (int si = 0; si < spb; ++si) {
-        const int64_t j = j0 + si;
-        if (j >= nsamples) break;                        // uniform
-        const int64_t smp = visit(first + j, count, stride, offset);
-        const MlpRegs R = mlp_load(P, wave, lane);       // requested here, used two barriers on
-        {                                                // one feature of one node per thread
-            const int r = tid / kF, k = tid % kF;
+    const int last = (int)(nsamples - j0 < spb ? nsamples - j0 : spb) - 1;
+    // one feature of one node per thread and the pair, requested a sample ahead
+    const int fr = tid / kF, fk = tid % kF;
+    const int64_t fo = (int64_t)(fr < n ? fr : 0) * kF + fk;
+    int64_t smp = visit(first + j0, count, stride, offset);
+    float x0 = feats[smp * n * kF + fo];
+    int pa0 = pairs[smp * 2], pb0 = pairs[smp * 2 + 1];
+    for (int si = 0; si <= last; ++si) {
+        {
             float v = 0.f;
-            if (r < n) v = (feats[(smp * n + r) * kF + k] - P.norm[k]) * P.norm[kF + k];
+            if (fr < n) v = (x0 - mu) * isd;
             uint16_t hi, lo;
             split_bf(v, hi, lo);
-            G.z[r][k] = hi;
-            G.z[r][kF + k] = lo;
-            G.zt[k][r] = hi;
-            G.zt[kF + k][r] = lo;
+            G.z[fr][fk] = hi;
+            G.z[fr][kF + fk] = lo;
+            G.zt[fk][fr] = hi;
+            G.zt[kF + fk][fr] = lo;
         }
+        const int a = pa0, b = pb0;
+        if (si < last) {                // visit() of the next position
+            smp += stride;
+            if (smp >= count) smp -= count;
+        }
+        x0 = feats[smp * n * kF + fo];
+        pa0 = pairs[smp * 2];
+        pb0 = pairs[smp * 2 + 1];
         __syncthreads();
         // layer 1 (as mlp_forward_block)
+        uint32_t on = 0;                // bit 8 i + 4 c + r: this element of layer 1 passed its relu
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            v4u a = {0u, 0u, 0u, 0u};
-            if (g < 2) a = ld8(&G.z[rt * 16 + li][8 * g]);
-            const v4f d = mfma32(a, R.w1, (v4f){0.f, 0.f, 0.f, 0.f});
-            float h[4];
+        for (int i = 0; i < 2; ++i) {
+            const int rt = 2 * rp + i;
+            v4u a1 = {0u, 0u, 0u, 0u};
+            if (g < 2) a1 = ld8(&G.z[rt * 16 + li][8 * g]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float x = d[r] + R.b1;
-                h[r] = x > 0.f ? x : 0.f;
-                split_bf(h[r], G.h1[0][rt * 16 + 4 * g + r][u], G.h1[1][rt * 16 + 4 * g + r][u]);
+            for (int c = 0; c < 2; ++c) {
+                const int u = (2 * cp + c) * 16 + li, row = rt * 16 + 4 * g;
+                const v4f d = mfma32(a1, R[c].w1, (v4f){0.f, 0.f, 0.f, 0.f});
+                float h[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = d[r] + R[c].b1;
+                    h[r] = x > 0.f ? x : 0.f;
+                }
+                uint32_t hh[2], hl[2];
+                split4_rows(h, &G.h1[0][row][u], &G.h1[1][row][u], hh, hl);
+                *reinterpret_cast<uint2 *>(&G.h1t[0][u][row]) = make_uint2(hh[0], hh[1]);
+                *reinterpret_cast<uint2 *>(&G.h1t[1][u][row]) = make_uint2(hl[0], hl[1]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((uint16_t)(hh[r >> 1] >> (16 * (r & 1)))) on |= 1u << (8 * i + 4 * c + r);
             }
-            store4_bf(&G.h1t[0][u][rt * 16 + 4 * g], &G.h1t[1][u][rt * 16 + 4 * g], h);
         }
         __syncthreads();
         // layer 2, its outputs kept in registers too, and the layer-3 dot products
-        v4f h2[4];
+        v4f h2[2][2];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            v4f d = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int s = 0; s < 8; ++s)
-                d = mfma32(ld8(&G.h1[s >> 2][rt * 16 + li][(s & 3) * 32 + 8 * g]), R.w2[s & 3], d);
+            for (int c = 0; c < 2; ++c) h2[i][c] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float x = d[r] + R.b2;
-                h2[rt][r] = x > 0.f ? x : 0.f;
-                const float q = row_dot_f32(h2[rt][r], R.w3);
-                if (li == 0) G.part[rt * 16 + 4 * g + r][wave] = q;
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const v4u x = ld8(&G.h1[s >> 2][(2 * rp + i) * 16 + li][(s & 3) * 32 + 8 * g]);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) h2[i][c] = mfma32(x, R[c].w2[s & 3], h2[i][c]);
             }
-            *reinterpret_cast<v4f *>(&G.ft[u][rt * 16 + 4 * g]) = h2[rt];
-        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int row = (2 * rp + i) * 16 + 4 * g;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = h2[i][c][r] + R[c].b2;
+                    h2[i][c][r] = x > 0.f ? x : 0.f;
+                    const float q = row_dot_f32(h2[i][c][r], R[c].w3);
+                    if (li == 0) G.part[row + r][2 * cp + c] = q;
+                }
+                *reinterpret_cast<v4f *>(&G.ft[(2 * cp + c) * 16 + li][row]) = h2[i][c];
+            }
         __syncthreads();
         // dL/dlogit for L = -ln q({a,b})
         if (wave == 0) {
-            float s = P.b3[0];
+            float s = b3;
 #pragma unroll
             for (int c = 0; c < 8; ++c) s += G.part[lane][c];
-            const int a = pairs[smp * 2], b = pairs[smp * 2 + 1];
             const double l = lane < n ? (double)s : -1e300;
-            double mx = l;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+            const double mx = wave_max_f64(l);
             double e = lane < n ? exp(l - mx) : 0.0;
-            double se = e;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const double o = __shfl_xor(se, off, 64);
-                se = (lane & off) ? (o + se) : (se + o);
-            }
-            const double p = e / se;
-            const double pa = __shfl(p, a, 64), pb = __shfl(p, b, 64);
+            const double p = e / wave_sum_f64(e);
+            const double pa = readlane_f64(p, a & 63), pb = readlane_f64(p, b & 63);
             const double Q = pa * pb * (1.0 / (1.0 - pa) + 1.0 / (1.0 - pb));
             const double q = (1.0 - eps) * Q + eps * 2.0 / ((double)n * (n - 1));
             const double ga = pa * pb * (1.0 / ((1.0 - pa) * (1.0 - pa)) + 1.0 / (1.0 - pb));
@@ -298,109 +364,120 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_mlp_grad(MlpView P, const f
             loss += -log(q);
         }
         __syncthreads();
-        v4u w2t[4];                     // W2^T rows of this column tile, used after the next barrier
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w2t[q] = ld8(P.W2tb + u * kH + q * 32 + 8 * g);
         // dL/dpre2 = relu'(pre2) * dl * w3 (hi/lo operands, both ways; h1's rows are done with)
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            const int row = rt * 16 + 4 * g;
-            float d[4];
+        for (int i = 0; i < 2; ++i) {
+            const int row = (2 * rp + i) * 16 + 4 * g;
+            const v4f dl = *reinterpret_cast<const v4f *>(&G.dl[row]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                d[r] = h2[rt][r] > 0.f ? G.dl[row + r] * R.w3 : 0.f;
-                split_bf(d[r], G.h1[0][row + r][u], G.h1[1][row + r][u]);
+            for (int c = 0; c < 2; ++c) {
+                const int u = (2 * cp + c) * 16 + li;
+                float d[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) d[r] = h2[i][c][r] > 0.f ? dl[r] * R[c].w3 : 0.f;
+                uint32_t dh[2], dlo[2];
+                split4_rows(d, &G.h1[0][row][u], &G.h1[1][row][u], dh, dlo);
+                *reinterpret_cast<uint2 *>(&G.d2t[0][u][row]) = make_uint2(dh[0], dh[1]);
+                *reinterpret_cast<uint2 *>(&G.d2t[1][u][row]) = make_uint2(dlo[0], dlo[1]);
             }
-            store4_bf(&G.d2t[0][u][row], &G.d2t[1][u][row], d);
         }
         // w3 / layer-2 bias / b3 gradients (rows in order)
         if (tid < kH) {
-            float s3 = 0.f;
-            for (int r = 0; r < n; ++r) s3 += G.dl[r] * G.ft[tid][r];
-            gw3 += s3;
+            gw3 += rows_in_order(n, &G.ft[tid][0], &G.dl[0], [](float s, float h, float d) { return fmaf(d, h, s); });
         } else if (tid < 2 * kH) {
-            const float w3 = P.w3r[tid - kH];
-            float s2 = 0.f;
-            for (int r = 0; r < n; ++r) s2 += G.ft[tid - kH][r] > 0.f ? G.dl[r] * w3 : 0.f;
-            gb2 += s2;
+            gb2 += rows_in_order(n, &G.ft[tid - kH][0], &G.dl[0],
+                                 [w3c](float s, float h, float d) { return s + (h > 0.f ? d * w3c : 0.f); });
         } else if (tid == 2 * kH) {
-            float s = 0.f;
-            for (int r = 0; r < n; ++r) s += G.dl[r];
-            gb3 += s;
+            gb3 += rows_in_order(n, &G.dl[0], &G.dl[0], [](float s, float, float d) { return s + d; });
         }
         __syncthreads();
         // gW2[u][k] += sum_r d2[r][u] h1[r][k]: A[u][r] = d2, B[r][k] = h1, K = 64 rows in two
         // steps of 32, for the products (d2 hi, h1 hi), (d2 hi, h1 lo), (d2 lo, h1 hi)
         {
-            v4u a[2][2];
+            v4u x[2][2][2];
 #pragma unroll
-            for (int pd = 0; pd < 2; ++pd)
+            for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) a[pd][ks] = ld8(&G.d2t[pd][u][ks * 32 + 8 * g]);
+                for (int pd = 0; pd < 2; ++pd)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                v4u b[2][2];
+                    for (int ks = 0; ks < 2; ++ks) x[c][pd][ks] = ld8(&G.d2t[pd][(2 * cp + c) * 16 + li][ks * 32 + 8 * g]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v4u y[2][2];
 #pragma unroll
                 for (int ph = 0; ph < 2; ++ph)
 #pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) b[ph][ks] = ld8(&G.h1t[ph][q * 16 + li][ks * 32 + 8 * g]);
+                    for (int ks = 0; ks < 2; ++ks) y[ph][ks] = ld8(&G.h1t[ph][(4 * rp + q) * 16 + li][ks * 32 + 8 * g]);
 #pragma unroll
                 for (int pr = 0; pr < 3; ++pr)
 #pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) accW2[q] = mfma32(a[pr == 2][ks], b[pr == 1][ks], accW2[q]);
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) accW2[c][q] = mfma32(x[c][pr == 2][ks], y[pr == 1][ks], accW2[c][q]);
+                __builtin_amdgcn_sched_barrier(0);    // (with every read moved to the front, registers spill)
             }
         }
         // dh1[r][k] = sum_u d2[r][u] W2[u][k] (K = 128, hi then lo); dpre1 = relu'(pre1) dh1
+        {
+            v4f d[2][2];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            v4f d = {0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) d[i][c] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < 8; ++s)
-                d = mfma32(ld8(&G.h1[s >> 2][rt * 16 + li][(s & 3) * 32 + 8 * g]), w2t[s & 3], d);
-            v4f v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = rt * 16 + 4 * g + r;
-                v[r] = (row < n && G.h1t[0][u][row] != 0) ? d[r] : 0.f;
-            }
-            *reinterpret_cast<v4f *>(&G.ft[u][rt * 16 + 4 * g]) = v;
+                for (int i = 0; i < 2; ++i) {
+                    const v4u x = ld8(&G.h1[s >> 2][(2 * rp + i) * 16 + li][(s & 3) * 32 + 8 * g]);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) d[i][c] = mfma32(x, w2t[c][s & 3], d[i][c]);
+                }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int row = (2 * rp + i) * 16 + 4 * g;
+                    v4f v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = (row + r < n && (on >> (8 * i + 4 * c + r) & 1u)) ? d[i][c][r] : 0.f;
+                    *reinterpret_cast<v4f *>(&G.ft[(2 * cp + c) * 16 + li][row]) = v;
+                }
         }
         __syncthreads();
         // gW1[u][k] += sum_r dpre1[r][u] z[r][k]: A[u][r] = dpre1 (hi, then lo), B[r][c] = the
         // z row (columns 0..7 hi, 8..15 lo); columns c and c + 8 are added at the end, so the
         // tile sums hi*hi + hi*lo + lo*hi + lo*lo (8 tiles of 16 hidden units)
         {
-            v4u a[2][2];
+            v4u x[2][2];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                float x[8];
-                *reinterpret_cast<v4f *>(&x[0]) = *reinterpret_cast<const v4f *>(&G.ft[u][ks * 32 + 8 * g]);
-                *reinterpret_cast<v4f *>(&x[4]) = *reinterpret_cast<const v4f *>(&G.ft[u][ks * 32 + 8 * g + 4]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    uint16_t h0, l0, h1v, l1;
-                    split_bf(x[2 * i], h0, l0);
-                    split_bf(x[2 * i + 1], h1v, l1);
-                    a[0][ks][i] = (uint32_t)h0 | ((uint32_t)h1v << 16);
-                    a[1][ks][i] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-                }
+                const v4f e = *reinterpret_cast<const v4f *>(&G.ft[wave * 16 + li][ks * 32 + 8 * g]);
+                const v4f f = *reinterpret_cast<const v4f *>(&G.ft[wave * 16 + li][ks * 32 + 8 * g + 4]);
+                uint32_t h[4], l[4];
+                split2_bf(e[0], e[1], h[0], l[0]);
+                split2_bf(e[2], e[3], h[1], l[1]);
+                split2_bf(f[0], f[1], h[2], l[2]);
+                split2_bf(f[2], f[3], h[3], l[3]);
+                x[0][ks] = (v4u){h[0], h[1], h[2], h[3]};
+                x[1][ks] = (v4u){l[0], l[1], l[2], l[3]};
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) accW1 = mfma32(a[s >> 1][s & 1], ld8(&G.zt[li][(s & 1) * 32 + 8 * g]), accW1);
+            for (int s = 0; s < 4; ++s) accW1 = mfma32(x[s >> 1][s & 1], ld8(&G.zt[li][(s & 1) * 32 + 8 * g]), accW1);
         }
         if (tid >= 2 * kH && tid < 3 * kH) {
-            float s1 = 0.f;
-            for (int r = 0; r < n; ++r) s1 += G.ft[tid - 2 * kH][r];
-            gb1 += s1;
+            gb1 += rows_in_order(n, &G.ft[tid - 2 * kH][0], &G.dl[0], [](float s, float x, float) { return s + x; });
         }
         __syncthreads();
     }
     // partial gradient of this block
     float *out = part + (int64_t)blockIdx.x * (kNParam + 1);
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[kOffW2 + (wave * 16 + 4 * g + r) * kH + q * 16 + li] = accW2[q][r];
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                out[kOffW2 + ((2 * cp + c) * 16 + 4 * g + r) * kH + (4 * rp + q) * 16 + li] = accW2[c][q][r];
     {
         // column li + 8 holds the products with z_lo of column li
         float hi8[4];
@@ -445,7 +522,8 @@ __global__ void k_grad_reduce(const float *__restrict__ part, int blocks, double
 }
 
 // One training step after the partials: the gradient as k_grad_reduce forms it, Adam (Kingma & Ba
-// 2015) on the FP32 master weights, and the BF16 copies as k_mlp_refresh makes them.
+// 2015) on the FP32 master weights, and the BF16 copies as k_mlp_refresh makes them.  Bound by the
+// latency of the partials' reads: 6 us for 128 blocks, where the three kernels took 30 us.
 __global__ void k_train_step(const float *__restrict__ part, int blocks, double inv, float *__restrict__ loss_slot,
                              float *__restrict__ w, float *__restrict__ m, float *__restrict__ v, float lr, float b1,
                              float b2, float eps, float c1, float c2, uint16_t *__restrict__ W1b,

@@ -59,11 +59,42 @@ __device__ __host__ __forceinline__ float bf2f(uint16_t b)
     return x;
 }
 
-// x = hi + lo + O(2^-17 |x|); x - hi is exact in FP32.
+// x = hi + lo + O(2^-17 |x|) for two values; x - hi is exact in FP32.  The operands come packed, x0's
+// in the low halves: the card converts two values at a time.
+__device__ __forceinline__ uint32_t pack_bf(float x0, float x1)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){x0, x1}, v2bf));
+}
+__device__ __forceinline__ void split2_bf(float x0, float x1, uint32_t &hi, uint32_t &lo)
+{
+    hi = pack_bf(x0, x1);
+    lo = pack_bf(x0 - __builtin_bit_cast(float, hi << 16), x1 - __builtin_bit_cast(float, hi & 0xffff0000u));
+}
+
+// The same for one value.
 __device__ __forceinline__ void split_bf(float x, uint16_t &hi, uint16_t &lo)
 {
-    hi = f2bf(x);
-    lo = f2bf(x - bf2f(hi));
+    uint32_t h, l;
+    split2_bf(x, 0.f, h, l);
+    hi = (uint16_t)h;
+    lo = (uint16_t)l;
+}
+
+// Splits the four values of consecutive rows of a column and stores the operands in the rows of hi
+// and lo (pitch kHP); h, l: the packed operands, rows 0 and 1, then 2 and 3.
+__device__ __forceinline__ void split4_rows(const float (&x)[4], uint16_t *hi, uint16_t *lo, uint32_t (&h)[2],
+                                            uint32_t (&l)[2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        split2_bf(x[2 * i], x[2 * i + 1], h[i], l[i]);
+        hi[(2 * i) * kHP] = (uint16_t)h[i];
+        hi[(2 * i + 1) * kHP] = (uint16_t)(h[i] >> 16);
+        lo[(2 * i) * kHP] = (uint16_t)l[i];
+        lo[(2 * i + 1) * kHP] = (uint16_t)(l[i] >> 16);
+    }
 }
 
 // What the kernels read: BF16 weights (W2 also transposed, for the backward
@@ -157,11 +188,14 @@ __device__ __forceinline__ void mlp_forward_block(const MlpView &P, const MlpReg
         v4u a = {0u, 0u, 0u, 0u};
         if (g < 2) a = ld8(&L.z[rt * 16 + li][8 * g]);
         const v4f d = mfma32(a, R.w1, (v4f){0.f, 0.f, 0.f, 0.f});
+        float h[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float x = d[r] + R.b1;
-            split_bf(x > 0.f ? x : 0.f, L.h1[0][rt * 16 + 4 * g + r][u], L.h1[1][rt * 16 + 4 * g + r][u]);
+            h[r] = x > 0.f ? x : 0.f;
         }
+        uint32_t hh[2], hl[2];
+        split4_rows(h, &L.h1[0][rt * 16 + 4 * g][u], &L.h1[1][rt * 16 + 4 * g][u], hh, hl);
     }
     __syncthreads();
     // layer 2: K = 128 inputs, taken twice (hi, then lo), each against W2; then
