@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -114,6 +115,12 @@ struct TableT {
     int64_t kept_total = 0;         // kept entries of all rows
     int64_t kept_steps = 0;         // scan steps of all kept rows
     int kept_steps_max = 0;         // and of the longest one
+
+    // bnos_score_order's buffers, held by one call at a time: the order (after the arities) and a
+    // pinned buffer the results are written to, made by the first call
+    std::mutex host_mu;
+    int32_t *d_order = nullptr;     // [64]
+    char *h_result = nullptr;
 
     // order-scoring workspace: per (order, node, chunk) partial reductions
     void *d_part = nullptr;

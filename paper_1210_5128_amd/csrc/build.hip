@@ -1471,6 +1471,7 @@ static void free_device(TableT *t)
     hipFree(t->d_cmask);
     hipFree(t->d_cscore);
     hipFree(t->d_part);
+    hipHostFree(t->h_result);
     free_kept(t);
     for (auto e : t->ev_start) hipEventDestroy(e);
     for (auto e : t->ev_stop) hipEventDestroy(e);
@@ -1619,7 +1620,8 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
         return fail(e == hipErrorOutOfMemory ? BNOS_E_NOMEM : BNOS_E_DEVICE);           \
     }
     ALLOC(t->d_data, (size_t)n * t->N_pad);
-    ALLOC(t->d_ar, sizeof(int32_t) * 2 * n);
+    ALLOC(t->d_ar, sizeof(int32_t) * (2 * n + 64));
+    t->d_order = t->d_ar + 2 * n;
     ALLOC(t->d_prior, sizeof(double) * n * n);
     ALLOC(t->d_nsets, sizeof(int64_t) * 64 * 8);
     ALLOC(t->d_masks, sizeof(uint64_t) * (size_t)n * t->S_pad);
