@@ -1458,7 +1458,6 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
 static void free_device(TableT *t)
 {
     hipFree(t->d_data);
-    hipFree(t->d_ar);
     hipFree(t->d_prior);
     hipFree(t->d_nsets);
     hipFree(t->d_masks);
@@ -1614,16 +1613,17 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     };
     hipError_t e;
     if ((e = hipGetDevice(&t->device)) != hipSuccess) { set_error(std::string("hipGetDevice: ") + hipGetErrorString(e)); return fail(BNOS_E_DEVICE); }
+    constexpr size_t kNsetsBytes = sizeof(int64_t) * 64 * 8;
 #define ALLOC(ptr, bytes)                                                               \
     if ((e = hipMalloc((void **)&(ptr), (bytes))) != hipSuccess) {                      \
         set_error(std::string("hipMalloc " #ptr ": ") + hipGetErrorString(e));          \
         return fail(e == hipErrorOutOfMemory ? BNOS_E_NOMEM : BNOS_E_DEVICE);           \
     }
     ALLOC(t->d_data, (size_t)n * t->N_pad);
-    ALLOC(t->d_ar, sizeof(int32_t) * (2 * n + 64));
+    ALLOC(t->d_nsets, kNsetsBytes + sizeof(int32_t) * (2 * n + 64));   // with the arities, uploaded together
+    t->d_ar = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(t->d_nsets) + kNsetsBytes);
     t->d_order = t->d_ar + 2 * n;
     ALLOC(t->d_prior, sizeof(double) * n * n);
-    ALLOC(t->d_nsets, sizeof(int64_t) * 64 * 8);
     ALLOC(t->d_masks, sizeof(uint64_t) * (size_t)n * t->S_pad);
     ALLOC(t->d_scores, sizeof(float) * (size_t)n * t->S_pad);
     ALLOC(t->d_nstat, sizeof(double) * (size_t)n * 5);
@@ -1636,7 +1636,7 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
 #undef ALLOC
     int8_t *d_rows = nullptr;
     float *d_prior_in = nullptr;
-    int32_t *d_lut_row = nullptr, *d_den = nullptr;
+    int32_t *d_lut_row = nullptr, *d_den = nullptr;          // these two after d_lut in its allocation
     double *d_lut = nullptr;
     std::vector<int64_t> nsets(64 * 8, 0);
     for (int b = 0; b < 64; ++b)
@@ -1645,7 +1645,7 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     if ((e = (call)) != hipSuccess) {                                                     \
         set_error(std::string(#call) + ": " + hipGetErrorString(e));                      \
         hipFree(d_rows); hipFree(d_prior_in);                                             \
-        hipFree(d_lut_row); hipFree(d_den); hipFree(d_lut);                               \
+        hipFree(d_lut);                                                                   \
         return fail(BNOS_E_DEVICE);                                                       \
     }
     if (N > 0 && !dev_data) CK(hipMalloc((void **)&d_rows, (size_t)N * n));
@@ -1655,8 +1655,9 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     if (prior) CK(hipMemcpyAsync(d_prior_in, prior, sizeof(float) * n * n, hipMemcpyHostToDevice, st));
     std::vector<int32_t> ar_magic(arities, arities + n);     // the arities, then their magic numbers (divmod_small)
     for (int v = 0; v < n; ++v) ar_magic.push_back(arities[v] > 1 ? (int32_t)(uint32_t)(0x100000000ull / arities[v] + 1) : 0);
-    CK(hipMemcpyAsync(t->d_ar, ar_magic.data(), sizeof(int32_t) * 2 * n, hipMemcpyHostToDevice, st));
-    CK(hipMemcpyAsync(t->d_nsets, nsets.data(), sizeof(int64_t) * 64 * 8, hipMemcpyHostToDevice, st));
+    nsets.resize(64 * 8 + n);
+    std::memcpy(nsets.data() + 64 * 8, ar_magic.data(), sizeof(int32_t) * 2 * n);
+    CK(hipMemcpyAsync(t->d_nsets, nsets.data(), kNsetsBytes + sizeof(int32_t) * 2 * n, hipMemcpyHostToDevice, st));
     if (N > 0) {
         int64_t tot = N * n;
         int blocks = (int)std::min<int64_t>((tot + 255) / 256, 1 << 16);
@@ -1718,14 +1719,15 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
             if (isd[d]) { row[d] = (int32_t)den.size(); den.push_back(d); }
         constexpr int64_t kLutBytes = 256ll << 20;
         if ((int64_t)den.size() * (N + 1) * 8 <= kLutBytes) {
-            CK(hipMalloc((void **)&d_den, sizeof(int32_t) * den.size()));
-            CK(hipMalloc((void **)&d_lut_row, sizeof(int32_t) * row.size()));
-            CK(hipMalloc((void **)&d_lut, sizeof(double) * den.size() * (size_t)(N + 1)));
-            CK(hipMemcpyAsync(d_den, den.data(), sizeof(int32_t) * den.size(), hipMemcpyHostToDevice, st));
-            CK(hipMemcpyAsync(d_lut_row, row.data(), sizeof(int32_t) * row.size(), hipMemcpyHostToDevice, st));
             const int64_t tot = (int64_t)den.size() * (N + 1);
+            const int dens = (int)den.size();
+            den.insert(den.end(), row.begin(), row.end());
+            CK(hipMalloc((void **)&d_lut, sizeof(double) * (size_t)tot + sizeof(int32_t) * den.size()));
+            d_den = reinterpret_cast<int32_t *>(d_lut + tot);
+            d_lut_row = d_den + dens;
+            CK(hipMemcpyAsync(d_den, den.data(), sizeof(int32_t) * den.size(), hipMemcpyHostToDevice, st));
             hipLaunchKernelGGL(k_lut, dim3((unsigned)std::min<int64_t>((tot + 255) / 256, 1 << 16)), dim3(256), 0, st,
-                               d_den, (int)den.size(), N, ess, scale, d_lut);
+                               d_den, dens, N, ess, scale, d_lut);
             CK(hipGetLastError());
         }
     }
@@ -1763,8 +1765,6 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
     CK(hipStreamSynchronize(st));
     hipFree(d_rows);
     hipFree(d_prior_in);
-    hipFree(d_lut_row);
-    hipFree(d_den);
     hipFree(d_lut);
 #undef CK
     t->magic = kMagic;
