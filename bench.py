@@ -736,11 +736,19 @@ def main():
     print(f"# table built in {build_s:.3f} s, S={S}", file=sys.stderr, flush=True)
 
     def launch_bytes(tab, ords, Bq, skip, eb, passes):
-        """Algorithmic bytes of one scoring launch of these orders: with tile skipping the
+        """Algorithmic bytes of one scoring launch of these orders.  A table with kept rows
+        (kept_entries() > 0): the 64-entry tiles of those rows the scans read (768 B each);
+        without skipping every kept entry and the streaming pass over the others (eb bytes an
+        entry plus a bit each that tells them apart).  Other tables, with tile skipping: the
         64-entry sub-tiles it loads (64 x eb bytes) plus the 8-byte summary of every tile of
         each pass and, with one order per block, the 8-byte summary of every sub-tile, the
         4-byte maximum of every tile and each node's 256 score-bound candidates (12 B);
         without, the full scan."""
+        kept = tab.kept_entries()
+        if kept and skip:
+            return tab.count_tiles(ords)[0] * 768
+        if kept:
+            return (eb * n * S + n * S // 4 + 12 * kept) * passes
         if not skip:
             return eb * n * S * passes
         tl, per_pass = tab.count_tiles(ords)
@@ -796,6 +804,8 @@ def main():
         # of an 8-byte anchor mask (6 B); otherwise mask + score (12 B)
         computed_now = bool(args.computed_masks) if computed is None else computed
         eb = 6 if (computed_now and passes_per_launch == Bq) else 12
+        if skip and tabs[0].kept_entries():
+            eb = 12                                        # a kept entry: its mask and its score
         cache = {}
         alg_tot, tiles_tot, per_pass = 0.0, 0, 1
         for s_ in timed_s:
@@ -816,6 +826,7 @@ def main():
                     entry_bytes=eb, timed_launches=len(timed_s),
                     tile_fraction=tiles_tot / max(1, len(timed_s) * passes_per_launch * per_pass) if skip else 1.0)
 
+    kept_entries = table.kept_entries()
     stream = torch.cuda.current_stream()
     # launch shape (chunk length, orders per block) tuned per batch size before timing
     tuned = {}
@@ -865,7 +876,8 @@ def main():
                 t2.set_launch(B, chunk_steps=args.chunk_steps)
             others.append(t2)
         rh = timed(B, extra_steps * args.hbm_tables, args.warmup, skip=True, tables=[table] + others)
-        read_set = sum(tb.info()["entries_per_node"] for tb in [table] + others) * n * 6
+        read_set = (sum(tb.kept_entries() * 12 for tb in [table] + others) if kept_entries else
+                    sum(tb.info()["entries_per_node"] for tb in [table] + others) * n * 6)
         for t2 in others:
             t2.free()
         print(f"# {args.hbm_tables} tables alternating: {rh['kernel_avg_ms'] * 1e3:.1f} us per launch, "
@@ -883,12 +895,12 @@ def main():
         "bytes_per_entry": rs["entry_bytes"], "achieved_GBs": rs["gbs"], "frac": rs["gbs"] / HBM_PEAK_GBS,
         "note": "one launch reads 12 B x n x S, more than the 256 MB Infinity Cache: HBM-resident"}
     hbm_resident = None if rh is None else {
-        "tables": args.hbm_tables, "read_set_bytes": read_set, "kernel": "k_score (tile skipping)",
+        "tables": args.hbm_tables, "read_set_bytes": read_set, "kernel": "kept rows" if kept_entries else "k_score (tile skipping)",
         "kernel_avg_us": rh["kernel_avg_ms"] * 1e3, "timed_launches": rh["timed_launches"],
         "algorithmic_bytes_per_launch": rh["alg_bytes"], "achieved_GBs": rh["gbs"], "frac": rh["gbs"] / HBM_PEAK_GBS,
         "order_scores_per_s": rh["value"],
-        "note": "B=1 launches alternating over independently built tables whose scores and anchors together "
-                "exceed the 256 MB Infinity Cache"}
+        "note": "B=1 launches alternating over independently built tables; without kept rows their scores and "
+                "anchors together exceed the 256 MB Infinity Cache"}
     batched = None
     if args.batched_check:
         rb = timed(args.batched_check, 20, 3)
@@ -924,17 +936,20 @@ def main():
             "frac": achieved_gbs / HBM_PEAK_GBS,
             "traffic": (measured_traffic(B, "full" if args.passes == "full" else "skip")
                         if args.workload == "mixed60" else None),
-            "kernel": "k_score (full scan)" if args.passes == "full" else "k_score (tile skipping)",
+            "kernel": ("k_score (full scan)" if args.passes == "full" else
+                       "k_kept_partials / k_score_kept (kept rows)" if kept_entries else "k_score (tile skipping)"),
+            "kept_entries": kept_entries,
             "kernel_avg_us": kernel_avg_ms * 1e3,
             "algorithmic_bytes_per_launch": r["alg_bytes"],
             "bytes_per_entry": r["entry_bytes"],
             "tile_fraction_read": r["tile_fraction"] if args.passes != "full" else 1.0,
             "timed_launches": r["timed_launches"],
-            "note": ("with tile skipping and the score bound a launch reads ~6% of the table's entries and the "
-                     "pass is bound by the latency of its longest wavefronts, not by bandwidth; full_scan "
+            "note": ("with kept rows a launch scans, per node, the entries no subset of theirs rules out for "
+                     "every order, in descending score, until the rest cannot matter: about a megabyte at "
+                     "n=60, so the pass is bound by launch and load latency, not by bandwidth; full_scan "
                      "(every entry, no skipping) is the streaming-bandwidth figure. Effective bandwidth: the "
                      "scores and anchors (176 MB at n=60) fit the 256 MB Infinity Cache between launches; "
-                     "hbm_resident and full_scan_stored_masks stream from HBM"),
+                     "full_scan_stored_masks streams from HBM"),
         },
         "hbm_resident": hbm_resident,
         "full_scan": full_scan,

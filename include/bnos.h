@@ -303,9 +303,11 @@ bnos_status bnos_mlp_train(bnos_mlp m, const float *feats, const int32_t *pairs,
  * new order on the table, and accepts iff ln u < new - old (u uniform in
  * (0,1)); the best-graph record starts from the initial order's greedy graph
  * and is replaced, after an accepted move, when the new order's max score
- * (Eq. (6)) is strictly larger.  All C proposals of an iteration are scored
- * in one pass over the table; sweep_len iterations are captured in one HIP
- * graph and replayed.
+ * (Eq. (6)) is strictly larger.  On a table with kept entries (bnos_table_kept)
+ * with the score bound on, one block runs a chain's iterations in one launch;
+ * elsewhere all C proposals of an iteration are scored in one pass over the
+ * table and sweep_len iterations are captured in one HIP graph and replayed.
+ * Results do not depend on sweep_len.
  *
  * Random numbers: one 64-bit draw per (seed, chain, purpose, step) from the
  * SplitMix64 finalizer mix(z) (Steele, Lea & Flood 2014):
@@ -326,7 +328,7 @@ typedef struct {
     int64_t chain_offset;     /* chain c draws from RNG stream chain_offset + c */
     int32_t trace_every;      /* >= 1; trace entry j is the score after iteration
                                  first_iteration + j*trace_every, j = 0..iterations/trace_every */
-    int32_t sweep_len;        /* iterations per captured graph; 0 = 32 */
+    int32_t sweep_len;        /* iterations per captured graph (tables without kept entries); 0 = 32 */
     int32_t proposal;         /* 0: uniform swap of two positions; 1: learned (needs mlp) */
     float eps;                /* learned: weight of the uniform pair in q, (0, 1]; 0 means 0.5 */
     struct bnos_mlp_s *mlp;   /* learned: the network (see bnos_mlp_*), read during the call */
@@ -405,6 +407,8 @@ bnos_status bnos_run_chains_multi(const bnos_table *tables, int32_t T, const bno
  * table and the chain count's bucket (1, 2-3, 4-7, 8-15, 16+).  Later sweeps
  * of that many chains on this table (bnos_run_chains, and bnos_run_chains_multi
  * where it is the first table: the chains per block are per launch) use it.
+ * A table whose chains run in one launch (kept entries, score bound on) has one
+ * shape, which is timed and returned.
  * With cfg->first_iteration > 0 every timed run resumes from a copy of `state`
  * (orders, scores, best_graphs, best_scores, accepted; e.g. burned-in chains);
  * with 0 they start fresh from cfg->seed and state may be NULL.  The caller's
