@@ -693,7 +693,24 @@ __global__ __launch_bounds__(WAVES * 64) void k_build(
 
 // Per-node static features of the learned proposal: prior terms summed as
 // child (row) and as parent (column), and max, mean and population standard
-// deviation of the node's stored FP32 scores (FP64 sums, fixed tree).
+// deviation of the node's stored FP32 scores (FP64 sums, fixed tree).  One block per row, each thread
+// adds its entries in order: bound by the loads it has in flight (60
+// nodes, 489,406 entries: 352 us one at a time, 86 us with 16).
+constexpr int kStatLoads = 16;
+template <typename Op>
+__device__ __forceinline__ void stat_entries(const float *__restrict__ row, int64_t S, int tid, Op op)
+{
+    int64_t e = tid;
+    for (; e + 1024 * (kStatLoads - 1) < S; e += 1024 * kStatLoads) {
+        float v[kStatLoads];
+#pragma unroll
+        for (int i = 0; i < kStatLoads; ++i) v[i] = row[e + 1024 * i];
+#pragma unroll
+        for (int i = 0; i < kStatLoads; ++i) op((double)v[i]);
+    }
+    for (; e < S; e += 1024) op((double)row[e]);
+}
+
 __global__ __launch_bounds__(1024) void k_node_stats(const float *__restrict__ scores, int64_t S, int64_t S_pad,
                                                      const double *__restrict__ prior, int n,
                                                      double *__restrict__ out)
@@ -703,11 +720,10 @@ __global__ __launch_bounds__(1024) void k_node_stats(const float *__restrict__ s
     const int tid = threadIdx.x;
     const float *row = scores + (int64_t)node * S_pad;
     double mx = -INFINITY, sum = 0.0;
-    for (int64_t e = tid; e < S; e += 1024) {
-        const double v = row[e];
+    stat_entries(row, S, tid, [&](double v) {
         mx = v > mx ? v : mx;
         sum += v;
-    }
+    });
     s_a[tid] = mx;
     s_b[tid] = sum;
     __syncthreads();
@@ -722,10 +738,10 @@ __global__ __launch_bounds__(1024) void k_node_stats(const float *__restrict__ s
     const double mean = s_b[0] / (double)S;
     __syncthreads();
     double sq = 0.0;
-    for (int64_t e = tid; e < S; e += 1024) {
-        const double d = (double)row[e] - mean;
+    stat_entries(row, S, tid, [&](double v) {
+        const double d = v - mean;
         sq += d * d;
-    }
+    });
     s_b[tid] = sq;
     __syncthreads();
     for (int w = 512; w >= 1; w >>= 1) {
@@ -1055,7 +1071,8 @@ __global__ __launch_bounds__(256) void k_keep_entries(const uint64_t *__restrict
 // A sort key for each kept entry, appended to its row's list (in any order: the sort fixes
 // it).  A key's high half falls as the score rises, its low half is the place in the row, so
 // ascending keys list descending scores and, among equal ones, ascending masks.  klen also
-// receives the rows' first entries, and holds the lists' cursors (zero at first).
+// receives the rows' first entries, and holds the lists' cursors (zero at first).  60 nodes: 363 us with
+// one byte of the bits per lane and round, 210 us with four (the cursors' updates bound it).
 __global__ __launch_bounds__(256) void k_keep_keys(const float *__restrict__ scores, int n, int64_t S_pad,
                                                    const uint8_t *__restrict__ kept, int64_t cap,
                                                    uint64_t *__restrict__ keys, int32_t *klen)
@@ -1067,8 +1084,10 @@ __global__ __launch_bounds__(256) void k_keep_keys(const float *__restrict__ sco
     if (!fits) return;                                               // uniform over the grid
     if (blockIdx.x == 0 && threadIdx.x == 0) klen[2 * n + node] = first;
     const int64_t row = (int64_t)node * S_pad;
-    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < S_pad / 4; q += (int64_t)gridDim.x * 256) {
-        const uint32_t bits = kept[row / 4 + q];
+    // four bytes of the bits, 16 entries, per lane (S_pad is a multiple of 1024)
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(kept + row / 4);
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < S_pad / 16; q += (int64_t)gridDim.x * 256) {
+        const uint32_t bits = words[q];
         const int mine = __popc(bits);
         int before = mine;
 #pragma unroll
@@ -1081,13 +1100,13 @@ __global__ __launch_bounds__(256) void k_keep_keys(const float *__restrict__ sco
         int base = 0;
         if (lane == 0) base = atomicAdd(&klen[3 * n + node], total); // one update per wavefront
         base = first + __shfl(base, 0, 64) + before - mine;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if ((bits >> e) & 1u) {
-                const uint32_t u = __float_as_uint(scores[row + 4 * q + e] + 0.0f);   // -0 sorts as +0
-                const uint32_t up = (u >> 31) ? ~u : (u | 0x80000000u);               // rises with the score
-                keys[base++] = ((uint64_t)~up << 32) | (uint32_t)(4 * q + e);
-            }
+        for (uint32_t x = bits; x; x &= x - 1) {                     // bit 8 b + e: entry 4 b + e of the 16
+            const int p = __builtin_ctz(x);
+            const int64_t at = 16 * q + 4 * (p >> 3) + (p & 7);
+            const uint32_t u = __float_as_uint(scores[row + at] + 0.0f);          // -0 sorts as +0
+            const uint32_t up = (u >> 31) ? ~u : (u | 0x80000000u);               // rises with the score
+            keys[base++] = ((uint64_t)~up << 32) | (uint32_t)at;
+        }
     }
 }
 
@@ -1428,7 +1447,7 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
                            sub_row, sub);
         hipLaunchKernelGGL(k_keep_entries, dim3(groups, (unsigned)n), dim3(256), 0, st, t->d_masks, t->d_scores,
                            t->d_nsets, n, K, t->S, t->S_pad, sub_row, sub, t->d_kept, t->d_klen);
-        hipLaunchKernelGGL(k_keep_keys, dim3(std::min(groups, 64u), (unsigned)n), dim3(256), 0, st, t->d_scores, n,
+        hipLaunchKernelGGL(k_keep_keys, dim3(std::min((groups + 3) / 4, 128u), (unsigned)n), dim3(256), 0, st, t->d_scores, n,
                            t->S_pad, t->d_kept, cells, keys, t->d_klen);
         hipLaunchKernelGGL(k_keep_sort, dim3(n, (longest + kKeptRun - 1) / kKeptRun), dim3(1024), 0, st, t->d_masks,
                            t->d_scores, n, t->S_pad, cells, t->d_klen, keys, t->d_kmask, t->d_kscore);
