@@ -122,9 +122,10 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
  * one; the build lists every row's other entries apart, in descending score, and
  * scoring and chains with the score bound on (bnos_table_score_bound) read those
  * alone.  *entries = kept entries of all rows, 0 for a table that has none listed
- * (more than 16,384 per row on average, or no memory for them within
- * BNOS_MAX_DEVICE_BYTES);
- * the streaming pass then serves it.
+ * (more per row on average than a sixteenth of it, at least 6,144 and at most
+ * 16,384, or no memory for them within BNOS_MAX_DEVICE_BYTES); the streaming pass
+ * then serves it, and also fewer than 4 chains with uniform swaps on a table with
+ * many kept entries.
  */
 bnos_status bnos_table_kept(bnos_table t, int64_t *entries);
 
@@ -304,7 +305,7 @@ bnos_status bnos_mlp_train(bnos_mlp m, const float *feats, const int32_t *pairs,
  * (0,1)); the best-graph record starts from the initial order's greedy graph
  * and is replaced, after an accepted move, when the new order's max score
  * (Eq. (6)) is strictly larger.  On a table with kept entries (bnos_table_kept)
- * with the score bound on, one block runs a chain's iterations in one launch;
+ * with the score bound on, one block usually runs a chain's iterations in one launch;
  * elsewhere all C proposals of an iteration are scored in one pass over the
  * table and sweep_len iterations are captured in one HIP graph and replayed.
  * Results do not depend on sweep_len.

@@ -57,10 +57,21 @@ constexpr float kBoundGap = 60.0f;
 // candidates, once for all orders.  A build therefore lists each row's other
 // entries, the kept ones, apart: at n = 60, K = 4, N = 5,000 they are 1,200 to
 // 6,200 of 489,406 per row on average, depending on the data, with single rows
-// of 100,000.  A table that keeps more than kKeptMean per row on average (few
+// of 100,000.  A table that keeps more than kept_mean() per row on average (few
 // samples of binary variables: nearly all of them) stays with the streaming pass,
-// which shares each streamed tile between orders.
-constexpr int kKeptMean = 16384;
+// which shares each streamed tile between orders.  The line: a chain's iteration
+// scans its kept rows at 20 to 45 us per 10,000 entries, and streams rows of S
+// entries in 20 us and more, the longer the rows the more.  One chain, kept against
+// streamed, us per iteration: 7,547 of 7,547 entries kept 22 / 22, 10,903 of 10,903
+// 34 / 21, 14,439 of 15,276 26 / 23, 31,284 of 489,406 106 / 63; and 32 chains with
+// 7,343 of 396,607 kept 49 / 91.  256 orders: 7,547 kept 43 / 36 us, 10,903
+// kept 63 / 44.  So up to a sixteenth of the row, at least 6,144 and at most 16,384.
+constexpr int kKeptMeanLow = 6144, kKeptMeanHigh = 16384;
+constexpr int64_t kept_mean(int64_t S)
+{
+    return S / 16 < kKeptMeanLow ? kKeptMeanLow : (S / 16 > kKeptMeanHigh ? kKeptMeanHigh : S / 16);
+}
+constexpr int kKeptStepsFew = 1600;        // see kept_chains
 constexpr int kKeptCap = 1 << 19;         // entries of one row
 constexpr int kKeptRun = 16384;           // sort keys of one block: 128 KB of LDS
 constexpr int kKeptTiles = 4;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
@@ -185,6 +196,14 @@ struct TableT {
     // the kept rows alone serve scoring and chains (with the score bound off, the streaming pass
     // adds the other entries)
     bool kept_rows() const { return d_kmask != nullptr && score_bound && tile_skip; }
+    // whether C chains run on them: a few chains of a table with many steps of kept entries are better
+    // streamed (57 nodes, 1,660 steps: one chain 48 us per iteration against 34, four 48 against 47,
+    // 32 49 against 91; 60 nodes, 1,480 steps: one chain 30 against 62, four 30 against 96);
+    // the learned proposal's streamed step alone takes 46
+    bool kept_chains(int C, bool learned) const
+    {
+        return kept_rows() && (learned || C >= 4 || kept_steps <= kKeptStepsFew);
+    }
     int64_t kept_bytes() const
     {
         return kept_cap * 12 + (int64_t)n * 16 + (int64_t)n * n * 4 + (int64_t)n * (S_pad / 4);

@@ -903,7 +903,7 @@ __global__ __launch_bounds__(256) void k_anchor(const uint64_t *__restrict__ mas
     anchor[g] = (m == ~0ull) ? (1ull << (n - 1)) : ((m & low) | ((m >> 1) & ~low));
 }
 
-// ---- kept entries (see kKeptMean)
+// ---- kept entries (see kept_mean)
 //
 // Subset records: sub[node][r], r the rank of a set among those of at most K - 1
 // members, holds (the largest score among the set's subsets and itself, its own
@@ -1411,7 +1411,7 @@ static void free_kept(TableT *t)
 }
 
 // Lists the table's kept rows after its rows are built (waits for the stream).  A table
-// without them (more kept entries than kKeptMean per row, a memory cap they would pass, no
+// without them (more kept entries than kept_mean per row, a memory cap they would pass, no
 // memory for them) is served by the streaming pass, so nothing here fails the build but a
 // device error.
 static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
@@ -1421,7 +1421,7 @@ static hipError_t list_kept(TableT *t, hipStream_t st, int64_t max_bytes)
     if (sub_row * n > kKeptSubsetCap) return hipSuccess;
     constexpr int64_t kStep = 64 * kKeptTiles;
     const int64_t row_cap = std::min<int64_t>((t->S + kStep - 1) / kStep * kStep, kKeptCap);
-    t->kept_cap = n * std::min<int64_t>(row_cap, kKeptMean);
+    t->kept_cap = n * std::min<int64_t>(row_cap, kept_mean(t->S));
     if (max_bytes > 0 && t->device_bytes() + t->kept_bytes() > max_bytes) return hipSuccess;
     // one allocation for the table (kept_bytes() of it) and one for the build's passes
     const int64_t cells = t->kept_cap;

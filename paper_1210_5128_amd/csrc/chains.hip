@@ -1112,10 +1112,10 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
     // iteration: entries 0 .. Tk - 1 of the arrays below, and Tk .. T - 1
     std::vector<int> order;
     for (int k = 0; k < T; ++k)
-        if (tabs[k]->kept_rows()) order.push_back(k);
+        if (tabs[k]->kept_chains(C, cfg->proposal == 1)) order.push_back(k);
     const int Tk = (int)order.size(), Ts = T - Tk;
     for (int k = 0; k < T; ++k)
-        if (!tabs[k]->kept_rows()) order.push_back(k);
+        if (!tabs[k]->kept_chains(C, cfg->proposal == 1)) order.push_back(k);
     for (int q = Tk; q < T; ++q)
         if ((s = ensure_workspace(tabs[order[q]], C)) != BNOS_OK) return s;
 
@@ -1228,7 +1228,9 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         V.kscore = t->d_kscore;
         V.klen = t->d_klen;
         V.kpm = t->d_kpm;
-        V.kept = t->d_kmask ? t->d_kept : nullptr;     // the streaming pass leaves out what slot 0 holds
+        // with the bound off the streaming pass leaves out what slot 0 holds; with it on a streamed table
+        // is read like one without kept rows
+        V.kept = t->d_kmask && !(q >= Tk && t->kept_rows()) ? t->d_kept : nullptr;
         V.slot0 = V.kept ? 1 : 0;
         V.slots = V.chunks + V.slot0;
         if (q < Tk) {
@@ -1459,7 +1461,7 @@ extern "C" bnos_status bnos_chains_autotune(bnos_table h, const bnos_chain_cfg *
     double best_ms = 1e300;
     int best_cs = 0, best_bt = 0;
     // chains on kept rows have one launch whatever the shape: time it once, as it is set
-    const bool kept = t->kept_rows();
+    const bool kept = t->kept_chains(C, cfg->proposal == 1);
     const int cs0 = kept ? t->chain_chunk_entries_for(C) / kEntriesPerStep : 1;
     const int bt0 = !kept ? 1 : ((old_bt > 0 && old_bt <= C) ? old_bt : pick_bt(t, C));
     for (int cs = cs0; cs <= (kept ? cs0 : t->pad_steps) && s == BNOS_OK; cs <<= 1) {

@@ -406,7 +406,7 @@ struct ScoreArgs {
     const float *cuts;         // [B][n] each order's cut per node, computed before the launch, or null
     float *cut_ws;             // [B][n] workspace for those cuts (several-order launches)
     int K;
-    // kept entries (see kKeptMean), or null
+    // kept entries (see kept_mean), or null
     const uint64_t *kmask;
     const float *kscore;
     const int32_t *klen;       // [n] entries, [n] nodes by descending entries, [n] first entries
@@ -437,7 +437,7 @@ struct TabView {
     const float *cuts;          // [orders][n] each order's (chain's) cut per node, computed by an
                                 // earlier launch, or null (the block computes it)
     int K;
-    const uint64_t *kmask;      // kept entries (see kKeptMean), or null
+    const uint64_t *kmask;      // kept entries (see kept_mean), or null
     const float *kscore;
     const int32_t *klen;        // [n] entries, [n] nodes by descending entries, [n] first entries
     const float *kpm;           // [n][n] largest kept score of row i among the sets holding node m
