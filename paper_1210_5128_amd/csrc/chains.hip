@@ -998,35 +998,39 @@ __global__ __launch_bounds__(W * 64) void k_chain_run(const TabView *__restrict_
 }
 
 // The kept entries' partial (slot 0) of every (chain, window node) pair, whole rows, for sweeps
-// whose streaming pass adds the other entries (score bound off); one wavefront per pair.
+// whose streaming pass adds the other entries (score bound off); one wavefront per pair.  The grid
+// is at most kKeptBlocks: the pairs of a call may pass what one launch can hold (2^32 work-items).
+constexpr int64_t kKeptBlocks = 1 << 20;
 __global__ __launch_bounds__(kScoreThreads) void k_chain_kept(const TabView *__restrict__ tviews,
                                                               const ChainView *__restrict__ views,
                                                               const int64_t *__restrict__ node_base, int T, int C)
 {
-    const int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t nodes = node_base[T];
-    if (g >= nodes * C) return;                              // uniform per wavefront
-    const int c = (int)(g / nodes);
-    const int64_t gn = g - (int64_t)c * nodes;
-    const int k = find_segment(node_base, T, gn);
-    const ChainView &H = views[k];
-    const TabView &V = tviews[k];
-    const int node = (int)(gn - node_base[k]);
-    if (!V.kept || !((H.wmask[c] >> node) & 1ull)) return;   // uniform
-    const int n = H.n;
-    const uint8_t *pp = H.ppos + (int64_t)c * n;
-    const int pv = pp[node], pu = pp[lane < n ? lane : n - 1];
-    const uint64_t pred = __ballot(lane < n && pu < pv);
-    const int64_t row = V.klen[2 * n + node];
     __shared__ KeptAcc s_part[kScoreThreads / 64][kStripes];
-    KeptAcc *part = s_part[threadIdx.x >> 6];
-    const int len = V.klen[node], nq = kept_stripes_of(len);
-    for (int q = 0; q < nq; ++q) {
-        const KeptAcc a = kept_scan<false>(V.kmask + row, V.kscore + row, len, q, ~pred, lane, nullptr);
-        if (lane == 0) part[q] = a;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    KeptAcc *part = s_part[wave];
+    const int64_t nodes = node_base[T];
+    for (int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + wave; g < nodes * C;
+         g += (int64_t)gridDim.x * (kScoreThreads / 64)) {   // uniform per wavefront
+        const int c = (int)(g / nodes);
+        const int64_t gn = g - (int64_t)c * nodes;
+        const int k = find_segment(node_base, T, gn);
+        const ChainView &H = views[k];
+        const TabView &V = tviews[k];
+        const int node = (int)(gn - node_base[k]);
+        if (!V.kept || !((H.wmask[c] >> node) & 1ull)) continue;   // uniform
+        const int n = H.n;
+        const uint8_t *pp = H.ppos + (int64_t)c * n;
+        const int pv = pp[node], pu = pp[lane < n ? lane : n - 1];
+        const uint64_t pred = __ballot(lane < n && pu < pv);
+        const int64_t row = V.klen[2 * n + node];
+        const int len = V.klen[node], nq = kept_stripes_of(len);
+        for (int q = 0; q < nq; ++q) {
+            const KeptAcc a = kept_scan<false>(V.kmask + row, V.kscore + row, len, q, ~pred, lane, nullptr);
+            if (lane == 0) part[q] = a;
+        }
+        if (lane == 0) kept_store(V, c, node, kept_combine(part, nq));
     }
-    if (lane == 0) kept_store(V, c, node, kept_combine(part, nq));
 }
 
 }  // namespace bnos
@@ -1309,7 +1313,8 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
                            d_cvs, d_node, Ts, C);
         dim3 grid((unsigned)((blk_base[Ts] + kXcds - 1) / kXcds * kXcds), groups);   // padded for xcd_block
         if (any_kept) {                          // score bound off: slot 0, then every entry not in it
-            hipLaunchKernelGGL(k_chain_kept, dim3((unsigned)((pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64))),
+            const int64_t blocks = (pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
+            hipLaunchKernelGGL(k_chain_kept, dim3((unsigned)(blocks < kKeptBlocks ? blocks : kKeptBlocks)),
                                dim3(kScoreThreads), 0, q, d_tvs, d_cvs, d_node, Ts, C);
             if (bt == 8) hipLaunchKernelGGL((k_score_multi<8, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
             else if (bt == 4) hipLaunchKernelGGL((k_score_multi<4, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);

@@ -1,0 +1,43 @@
+"""Calls whose (order or chain, node) pairs are more than one launch can hold as a wavefront each (2^32
+work-items): they run, and give what smaller calls give."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1210_5128_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bnos():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1210_5128_amd import bnos as b
+    return b
+
+
+def test_many_chains_on_kept_rows_with_the_bound_off(bnos):
+    # 57 tables x 65,536 chains x 18 nodes: 67,239,936 pairs, 4.3e9 work-items; the first, a middle and the
+    # last table against the same chains on that table alone
+    n, C, T, seed = 18, 65536, 57, 3
+    tabs, states = [], []
+    try:
+        for k in range(T):
+            net = datagen.random_network(n, 60, (2, 3), 3, seed=k)
+            t = bnos.build_score_table(net.data, net.arities, 1)
+            tabs.append(t)
+            assert t.kept_entries() > 0
+            t.score_bound(False)
+            states.append(t.new_chain_state(C, 1))
+        bnos.run_chains_multi(tabs, states, 1, seed)
+        for k in (0, T // 2, T - 1):
+            ref = tabs[k].new_chain_state(C, 1)
+            tabs[k].run_chains(ref, 1, seed, chain_offset=k * C)
+            torch.cuda.synchronize()
+            for key in ("orders", "scores", "best_graphs", "best_scores", "accepted", "trace"):
+                assert torch.equal(states[k][key], ref[key]), (k, key)
+    finally:
+        for t in tabs:
+            t.free()
