@@ -131,12 +131,11 @@ __global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
 {
     __shared__ KeptAcc s_part[kStripes];
     __shared__ int s_hint;
-    const int64_t g = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = A.n;
-    const int k = (int)(g / A.B), b = (int)(g - (int64_t)k * A.B);
-    const int node = A.klen[n + k];
+    const int b = blockIdx.x;                   // (node's place in y: all pairs in x could pass 2^32 work-items)
+    const int node = A.klen[n + blockIdx.y];
     const int len = A.klen[node];
     if (threadIdx.x == 0) s_hint = ordered_f32(-INFINITY);
     bool valid;
@@ -156,11 +155,11 @@ __global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
 // k_kept_partials reads for these orders, one count per (order, node).
 __global__ __launch_bounds__(kScoreThreads) void k_count_kept(ScoreArgs A, int stop, unsigned *__restrict__ counts)
 {
-    const int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int node = blockIdx.y;
     const int lane = threadIdx.x & 63;
     const int n = A.n;
-    if (g >= (int64_t)A.B * n) return;
-    const int b = (int)(g / n), node = (int)(g - (int64_t)b * n);
+    if (b >= A.B) return;
     bool valid;
     const uint64_t np = ~wave_pred(A.orders + (int64_t)b * n, n, node, lane, valid);
     const int64_t row = A.klen[2 * n + node];
@@ -170,7 +169,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_count_kept(ScoreArgs A, int s
     int steps = stop ? 0 : kept_steps_of(A.klen[node]);
     for (int q = 0; stop && q < kept_stripes_of(A.klen[node]); ++q)
         kept_scan<true>(A.kmask + row, A.kscore + row, A.klen[node], q, np, lane, hint, &steps);
-    if (lane == 0) counts[g] = (unsigned)(steps * kKeptTiles);
+    if (lane == 0) counts[(int64_t)b * n + node] = (unsigned)(steps * kKeptTiles);
 }
 
 // Gather pass: see the comment at kGatherMaxK (score_device.h).
@@ -462,7 +461,7 @@ bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt,
     const int nbx = t->n * A.chunks;
     ScoreArgs A2 = A;
     if (A.kept) {
-        hipLaunchKernelGGL((k_kept_partials<1, false>), dim3((unsigned)((int64_t)A.B * A.n)), dim3(64), 0, st, A);
+        hipLaunchKernelGGL((k_kept_partials<1, false>), dim3((unsigned)A.B, (unsigned)A.n), dim3(64), 0, st, A);
     }
     if (bt > 1 && A.tmax && A.tand && A.cut_ws) {
         // every (order, node) cut once, before the blocks that stream the node's row
@@ -508,7 +507,7 @@ bnos_status launch_merge(const ScoreArgs &A, hipStream_t st)
 template <int W>
 static void launch_partials(const ScoreArgs &A, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
-    const dim3 grid((unsigned)((int64_t)A.B * A.n));
+    const dim3 grid((unsigned)A.B, (unsigned)A.n);
     if (e0) hipExtLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, e0, e1, 0, A);
     else hipLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, A);
 }
@@ -687,7 +686,7 @@ extern "C" bnos_status bnos_table_count_tiles(bnos_table h, const int32_t *order
     BNOS_HIP(hipMalloc((void **)&d, sizeof(unsigned) * blocks));
     unsigned *const d_all = d;
     if (pairs) {
-        hipLaunchKernelGGL(k_count_kept, dim3((unsigned)((pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64))),
+        hipLaunchKernelGGL(k_count_kept, dim3((unsigned)((B + kScoreThreads / 64 - 1) / (kScoreThreads / 64)), (unsigned)t->n),
                            dim3(kScoreThreads), 0, 0, A, bound ? 1 : 0, d);
         d += pairs;
     }

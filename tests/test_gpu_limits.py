@@ -41,3 +41,31 @@ def test_many_chains_on_kept_rows_with_the_bound_off(bnos):
     finally:
         for t in tabs:
             t.free()
+
+
+def test_most_orders_on_64_nodes(bnos):
+    # 2^20 orders of 64 nodes: 2^26 pairs, 2^32 work-items; against the same orders in calls of 2^17
+    n, B, step = 64, 1 << 20, 1 << 17
+    net = datagen.random_network(n, 129, (2,), 3, seed=84)
+    t = bnos.build_score_table(net.data, net.arities, 2)
+    try:
+        assert t.kept_entries() // 256 > 128             # more than one block per order scans
+        g = torch.Generator(device="cuda").manual_seed(1)
+        orders = torch.cat([torch.rand((step, n), device="cuda", generator=g).argsort(dim=1).to(torch.int32)
+                            for _ in range(B // step)])
+
+        def score(o):
+            lse = torch.empty(o.shape[0], dtype=torch.float64, device="cuda")
+            mx, best = torch.empty_like(lse), torch.empty(o.shape, dtype=torch.int64, device="cuda")
+            t.score_orders(o, lse, mx, best)
+            return lse, mx, best
+
+        whole = score(orders)
+        for b in range(0, B, step):
+            part = score(orders[b:b + step])
+            for w, p in zip(whole, part):
+                assert torch.equal(w[b:b + step], p), b
+        read, _ = t.count_tiles(orders)
+        assert read == sum(t.count_tiles(orders[b:b + step])[0] for b in range(0, B, step))
+    finally:
+        t.free()
