@@ -124,8 +124,9 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
  * alone.  *entries = kept entries of all rows, 0 for a table that has none listed
  * (more per row on average than a sixteenth of it, at least 6,144 and at most
  * 16,384, or no memory for them within BNOS_MAX_DEVICE_BYTES); the streaming pass
- * then serves it, and also fewer than 4 chains with uniform swaps on a table with
- * many kept entries.
+ * then serves it.  Fewer than 4 chains with uniform swaps on a table with many
+ * kept entries are streamed too, so there the number of chains can move a chain's
+ * log-sum-exps in the last bits, as a launch shape can (bnos_chains_autotune).
  */
 bnos_status bnos_table_kept(bnos_table t, int64_t *entries);
 

@@ -71,7 +71,7 @@ constexpr int64_t kept_mean(int64_t S)
 {
     return S / 16 < kKeptMeanLow ? kKeptMeanLow : (S / 16 > kKeptMeanHigh ? kKeptMeanHigh : S / 16);
 }
-constexpr int kKeptStepsFew = 1600;        // see kept_chains
+constexpr int kKeptStepsFew = 1600;        // see chains_fold_kept
 constexpr int kKeptCap = 1 << 19;         // entries of one row
 constexpr int kKeptRun = 16384;           // sort keys of one block: 128 KB of LDS
 constexpr int kKeptTiles = 4;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
@@ -196,14 +196,17 @@ struct TableT {
     // the kept rows alone serve scoring and chains (with the score bound off, the streaming pass
     // adds the other entries)
     bool kept_rows() const { return d_kmask != nullptr && score_bound && tile_skip; }
-    // whether C chains run on them: a few chains of a table with many steps of kept entries are better
-    // streamed (57 nodes, 1,660 steps: one chain 48 us per iteration against 34, four 48 against 47,
-    // 32 49 against 91; 60 nodes, 1,480 steps: one chain 30 against 62, four 30 against 96);
-    // the learned proposal's streamed step alone takes 46
-    bool kept_chains(int C, bool learned) const
+    // whether C chains fold their kept rows apart from the other entries, with the score bound on (where
+    // they need nothing else) and off alike, so that both add FP32 sums in the same order: a few chains of
+    // a table with many steps of kept entries are better streamed whole (57 nodes, 1,660 steps: one
+    // chain 48 us per iteration against 34, four 48 against 47, 32 49 against 91; 60 nodes, 1,480
+    // steps: one chain 30 against 62, four 30 against 96); the learned proposal's streamed step alone takes 46
+    bool chains_fold_kept(int C, bool learned) const
     {
-        return kept_rows() && (learned || C >= 4 || kept_steps <= kKeptStepsFew);
+        return d_kmask != nullptr && (learned || C >= 4 || kept_steps <= kKeptStepsFew);
     }
+    // whether they run on the kept rows alone
+    bool kept_chains(int C, bool learned) const { return kept_rows() && chains_fold_kept(C, learned); }
     int64_t kept_bytes() const
     {
         return kept_cap * 12 + (int64_t)n * 16 + (int64_t)n * n * 4 + (int64_t)n * (S_pad / 4);

@@ -1232,9 +1232,8 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         V.kscore = t->d_kscore;
         V.klen = t->d_klen;
         V.kpm = t->d_kpm;
-        // with the bound off the streaming pass leaves out what slot 0 holds; with it on a streamed table
-        // is read like one without kept rows
-        V.kept = t->d_kmask && !(q >= Tk && t->kept_rows()) ? t->d_kept : nullptr;
+        // with the bound off the streaming pass leaves out what slot 0 holds
+        V.kept = t->chains_fold_kept(C, cfg->proposal == 1) ? t->d_kept : nullptr;
         V.slot0 = V.kept ? 1 : 0;
         V.slots = V.chunks + V.slot0;
         if (q < Tk) {

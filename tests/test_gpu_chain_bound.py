@@ -1,0 +1,32 @@
+"""The score bound leaves chains unchanged, bit for bit, whichever path serves them: on kept rows of more
+than eight scan parts, and streamed whole where a table with kept rows has few chains."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1210_5128_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("chains", [1, 3, 4, 9])
+def test_bound_on_and_off_on_long_kept_rows(chains):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1210_5128_amd import bnos
+    net = datagen.random_network(57, 1066, (2, 3, 4), 3, seed=68)
+    t = bnos.build_score_table(net.data, net.arities, 4)
+    try:
+        assert t.kept_entries() // 256 > 1600             # fewer than 4 chains are streamed
+        runs = []
+        for on in (True, False):
+            t.score_bound(on)
+            st = t.new_chain_state(chains, 120, flags=True, topk=4)
+            t.run_chains(st, 120, 21)
+            torch.cuda.synchronize()
+            runs.append({k: v.cpu().numpy() for k, v in st.items() if torch.is_tensor(v)})
+        for k in runs[0]:
+            assert np.array_equal(runs[0][k].view(np.uint8), runs[1][k].view(np.uint8)), k
+    finally:
+        t.free()
