@@ -137,11 +137,13 @@ bnos_status bnos_table_kept(bnos_table t, int64_t *entries);
  * gather pass (each block enumerates the consistent parent sets of a node
  * with a given top member and reads only their scores, at their ranks in the
  * row: Alg. 2's traversal on the dense table), `reps` launches each after one
- * warm-up (a table scored from its kept entries has one launch whatever the
- * shape, which is timed once), and keeps the fastest for this table and batch size (batch sizes
+ * warm-up, and keeps the fastest for this table and batch size (batch sizes
  * are bucketed as 1, 2-3, 4-7, 8-15, 16+).  Outputs (may be NULL): the chosen
  * chunk steps and orders per block of the streaming pass, whether the gather
- * pass won (1) or not (0), and the mean time per launch in ms.  Both passes and
+ * pass won (1) or not (0), and the mean time per launch in ms.  A table scored
+ * from its kept entries is scored in the same way whatever the shape: that is
+ * timed too, its time takes the streaming pass's place, and the shape serves
+ * the calls on the table that are streamed (bnos_table_kept).  Both passes and
  * every shape give the same argmax parent sets; log-sum-exp values move in the
  * last bits with the order of the partial sums.  Synchronous on `stream`.
  */

@@ -408,6 +408,14 @@ ScoreArgs score_args(const TableT *t, const int32_t *orders, int B, double *lse,
     return A;
 }
 
+// The streaming pass over whole rows, the kept entries among them.
+static void stream_whole(ScoreArgs &A)
+{
+    A.kept = nullptr;
+    A.slot0 = 0;
+    A.slots = A.chunks;
+}
+
 template <void (*KERNEL)(ScoreArgs)>
 static void launch_one(dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, const ScoreArgs &A)
 {
@@ -771,28 +779,22 @@ extern "C" bnos_status bnos_table_autotune(bnos_table h, const int32_t *orders, 
     double best_ms = 1e300;
     int best_cs = t->chunk_entries / kEntriesPerStep, best_bt = pick_bt(t, B);
     bnos_status s = BNOS_OK;
-    // Kept rows take one launch whatever the shape: it is timed once.  The shape then serves the streaming
-    // pass with the bound or tile skipping off, which reads whole rows: the longest chunk (60 nodes,
-    // one order: 34 us against 78 us in 1-step chunks).
+    // On a table with kept rows the shapes serve the calls that are streamed all the same (few chains,
+    // the bound or tile skipping off), so they are timed as on a table without; a shape whose
+    // partials do not fit is passed over, since scoring does not need them.
     const bool kept = t->kept_rows();
-    if (kept && e == hipSuccess) s = ensure_kept_workspace(t, B);
-    if (kept) best_cs = t->pad_steps;
-    for (int cs = kept ? best_cs : 1; cs <= t->pad_steps && e == hipSuccess && s == BNOS_OK; cs <<= 1) {
-        if (!kept) {
-            t->tuned_cs[bk] = cs;
-            if ((s = ensure_workspace(t, B)) != BNOS_OK) break;
-        } else if (best_ms < 1e300) {
-            break;
+    for (int cs = 1; cs <= t->pad_steps && e == hipSuccess && s == BNOS_OK; cs <<= 1) {
+        t->tuned_cs[bk] = cs;
+        if ((s = ensure_workspace(t, B)) != BNOS_OK) {
+            if (!kept || s != BNOS_E_NOMEM) break;
+            s = BNOS_OK;
+            continue;
         }
-        for (int bt = kept ? best_bt : 1; bt <= 8 && bt <= B && s == BNOS_OK; bt <<= 1) {
-            if (kept && best_ms < 1e300) break;
+        for (int bt = 1; bt <= 8 && bt <= B && s == BNOS_OK; bt <<= 1) {
             ScoreArgs A = score_args(t, orders, B, d_out, d_out + B, d_best, nullptr, nullptr);
+            if (kept) stream_whole(A);
             for (int r = 0; r <= reps && s == BNOS_OK; ++r) {
                 if (r == 1) e = hipEventRecord(e0, st);
-                if (kept) {
-                    s = launch_kept(t, A, st, false);
-                    continue;
-                }
                 if ((s = launch_stream(t, A, st, bt)) != BNOS_OK) break;
                 hipLaunchKernelGGL(k_merge, dim3(B), dim3(kMergeWaves * 64), 0, st, A);
             }
@@ -806,6 +808,22 @@ extern "C" bnos_status bnos_table_autotune(bnos_table h, const int32_t *orders, 
                 best_cs = cs;
                 best_bt = bt;
             }
+        }
+    }
+    // scoring from the kept rows, one launch whatever the shape
+    if (kept && e == hipSuccess && s == BNOS_OK) {
+        t->tuned_cs[bk] = best_cs;
+        if ((s = ensure_kept_workspace(t, B)) == BNOS_OK) {
+            const ScoreArgs A = score_args(t, orders, B, d_out, d_out + B, d_best, nullptr, nullptr);
+            for (int r = 0; r <= reps && s == BNOS_OK; ++r) {
+                if (r == 1) e = hipEventRecord(e0, st);
+                s = launch_kept(t, A, st, false);
+            }
+            if (e == hipSuccess && s == BNOS_OK) e = hipEventRecord(e1, st);
+            if (e == hipSuccess && s == BNOS_OK) e = hipEventSynchronize(e1);
+            float ms = 0.f;
+            if (e == hipSuccess && s == BNOS_OK) e = hipEventElapsedTime(&ms, e0, e1);
+            best_ms = ms / reps;
         }
     }
     // the gather pass (enumerating the consistent sets), where the table allows it
@@ -844,7 +862,7 @@ extern "C" bnos_status bnos_table_autotune(bnos_table h, const int32_t *orders, 
     t->tuned_cs[bk] = best_cs;
     t->tuned_bt[bk] = best_bt;
     t->tuned_gather[bk] = best_g;
-    if ((s = ensure_workspace(t, B)) != BNOS_OK) return s;
+    if ((s = kept && !best_g ? ensure_kept_workspace(t, B) : ensure_workspace(t, B)) != BNOS_OK) return s;
     if (chunk_steps) *chunk_steps = best_cs;
     if (orders_per_block) *orders_per_block = best_bt;
     if (gather) *gather = best_g;
@@ -953,9 +971,7 @@ extern "C" bnos_status bnos_score_orders_noalloc(bnos_table h, const int32_t *or
     int64_t extra = (A.kept && !t->gather_for(B)) ? (int64_t)B * t->n * (int64_t)sizeof(Partial) : 0;
     if (need + extra > (int64_t)kNoAllocScratchBytes) {
         extra = 0;
-        A.kept = nullptr;
-        A.slot0 = 0;
-        A.slots = A.chunks;
+        stream_whole(A);
     }
     A.part = reinterpret_cast<Partial *>(part);
     A.cut_ws = reinterpret_cast<float *>(static_cast<char *>(part) + ((part_bytes + extra + 255) & ~(int64_t)255));
