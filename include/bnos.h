@@ -464,8 +464,9 @@ bnos_status bnos_table_timing(bnos_table t, int32_t enable);
  * Such a launch also reads every tile summary of each pass (8 B per 256
  * entries) and, with one order per block, every sub-tile summary (8 B per 64
  * entries).  For a table with kept entries tiles_read counts the 64-entry tiles
- * (768 B) of the kept rows that each order's scan reads, and the streaming pass's
- * sub-tiles only while the score bound is off.  Synchronous.
+ * (768 B) of the kept rows that each order's scan reads -- all that it requests, the
+ * step behind its last one among them -- when one wavefront scans a row, and the
+ * streaming pass's sub-tiles only while the score bound is off.  Synchronous.
  */
 bnos_status bnos_table_tile_skip(bnos_table t, int32_t enable);
 

@@ -151,8 +151,10 @@ __global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
     if (threadIdx.x == 0) kept_store(view_of(A), b, node, kept_combine(s_part, nq));
 }
 
-// Measurement only: the 64-entry tiles of the kept rows k_score_kept (stop) or
-// k_kept_partials reads for these orders, one count per (order, node).
+// Measurement only: the 64-entry tiles of the kept rows that scans down to the gap (stop), or of
+// whole rows, read for these orders, one count per (order, node).  One wavefront scans a row's
+// stripes in turn, as k_score_kept does; with several, a stripe may start before another has
+// found the gap and read a step or two more.
 __global__ __launch_bounds__(kScoreThreads) void k_count_kept(ScoreArgs A, int stop, unsigned *__restrict__ counts)
 {
     const int b = blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -1252,7 +1252,7 @@ __device__ __forceinline__ int ordered_f32(float x)
 // Scan of stripe q of a row of `len` entries for the predecessor complement np.  STOP: end at the
 // gap (else the whole stripe); then *hint (LDS, ordered_f32 of -inf at first) holds the highest
 // gap end that any stripe of the row has found, and no entry below it is scanned for.  `steps`
-// (may be null) is raised by the steps folded.
+// (may be null) is raised by the steps read.
 template <bool STOP>
 __device__ __forceinline__ KeptAcc kept_scan(const uint64_t *__restrict__ km, const float *__restrict__ ks, int len,
                                              int q, uint64_t np, int lane, int *hint, int *steps = nullptr)
@@ -1286,7 +1286,7 @@ __device__ __forceinline__ KeptAcc kept_scan(const uint64_t *__restrict__ km, co
     }
     if (shared && S.found == 2 && lane == 0) atomicMax(hint, ordered_f32(S.stop));
     S.a.s = wave_sum_u64(S.a.s);
-    if (steps) *steps += t;
+    if (steps) *steps += t + 2 < ns ? t + 2 : ns;            // the step the scan ended at, and the one requested behind it
     return S.a;
 }
 

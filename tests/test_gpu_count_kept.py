@@ -1,0 +1,71 @@
+"""bnos_table_count_tiles on kept rows against a plain emulation of the scan: every step it requests."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1210_5128_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+STEP, GAP = 256, np.float32(60)
+
+
+def gap_below(b, one_lower=True):
+    """60 below b: the nearest float, or the next one where that is less than 60 away; the build's list of
+    kept entries leaves none out there."""
+    g = np.float32(b - GAP)
+    if one_lower and np.float32(b - g) < GAP:
+        g = np.nextafter(g, np.float32(-np.inf))
+    return g if np.float32(b - g) >= GAP else np.float32(-np.inf)
+
+
+def kept_row(masks, scores):
+    """A row's kept entries (no subset 60 nats above and two above an entry), best score first."""
+    at = {int(m): x for m, x in zip(masks, scores)}
+    top, keep = {}, []
+    for m in sorted(at, key=lambda m: (bin(m).count("1"), m)):
+        bits = [1 << b for b in range(64) if m >> b & 1]
+        below = max((top[m ^ b] for b in bits), default=np.float32(-np.inf))
+        top[m] = max(at[m], below)
+        if len(bits) >= 2:
+            own = sorted([at[m ^ b] for b in bits] + [at[0]])
+            if at[m] < gap_below(below, False) and at[m] < own[-2]:
+                continue
+        keep.append(m)
+    keep.sort(key=lambda m: (-at[m], m))
+    return keep, np.array([at[m] for m in keep], dtype=np.float32)
+
+
+def steps_read(keep, x, pred):
+    ns = -(-len(keep) // STEP)
+    found, stop = [], np.float32(-np.inf)
+    for t in range(ns):
+        if x[t * STEP] < stop:
+            return min(t + 2, ns)
+        found += [x[i] for i in range(t * STEP, min((t + 1) * STEP, len(keep))) if keep[i] & ~pred == 0][:2]
+        if len(found) >= 2:
+            stop = min(gap_below(found[0]), found[1])
+    return ns
+
+
+@pytest.mark.parametrize("n,K,N,seed", [(8, 3, 200, 8), (13, 5, 600, 2), (13, 5, 1500, 13)])
+def test_count_of_kept_tiles(n, K, N, seed):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1210_5128_amd import bnos
+    net = datagen.random_network(n, N, (2, 3), 3, seed=seed)
+    t = bnos.build_score_table(net.data, net.arities, K)
+    try:
+        rows = [kept_row(*t.export(i)) for i in range(n)]
+        assert sum(len(k) for k, _ in rows) == t.kept_entries()
+        orders = np.concatenate([datagen.random_orders(n, 5, seed=4), np.asarray(net.perm, dtype=np.int32)[None]])
+        want = 0
+        for o in orders:
+            seen = 0
+            for v in o:
+                want += 4 * steps_read(*rows[v], seen)
+                seen |= 1 << int(v)
+        assert t.count_tiles(torch.from_numpy(np.ascontiguousarray(orders)).cuda())[0] == want
+    finally:
+        t.free()
