@@ -49,7 +49,9 @@ def steps_read(keep, x, pred):
     return ns
 
 
-@pytest.mark.parametrize("n,K,N,seed", [(8, 3, 200, 8), (13, 5, 600, 2), (13, 5, 1500, 13)])
+@pytest.mark.parametrize("n,K,N,seed", [
+    (8, 3, 200, 8), (13, 5, 600, 2), (13, 5, 1500, 13),
+    (12, 6, 400, 12), (13, 5, 600, 1)])       # best scores whose gap's end rounds towards them
 def test_count_of_kept_tiles(n, K, N, seed):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
