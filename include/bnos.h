@@ -124,9 +124,10 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
  * alone.  *entries = kept entries of all rows, 0 for a table that has none listed
  * (more per row on average than a sixteenth of it, at least 6,144 and at most
  * 16,384, or no memory for them within BNOS_MAX_DEVICE_BYTES); the streaming pass
- * then serves it.  Fewer than 4 chains with uniform swaps on a table with many
- * kept entries are streamed too, so there the number of chains can move a chain's
- * log-sum-exps in the last bits, as a launch shape can (bnos_chains_autotune).
+ * then serves it.  Chains with uniform swaps on a table with many kept entries are
+ * streamed too when they are few (1 to 3, 4 to 15 or more have their own lines), so
+ * there the number of chains can move a chain's log-sum-exps in the last bits, as a
+ * launch shape can (bnos_chains_autotune).
  */
 bnos_status bnos_table_kept(bnos_table t, int64_t *entries);
 
@@ -391,7 +392,8 @@ bnos_status bnos_run_chains(bnos_table t, const bnos_chain_cfg *cfg, bnos_chain_
  * blocks, one block per chain of every table).  tables[k] gets
  * cfg->chains chains whose RNG stream ids are chain_offset + k*chains + c,
  * and its own state states[k] (sized by tables[k]'s n).  Each chain's
- * trajectory is the one bnos_run_chains gives it with that chain id.
+ * trajectory is the one bnos_run_chains gives it with that chain id (of as many
+ * chains; see bnos_table_kept).
  * T is 1..4096; a table may appear once.  With the score bound on, the
  * per-iteration launch that lists each node's chains also holds one
  * wavefront per (chain, node) pair; a call whose pairs (summed over the

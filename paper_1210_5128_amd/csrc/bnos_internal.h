@@ -59,19 +59,27 @@ constexpr float kBoundGap = 60.0f;
 // 6,200 of 489,406 per row on average, depending on the data, with single rows
 // of 100,000.  A table that keeps more than kept_mean() per row on average (few
 // samples of binary variables: nearly all of them) stays with the streaming pass,
-// which shares each streamed tile between orders.  The line: a chain's iteration
-// scans its kept rows at 20 to 45 us per 10,000 entries, and streams rows of S
-// entries in 20 us and more, the longer the rows the more.  One chain, kept against
-// streamed, us per iteration: 7,547 of 7,547 entries kept 22 / 22, 10,903 of 10,903
-// 34 / 21, 14,439 of 15,276 26 / 23, 31,284 of 489,406 106 / 63; and 32 chains with
-// 7,343 of 396,607 kept 49 / 91.  256 orders: 7,547 kept 43 / 36 us, 10,903
-// kept 63 / 44.  So up to a sixteenth of the row, at least 6,144 and at most 16,384.
+// which shares each streamed tile between orders.  The lines, from 1,044 tables of 16 to
+// 60 nodes drawn below them, scored both ways: with up to 6,144 kept entries per row
+// one order takes 0.68 times the streamed time (geometric mean; over 5% more on 15 of 906
+// tables), 256 orders 0.25 times; whole rows cross over near there (256 orders: 5,036 of 5,036
+// entries kept 29 / 28 us, 6,018 of 6,018 38 to 49 / 40 to 44, 7,547 of 7,547 43 / 36).
+// Above it rows are long enough to be streamed in many tiles: with 6,144 to 16,384, at most a
+// sixteenth of the row, 0.43 times for one order and 0.23 for 256 (over 5% more on 11
+// and none of 138; eight orders on 19, up to 2.3 times: tables with one row of 400 steps and
+// more); 18,184 of 231,526 entries 30 / 30 and 134 / 512 us, 39,150 of 489,406 68 / 91 and 245 / 857.
 constexpr int kKeptMeanLow = 6144, kKeptMeanHigh = 16384;
 constexpr int64_t kept_mean(int64_t S)
 {
     return S / 16 < kKeptMeanLow ? kKeptMeanLow : (S / 16 > kKeptMeanHigh ? kKeptMeanHigh : S / 16);
 }
-constexpr int kKeptStepsFew = 1600;        // see chains_fold_kept
+// Steps of all kept rows up to which uniform chains run on them, from S entries per row; see
+// chains_fold_kept.
+constexpr int64_t kept_chain_steps(int C, int64_t S)
+{
+    const int64_t least = C < 4 ? 600 : (C < 16 ? 800 : 1600), share = S / (C < 4 ? 256 : (C < 16 ? 150 : 100));
+    return least > share ? least : share;
+}
 constexpr int kKeptCap = 1 << 19;         // entries of one row
 constexpr int kKeptRun = 16384;           // sort keys of one block: 128 KB of LDS
 constexpr int kKeptTiles = 4;             // 64-entry tiles a wavefront takes per step; rows are padded to whole steps
@@ -197,13 +205,18 @@ struct TableT {
     // adds the other entries)
     bool kept_rows() const { return d_kmask != nullptr && score_bound && tile_skip; }
     // whether C chains fold their kept rows apart from the other entries, with the score bound on (where
-    // they need nothing else) and off alike, so that both add FP32 sums in the same order: a few chains of
-    // a table with many steps of kept entries are better streamed whole (57 nodes, 1,660 steps: one
-    // chain 48 us per iteration against 34, four 48 against 47, 32 49 against 91; 60 nodes, 1,480
-    // steps: one chain 30 against 62, four 30 against 96); the learned proposal's streamed step alone takes 46
+    // they need nothing else) and off alike, so that both add FP32 sums in the same order.  An
+    // iteration on kept rows takes the longer the more steps they have, and little more for more
+    // chains; streamed, it takes the longer the longer the rows, and the more chains.  Kept / streamed us
+    // per iteration: 57 nodes, 1,665 steps, 1 chain 48 / 31, 4 chains 48 / 44, 16 48 / 79, 256 52 / 314;
+    // 45 nodes and 14,235 entries per row, 753 steps, 26 / 21, 28 / 25, 28 / 37, 31 / 62; 60 nodes, 1,480 steps,
+    // 1 chain 30 / 61.  Of the 1,044 tables of kept_mean(), on this side of the lines 1 is over 5% slower
+    // kept for 1 to 3 chains, 6 (table, count) pairs for 4 to 15 and 1 for more; with one line of 1,600
+    // steps below 4 chains and none above it was 65, 39 and 7.  The learned proposal's streamed
+    // step takes 40 to 60 us alone: on 347 tables of 500 kept steps and more, one chain is slower kept on 8.
     bool chains_fold_kept(int C, bool learned) const
     {
-        return d_kmask != nullptr && (learned || C >= 4 || kept_steps <= kKeptStepsFew);
+        return d_kmask != nullptr && (learned || kept_steps <= kept_chain_steps(C, S));
     }
     // whether they run on the kept rows alone
     bool kept_chains(int C, bool learned) const { return kept_rows() && chains_fold_kept(C, learned); }
