@@ -968,17 +968,29 @@ extern "C" bnos_status bnos_score_orders_noalloc(bnos_table h, const int32_t *or
         A.part = reinterpret_cast<Partial *>(part);      // one slot per (order, node), less than what was checked
         return launch_kept(t, A, st, false);
     }
-    // kept rows beside the streaming pass (bound off) take one slot more; where that passes the
-    // array, the pass streams the whole rows
-    int64_t extra = (A.kept && !t->gather_for(B)) ? (int64_t)B * t->n * (int64_t)sizeof(Partial) : 0;
-    if (need + extra > (int64_t)kNoAllocScratchBytes) {
-        extra = 0;
-        stream_whole(A);
-    }
     A.part = reinterpret_cast<Partial *>(part);
-    A.cut_ws = reinterpret_cast<float *>(static_cast<char *>(part) + ((part_bytes + extra + 255) & ~(int64_t)255));
-    if (t->gather_for(B)) s = launch_gather(t, A, st, false);
-    else s = launch_stream(t, A, st, 0, false);
-    if (s != BNOS_OK) return s;
-    return launch_merge(A, st);
+    if (t->gather_for(B)) {
+        if ((s = launch_gather(t, A, st, false)) != BNOS_OK) return s;
+        return launch_merge(A, st);
+    }
+    // kept rows beside the streaming pass (bound off) take one slot more: where that passes the
+    // array, the orders go in two halves (the slot is at most 24 bytes beside 28)
+    const int64_t per = (int64_t)t->n * (A.slots * (int64_t)sizeof(Partial) + (int64_t)sizeof(float));
+    const int half = per * B + 256 > (int64_t)kNoAllocScratchBytes && A.slots > slots ? (B + 1) / 2 : B;
+    for (int b = 0; b < B; b += half) {
+        ScoreArgs P = A;
+        const int64_t at = (int64_t)b * t->n;
+        P.B = B - b < half ? B - b : half;
+        P.orders += at;
+        P.lse += b;
+        P.maxs += b;
+        P.best += at;
+        if (P.node_lse) P.node_lse += at;
+        if (P.node_second) P.node_second += at;
+        const int64_t cuts = ((int64_t)P.B * A.slots * t->n * (int64_t)sizeof(Partial) + 255) & ~(int64_t)255;
+        P.cut_ws = reinterpret_cast<float *>(static_cast<char *>(part) + cuts);
+        if ((s = launch_stream(t, P, st, pick_bt(t, B), false)) != BNOS_OK) return s;
+        if ((s = launch_merge(P, st)) != BNOS_OK) return s;
+    }
+    return BNOS_OK;
 }
