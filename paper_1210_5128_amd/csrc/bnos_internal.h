@@ -144,6 +144,8 @@ struct TableT {
     // order-scoring workspace: per (order, node, chunk) partial reductions
     void *d_part = nullptr;
     int64_t part_bytes = 0;         // capacity in bytes
+    void *d_kpart = nullptr;        // and of the kept rows: per (order, node) one
+    int64_t kpart_bytes = 0;
 
     // kernel timing: a ring of kEventRing event pairs, created when timing is
     // first enabled; launches in flight occupy ev_count slots from ev_head on

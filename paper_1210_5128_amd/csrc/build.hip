@@ -47,7 +47,7 @@ int64_t TableT::device_bytes() const
 {
     return (int64_t)n * S_pad * (int64_t)(sizeof(uint64_t) + sizeof(float)) + (int64_t)n * N_pad +
            (int64_t)n * (int64_t)(sizeof(int32_t) + n * sizeof(double) + 5 * sizeof(double)) + 64 * 8 * 8 +
-           part_bytes + (int64_t)n * (S_pad / 256) * 8 + (int64_t)n * (S_pad / 64) * 8 +
+           part_bytes + kpart_bytes + (int64_t)n * (S_pad / 256) * 8 + (int64_t)n * (S_pad / 64) * 8 +
            (int64_t)n * (S_pad / 4) * 8 + (int64_t)n * (S_pad / 256) * 4 + (int64_t)n * kBoundSlots * 12 +
            (d_kmask ? kept_bytes() : 0);
 }
@@ -1489,6 +1489,7 @@ static void free_device(TableT *t)
     hipFree(t->d_cmask);
     hipFree(t->d_cscore);
     hipFree(t->d_part);
+    hipFree(t->d_kpart);
     hipHostFree(t->h_result);
     free_kept(t);
     for (auto e : t->ev_start) hipEventDestroy(e);

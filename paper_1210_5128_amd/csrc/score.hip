@@ -289,37 +289,38 @@ int pick_bt(const TableT *t, int B)
     return bt;
 }
 
-// Scoring workspace of at least `need` bytes (`want` when it has to be allocated).
-static bnos_status ensure_bytes(TableT *t, int64_t need, int64_t want)
+// A workspace of at least `need` bytes (`want` when it has to be allocated).
+static bnos_status ensure_bytes(void *&buf, int64_t &held, int64_t need, int64_t want)
 {
-    if (t->part_bytes >= need) return BNOS_OK;
+    if (held >= need) return BNOS_OK;
     // A launch still in flight may use the old buffer.
     BNOS_HIP(hipDeviceSynchronize());
-    BNOS_HIP(hipFree(t->d_part));
-    t->d_part = nullptr;
-    t->part_bytes = 0;
+    BNOS_HIP(hipFree(buf));
+    buf = nullptr;
+    held = 0;
     if (want < need) want = need;
-    hipError_t e = hipMalloc(&t->d_part, (size_t)want);
+    hipError_t e = hipMalloc(&buf, (size_t)want);
     if (e != hipSuccess) {
+        buf = nullptr;
         set_error(std::string("hipMalloc scoring workspace: ") + hipGetErrorString(e));
-        t->d_part = nullptr;
         return e == hipErrorOutOfMemory ? BNOS_E_NOMEM : BNOS_E_DEVICE;
     }
-    t->part_bytes = want;
+    held = want;
     return BNOS_OK;
 }
 
 // For up to `B` orders: the chunk partials.
 bnos_status ensure_workspace(TableT *t, int B)
 {
-    return ensure_bytes(t, t->workspace_bytes_for(B), t->workspace_bytes_for(64));
+    return ensure_bytes(t->d_part, t->part_bytes, t->workspace_bytes_for(B), t->workspace_bytes_for(64));
 }
 
-// For up to `B` orders scored from the kept rows: one partial per (order, node).
+// For up to `B` orders scored from the kept rows: one partial per (order, node).  A buffer of its own: a
+// captured launch keeps its address, and the streaming pass's, which is larger, may be allocated later.
 static bnos_status ensure_kept_workspace(TableT *t, int B)
 {
     const int64_t per = (int64_t)t->n * (int64_t)sizeof(Partial);
-    return ensure_bytes(t, B * per, 64 * per);
+    return ensure_bytes(t->d_kpart, t->kpart_bytes, B * per, 64 * per);
 }
 
 // Adds the oldest timed launch in the ring to the totals and frees its slot.
@@ -571,7 +572,10 @@ static bnos_status score_impl(TableT *t, const int32_t *orders, int B, double *l
     bnos_status s = kept ? ensure_kept_workspace(t, B) : ensure_workspace(t, B);
     if (s != BNOS_OK) return s;
     ScoreArgs A = score_args(t, orders, B, lse, maxs, best, node_lse, node_second);
-    if (kept) return launch_kept(t, A, st);
+    if (kept) {
+        A.part = reinterpret_cast<Partial *>(t->d_kpart);
+        return launch_kept(t, A, st);
+    }
     if (t->gather_for(B)) s = launch_gather(t, A, st);
     else s = launch_stream(t, A, st, 0);
     if (s != BNOS_OK) return s;
@@ -816,7 +820,8 @@ extern "C" bnos_status bnos_table_autotune(bnos_table h, const int32_t *orders, 
     if (kept && e == hipSuccess && s == BNOS_OK) {
         t->tuned_cs[bk] = best_cs;
         if ((s = ensure_kept_workspace(t, B)) == BNOS_OK) {
-            const ScoreArgs A = score_args(t, orders, B, d_out, d_out + B, d_best, nullptr, nullptr);
+            ScoreArgs A = score_args(t, orders, B, d_out, d_out + B, d_best, nullptr, nullptr);
+            A.part = reinterpret_cast<Partial *>(t->d_kpart);
             for (int r = 0; r <= reps && s == BNOS_OK; ++r) {
                 if (r == 1) e = hipEventRecord(e0, st);
                 s = launch_kept(t, A, st, false);
