@@ -4,6 +4,7 @@
 // kernel, and sweeps of iterations captured as HIP graphs.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -998,38 +999,40 @@ __global__ __launch_bounds__(W * 64) void k_chain_run(const TabView *__restrict_
 }
 
 // The kept entries' partial (slot 0) of every (chain, window node) pair, whole rows, for sweeps
-// whose streaming pass adds the other entries (score bound off); one wavefront per pair.  The grid
-// is at most kKeptBlocks: the pairs of a call may pass what one launch can hold (2^32 work-items).
+// whose streaming pass adds the other entries (score bound off); W wavefronts per pair (kept_waves).
+// The grid is at most kKeptBlocks: the pairs of a call may pass what one launch can hold (2^32
+// work-items).
 constexpr int64_t kKeptBlocks = 1 << 20;
-__global__ __launch_bounds__(kScoreThreads) void k_chain_kept(const TabView *__restrict__ tviews,
-                                                              const ChainView *__restrict__ views,
-                                                              const int64_t *__restrict__ node_base, int T, int C)
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_chain_kept(const TabView *__restrict__ tviews,
+                                                       const ChainView *__restrict__ views,
+                                                       const int64_t *__restrict__ node_base, int T, int C)
 {
-    __shared__ KeptAcc s_part[kScoreThreads / 64][kStripes];
+    __shared__ KeptAcc s_part[kStripes];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    KeptAcc *part = s_part[wave];
     const int64_t nodes = node_base[T];
-    for (int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + wave; g < nodes * C;
-         g += (int64_t)gridDim.x * (kScoreThreads / 64)) {   // uniform per wavefront
+    for (int64_t g = blockIdx.x; g < nodes * C; g += gridDim.x) {      // uniform over the block
         const int c = (int)(g / nodes);
         const int64_t gn = g - (int64_t)c * nodes;
         const int k = find_segment(node_base, T, gn);
         const ChainView &H = views[k];
         const TabView &V = tviews[k];
         const int node = (int)(gn - node_base[k]);
-        if (!V.kept || !((H.wmask[c] >> node) & 1ull)) continue;   // uniform
+        if (!V.kept || !((H.wmask[c] >> node) & 1ull)) continue;
         const int n = H.n;
         const uint8_t *pp = H.ppos + (int64_t)c * n;
         const int pv = pp[node], pu = pp[lane < n ? lane : n - 1];
         const uint64_t pred = __ballot(lane < n && pu < pv);
         const int64_t row = V.klen[2 * n + node];
         const int len = V.klen[node], nq = kept_stripes_of(len);
-        for (int q = 0; q < nq; ++q) {
+        for (int q = wave; q < nq; q += W) {
             const KeptAcc a = kept_scan<false>(V.kmask + row, V.kscore + row, len, q, ~pred, lane, nullptr);
-            if (lane == 0) part[q] = a;
+            if (lane == 0) s_part[q] = a;
         }
-        if (lane == 0) kept_store(V, c, node, kept_combine(part, nq));
+        if (W > 1) __syncthreads();
+        if (threadIdx.x == 0) kept_store(V, c, node, kept_combine(s_part, nq));
+        if (W > 1) __syncthreads();              // the next pair's stripes
     }
 }
 
@@ -1297,11 +1300,14 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
         }
     }
     bool any_bound = false, any_kept = false;    // of the streamed tables
+    int kept_max = 0;                            // and their longest kept row, in steps
     for (int q = Tk; q < T; ++q) {
         any_bound = any_bound || cv[q].cuts != nullptr;
         any_kept = any_kept || tv[q].kept != nullptr;
+        if (tv[q].kept) kept_max = std::max(kept_max, tabs[order[q]]->kept_steps_max);
     }
     const int64_t pairs = node_base[Ts] * (int64_t)C;
+    const int kw = any_kept ? kept_waves(kept_max, pairs) : 1;
     // blocks of k_worklist that compute the score-bound cuts after the list blocks
     const int64_t cut_blocks = any_bound ? (pairs + kListThreads / 64 - 1) / (kListThreads / 64) : 0;
     if (Tk > 0) hipLaunchKernelGGL(k_chain_init, dim3(run_chains), dim3(64), 0, us, d_cv, d_run, Tk);
@@ -1312,9 +1318,11 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
                            d_cvs, d_node, Ts, C);
         dim3 grid((unsigned)((blk_base[Ts] + kXcds - 1) / kXcds * kXcds), groups);   // padded for xcd_block
         if (any_kept) {                          // score bound off: slot 0, then every entry not in it
-            const int64_t blocks = (pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
-            hipLaunchKernelGGL(k_chain_kept, dim3((unsigned)(blocks < kKeptBlocks ? blocks : kKeptBlocks)),
-                               dim3(kScoreThreads), 0, q, d_tvs, d_cvs, d_node, Ts, C);
+            const dim3 kgrid((unsigned)(pairs < kKeptBlocks ? pairs : kKeptBlocks));
+            if (kw == 1) hipLaunchKernelGGL(k_chain_kept<1>, kgrid, dim3(64), 0, q, d_tvs, d_cvs, d_node, Ts, C);
+            else if (kw == 2) hipLaunchKernelGGL(k_chain_kept<2>, kgrid, dim3(128), 0, q, d_tvs, d_cvs, d_node, Ts, C);
+            else if (kw == 4) hipLaunchKernelGGL(k_chain_kept<4>, kgrid, dim3(256), 0, q, d_tvs, d_cvs, d_node, Ts, C);
+            else hipLaunchKernelGGL(k_chain_kept<8>, kgrid, dim3(512), 0, q, d_tvs, d_cvs, d_node, Ts, C);
             if (bt == 8) hipLaunchKernelGGL((k_score_multi<8, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
             else if (bt == 4) hipLaunchKernelGGL((k_score_multi<4, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);
             else if (bt == 2) hipLaunchKernelGGL((k_score_multi<2, true>), grid, dim3(kScoreThreads), 0, q, d_tvs, d_blk, Ts);

@@ -459,6 +459,24 @@ static void launch_bt(const ScoreArgs &A, int nblocks_x, hipStream_t st, hipEven
     else hipLaunchKernelGGL(k_score<BT>, grid, dim3(kScoreThreads), 0, st, A);
 }
 
+template <int W, bool STOP>
+static void launch_partials_w(const ScoreArgs &A, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+{
+    const dim3 grid((unsigned)A.B, (unsigned)A.n);
+    if (e0) hipExtLaunchKernelGGL(k_kept_partials<W, STOP>, grid, dim3(W * 64), 0, st, e0, e1, 0, A);
+    else hipLaunchKernelGGL((k_kept_partials<W, STOP>), grid, dim3(W * 64), 0, st, A);
+}
+
+template <bool STOP>
+static void launch_partials(const TableT *t, const ScoreArgs &A, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+{
+    const int w = kept_waves(t->kept_steps_max, (int64_t)A.B * A.n);
+    if (w == 1) launch_partials_w<1, STOP>(A, st, e0, e1);
+    else if (w == 2) launch_partials_w<2, STOP>(A, st, e0, e1);
+    else if (w == 4) launch_partials_w<4, STOP>(A, st, e0, e1);
+    else launch_partials_w<8, STOP>(A, st, e0, e1);
+}
+
 // The streaming pass (k_score) with the table's block shape; timed when enabled.
 // The workspace must already hold A.B orders.
 bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt, bool allow_timing)
@@ -471,9 +489,7 @@ bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt,
     }
     const int nbx = t->n * A.chunks;
     ScoreArgs A2 = A;
-    if (A.kept) {
-        hipLaunchKernelGGL((k_kept_partials<1, false>), dim3((unsigned)A.B, (unsigned)A.n), dim3(64), 0, st, A);
-    }
+    if (A.kept) launch_partials<false>(t, A, st, nullptr, nullptr);      // slot 0: the kept entries, whole rows
     if (bt > 1 && A.tmax && A.tand && A.cut_ws) {
         // every (order, node) cut once, before the blocks that stream the node's row
         const int64_t pairs = (int64_t)A.B * A.n;
@@ -515,14 +531,6 @@ bnos_status launch_merge(const ScoreArgs &A, hipStream_t st)
     return BNOS_OK;
 }
 
-template <int W>
-static void launch_partials(const ScoreArgs &A, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
-{
-    const dim3 grid((unsigned)A.B, (unsigned)A.n);
-    if (e0) hipExtLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, e0, e1, 0, A);
-    else hipLaunchKernelGGL((k_kept_partials<W, true>), grid, dim3(W * 64), 0, st, A);
-}
-
 // Scoring from the kept rows; timed when enabled (each order makes its own pass).
 bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timing)
 {
@@ -540,16 +548,8 @@ bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timin
         BNOS_HIP(hipGetLastError());
         return BNOS_OK;
     }
-    // W wavefronts per (order, node): a longest row of M steps takes M / W of them one after the
-    // other (0.17 us each), and every wavefront of a pair costs the chip 0.7 ns, so with P pairs
-    // W^2 = 235 M / P is the least of the sum; the power of two nearest.  (60 nodes, M = 50: one
-    // order 12.6 / 11.6 / 10.4 / 10.7 us for W = 1 / 2 / 4 / 8, 64 orders 19.7 / 20.7 / 24.8 / 36.8.)
-    const double w2 = 235.0 * t->kept_steps_max / ((double)A.B * t->n);
     A.slots = 1;
-    if (w2 < 2.0) launch_partials<1>(A, st, e0, e1);
-    else if (w2 < 8.0) launch_partials<2>(A, st, e0, e1);
-    else if (w2 < 32.0) launch_partials<4>(A, st, e0, e1);
-    else launch_partials<8>(A, st, e0, e1);
+    launch_partials<true>(t, A, st, e0, e1);
     BNOS_HIP(hipGetLastError());
     return launch_merge(A, st);
 }

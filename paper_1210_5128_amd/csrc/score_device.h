@@ -1326,6 +1326,16 @@ __device__ __forceinline__ Acc kept_combine(const KeptAcc *P, int nq)
     return r;
 }
 
+// Wavefronts per (order, node), W, for P pairs and a longest row of M steps: M / W of them one after
+// the other (0.17 us each), and every wavefront of a pair costs the chip 0.7 ns, so W^2 = 235 M / P
+// is the least of the sum; the power of two nearest.  (60 nodes, M = 50: one order 12.6 / 11.6 /
+// 10.4 / 10.7 us for W = 1 / 2 / 4 / 8, 64 orders 19.7 / 20.7 / 24.8 / 36.8.)
+inline int kept_waves(int M, int64_t P)
+{
+    const double w2 = 235.0 * M / (double)P;
+    return w2 < 2.0 ? 1 : (w2 < 8.0 ? 2 : (w2 < 32.0 ? 4 : 8));
+}
+
 // Slot 0 of (order b, node).
 __device__ __forceinline__ void kept_store(const TabView &V, int b, int node, const Acc &a)
 {
