@@ -440,7 +440,9 @@ bnos_status bnos_chains_set_launch(bnos_table t, int32_t chains, int32_t chunk_s
  * order-scoring launch of this table (bnos_score_orders / bnos_score_order),
  * starting with the first, carries a pair of HIP events that take the
  * streaming kernel's own start and end on the launch stream
- * (hipExtLaunchKernel); 0 disables, negative values are E_RANGE.  (A launch
+ * (hipExtLaunchKernel; on a table with kept entries those of the pass over
+ * them, or, while that leaves the other entries to the streaming kernel, the
+ * former's start and the latter's end); 0 disables, negative values are E_RANGE.  (A launch
  * with events costs the host about 15 us more than one without: for short
  * launches, sample with k > 1 so that the timed loop is not host-bound.)  bnos_table_timing_read waits for them and
  * returns the sum of the streaming kernels' durations (ms), the number of

@@ -422,7 +422,7 @@ static void stream_whole(ScoreArgs &A)
 template <void (*KERNEL)(ScoreArgs)>
 static void launch_one(dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, const ScoreArgs &A)
 {
-    if (e0) hipExtLaunchKernelGGL(KERNEL, grid, dim3(kScoreThreads), 0, st, e0, e1, 0, A);
+    if (e1) hipExtLaunchKernelGGL(KERNEL, grid, dim3(kScoreThreads), 0, st, e0, e1, 0, A);
     else hipLaunchKernelGGL(KERNEL, grid, dim3(kScoreThreads), 0, st, A);
 }
 
@@ -489,7 +489,10 @@ bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt,
     }
     const int nbx = t->n * A.chunks;
     ScoreArgs A2 = A;
-    if (A.kept) launch_partials<false>(t, A, st, nullptr, nullptr);      // slot 0: the kept entries, whole rows
+    if (A.kept) {                                // slot 0: the kept entries, whole rows
+        launch_partials<false>(t, A, st, e0, nullptr);       // (timed from here)
+        e0 = nullptr;
+    }
     if (bt > 1 && A.tmax && A.tand && A.cut_ws) {
         // every (order, node) cut once, before the blocks that stream the node's row
         const int64_t pairs = (int64_t)A.B * A.n;
