@@ -135,11 +135,10 @@ struct TableT {
     int64_t kept_steps = 0;         // scan steps of all kept rows
     int kept_steps_max = 0;         // and of the longest one
 
-    // bnos_score_order's buffers, held by one call at a time: the order (after the arities) and a
-    // pinned buffer the results are written to, made by the first call
+    // bnos_score_order's buffers, held by one call at a time, after the arities
     std::mutex host_mu;
     int32_t *d_order = nullptr;     // [64]
-    char *h_result = nullptr;
+    double *d_result = nullptr;     // two sums, then a mask per node
 
     // order-scoring workspace: per (order, node, chunk) partial reductions
     void *d_part = nullptr;
@@ -228,6 +227,7 @@ struct TableT {
     }
 };
 
+constexpr size_t kHostResult = sizeof(double) * 2 + sizeof(uint64_t) * 64;
 constexpr uint32_t kMagic = 0xB0A5C0DEu;
 
 void set_error(const std::string &msg);

@@ -1490,7 +1490,6 @@ static void free_device(TableT *t)
     hipFree(t->d_cscore);
     hipFree(t->d_part);
     hipFree(t->d_kpart);
-    hipHostFree(t->h_result);
     free_kept(t);
     for (auto e : t->ev_start) hipEventDestroy(e);
     for (auto e : t->ev_stop) hipEventDestroy(e);
@@ -1640,9 +1639,10 @@ extern "C" bnos_status bnos_build_score_table(const int8_t *data, int64_t N, int
         return fail(e == hipErrorOutOfMemory ? BNOS_E_NOMEM : BNOS_E_DEVICE);           \
     }
     ALLOC(t->d_data, (size_t)n * t->N_pad);
-    ALLOC(t->d_nsets, kNsetsBytes + sizeof(int32_t) * (2 * n + 64));   // with the arities, uploaded together
+    ALLOC(t->d_nsets, kNsetsBytes + kHostResult + sizeof(int32_t) * (2 * n + 64));   // with the arities, uploaded together
     t->d_ar = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(t->d_nsets) + kNsetsBytes);
     t->d_order = t->d_ar + 2 * n;
+    t->d_result = reinterpret_cast<double *>(t->d_order + 64);
     ALLOC(t->d_prior, sizeof(double) * n * n);
     ALLOC(t->d_masks, sizeof(uint64_t) * (size_t)n * t->S_pad);
     ALLOC(t->d_scores, sizeof(float) * (size_t)n * t->S_pad);

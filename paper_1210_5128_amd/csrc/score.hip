@@ -534,6 +534,11 @@ bnos_status launch_merge(const ScoreArgs &A, hipStream_t st)
     return BNOS_OK;
 }
 
+// Short rows: a few steps per wavefront of one block (k_score_kept, without partials) take less than a
+// second launch would (8-20 nodes, up to 214 entries per row: 7.4 us per call against 9.8 at up
+// to 256 orders).
+static bool kept_short(const TableT *t) { return t->kept_steps <= kKeptWaves * 8 && t->kept_steps_max <= 4; }
+
 // Scoring from the kept rows; timed when enabled (each order makes its own pass).
 bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timing)
 {
@@ -542,9 +547,7 @@ bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timin
     if (allow_timing && t->timing && t->timing_seen++ % t->timing_every == 0) {
         if ((s = next_events(t, e0, e1, A.B)) != BNOS_OK) return s;
     }
-    if (t->kept_steps <= kKeptWaves * 8 && t->kept_steps_max <= 4) {
-        // short rows: a few steps per wavefront of one block take less than a second launch would
-        // (8-20 nodes, up to 214 entries per row: 7.4 us per call against 9.8 at up to 256 orders)
+    if (kept_short(t)) {
         const dim3 grid((unsigned)A.B), block(64 * (unsigned)(t->n < kKeptWaves ? t->n : kKeptWaves));
         if (e0) hipExtLaunchKernelGGL(k_score_kept, grid, block, 0, st, e0, e1, 0, A);
         else hipLaunchKernelGGL(k_score_kept, grid, block, 0, st, A);
@@ -561,7 +564,6 @@ bnos_status launch_kept(TableT *t, ScoreArgs A, hipStream_t st, bool allow_timin
 struct HostOrder {
     uint8_t v[64];
 };
-constexpr size_t kHostResult = sizeof(double) * 2 + sizeof(uint64_t) * 64;
 
 __global__ void k_order_in(HostOrder in, int32_t *__restrict__ order)
 {
@@ -572,7 +574,9 @@ static bnos_status score_impl(TableT *t, const int32_t *orders, int B, double *l
                               uint64_t *best, double *node_lse, float *node_second, hipStream_t st)
 {
     const bool kept = t->kept_rows() && !t->gather_for(B);
-    bnos_status s = kept ? ensure_kept_workspace(t, B) : ensure_workspace(t, B);
+    bnos_status s = BNOS_OK;
+    if (!kept) s = ensure_workspace(t, B);
+    else if (!kept_short(t)) s = ensure_kept_workspace(t, B);
     if (s != BNOS_OK) return s;
     ScoreArgs A = score_args(t, orders, B, lse, maxs, best, node_lse, node_second);
     if (kept) {
@@ -619,33 +623,21 @@ extern "C" bnos_status bnos_score_order(bnos_table h, const int32_t *order, doub
         seen |= 1ull << order[p];
     }
     BNOS_HIP(hipSetDevice(t->device));
-    // The order rides in a launch's arguments and the results are written to pinned memory, so a call
-    // waits once: 21 us at 8 nodes, 55 us with three device buffers and as many copies per call.
-    // Where no pinned memory is to be had, the results come through a device buffer.
+    // The order rides in a launch's arguments, and the results come back from the table's own buffer in one
+    // copy, which waits: 21 us at 8 nodes (57 us with three device buffers and as many copies per call),
+    // 24 us on a table's first call (71).  Results written to pinned memory took as long, but
+    // 63 to 85 us on the first call, which made that memory, and 20 us more to free the table.
     HostOrder in = {};
     for (int p = 0; p < n; ++p) in.v[p] = (uint8_t)order[p];
     std::lock_guard<std::mutex> lk(t->host_mu);
-    if (!t->h_result && hipHostMalloc((void **)&t->h_result, kHostResult, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        t->h_result = nullptr;
-    }
-    char *out = t->h_result, *dev = nullptr;
-    if (!out) BNOS_HIP(hipMalloc((void **)&dev, kHostResult));
-    double *sums = reinterpret_cast<double *>(out ? out : dev);
-    uint64_t *best = reinterpret_cast<uint64_t *>(sums + 2);
+    double *sums = t->d_result;
     hipLaunchKernelGGL(k_order_in, dim3(1), dim3(64), 0, nullptr, in, t->d_order);
-    hipError_t e = hipGetLastError();
-    bnos_status s = BNOS_OK;
-    if (e == hipSuccess) s = score_impl(t, t->d_order, 1, sums, sums + 1, best, nullptr, nullptr, nullptr);
-    char host[kHostResult];
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e == hipSuccess && s == BNOS_OK) {
-        if (out) std::memcpy(host, out, sizeof(double) * 2 + sizeof(uint64_t) * n);
-        else e = hipMemcpy(host, dev, kHostResult, hipMemcpyDeviceToHost);
-    }
-    hipFree(dev);
+    BNOS_HIP(hipGetLastError());
+    const bnos_status s = score_impl(t, t->d_order, 1, sums, sums + 1, reinterpret_cast<uint64_t *>(sums + 2), nullptr,
+                                     nullptr, nullptr);
     if (s != BNOS_OK) return s;
-    BNOS_HIP(e);
+    char host[kHostResult];
+    BNOS_HIP(hipMemcpy(host, sums, kHostResult, hipMemcpyDeviceToHost));
     std::memcpy(lse, host, sizeof(double));
     std::memcpy(maxs, host + sizeof(double), sizeof(double));
     if (best_parents) std::memcpy(best_parents, host + 2 * sizeof(double), sizeof(uint64_t) * n);
