@@ -425,7 +425,7 @@ __device__ __forceinline__ int family_base(const Subset &S, int c, int k)
 // sum, k_build's order over one family's cells and any lane assignment store the same score,
 // bit for bit.  lut_scale picks the unit: a family's sum stays below 2^62 of them, and a term,
 // rounded to the nearest, is closer to its FP64 value than FP64 additions of the family's
-// terms keep it (n = 60, N = 5,000: units of 2^-43).
+// terms keep it (n = 60, N = 5,000: units of 2^-45).
 
 // Adds this lane's cells (c, c + 64, ...) of the joint histogram: the N_ijk terms to `all`,
 // and to of[t] the N_ik terms of the family whose child is member t, each taken at the cell

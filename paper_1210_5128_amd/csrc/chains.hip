@@ -581,8 +581,9 @@ __global__ __launch_bounds__(kStepWaves * 64) void k_chain_step(const TabView *_
 // A swap changes the predecessor set of the nodes from one swapped position to the other,
 // by the swapped nodes for those between, by the whole range for the two themselves.  A
 // node whose kept entries that hold a changed node all score below the node's second best
-// and kBoundGap below its best keeps its result, bit for bit: no such entry was or becomes
-// the best or the second best, and their terms round to zero in its sum.  `kpm` (the
+// and kBoundGap below its best keeps its result: no such entry was or becomes the best or
+// the second best, and their terms are below what the sum resolves (see kept_combine; no bit
+// has differed from a scan in any case tested).  `kpm` (the
 // largest kept score of a row among the sets holding each node) answers that without a
 // scan for most nodes of the window.
 //

@@ -1108,10 +1108,13 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_multi(const TabView *__
 // exp(x - stripe's best), in FP32 and at most 1, is rounded to a multiple of
 // 2^-47 and added as a 64-bit integer (a row of at most kKeptCap entries deals a
 // stripe 2^16 of them).
-// kept_combine adds the stripes in order in FP64.  Every launch shape and every
-// path so gives the same bits.  A term below e^-kBoundGap of the row's best is
-// lost in the rounding of that sum, which is why a scan may stop there and why
-// the left-out entries of the row change no bit.  (The integers move a stripe's
+// kept_combine adds the stripes in order in FP64, so which lane or wavefront scans what moves no bit.
+// What it reads can differ: a scan stops at the gap below the row's best, which another stripe may
+// find sooner or later, and left-out entries of the row lie below it too.  Such terms, each below
+// e^-kBoundGap of the largest, round to zero in a stripe whose best is the row's; in one
+// with a lower best some do not, and reach the FP64 sum at less than 2^19 e^-kBoundGap = 5e-21
+// of it, where its own rounding is 1e-16: the FP32 result is the same in every case tested
+// (whatever the launch, the bound on and off), though no bit is proven.  (The integers move a stripe's
 // sum by at most 2^-48 per term; FP32, in which the partials hold it, resolves
 // 2^-24.)  The rounding is that of an FP64 addition to 48 = 1.5 * 2^5, whose ulp is
 // 2^-47: the integers are the bits of the results less those of 48.
