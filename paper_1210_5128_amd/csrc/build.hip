@@ -227,26 +227,6 @@ __global__ void k_lut(const int32_t *__restrict__ den, int rows, int64_t N, doub
     }
 }
 
-// Sum of a 64-bit integer over the wavefront (uniform), on the DPP lane network.
-template <int CTRL>
-__device__ __forceinline__ uint64_t lane_moved_u64(uint64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, false);
-    return ((uint64_t)hi << 32) | lo;
-}
-__device__ __forceinline__ uint64_t wave_total_u64(uint64_t v)
-{
-    v += lane_moved_u64<0xb1>(v);       // lane ^ 1, lane ^ 2, rows shifted by 4 and 8, row broadcasts
-    v += lane_moved_u64<0x4e>(v);
-    v += lane_moved_u64<0x114>(v);
-    v += lane_moved_u64<0x118>(v);
-    v += lane_moved_u64<0x142>(v);
-    v += lane_moved_u64<0x143>(v);
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
-}
-
 // Rank of a mask among the masks over `bits` bits with at most K set bits, in
 // ascending numeric order (the inverse of unrank_ascending).
 __device__ __forceinline__ int64_t rank_ascending(uint64_t m, int bits, int K, const int64_t *__restrict__ nsets)
@@ -499,13 +479,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_build_joint(
         case 6: subset_terms_j<6>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
         default: subset_terms_j<kMaxK + 1>(Sb, hist, lane, lut_row, lut, N + 1, all, of); break;
         }
-        all = wave_total_u64(all);
+        all = wave_sum_u64(all);
         uint64_t sum = 0ull;           // lane t: the family of member t
         int node = 0;
 #pragma unroll
         for (int t = 0; t <= kMaxK; ++t)
             if (t < Sb.j) {            // uniform
-                const uint64_t o = wave_total_u64(of[t]);
+                const uint64_t o = wave_sum_u64(of[t]);
                 sum = lane == t ? all - o : sum;
                 node = lane == t ? Sb.u[t] : node;
             }
@@ -647,7 +627,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_build(
                 }
                 sum -= (uint64_t)L_ik[nik];
             }
-            acc = (double)(int64_t)wave_total_u64(sum) * unit;
+            acc = (double)(int64_t)wave_sum_u64(sum) * unit;
         } else if (lut) {
             // lnG(c + a) - lnG(a) looked up per count (same FP64 values as computed below)
             const double *L_ijk = lut + (int64_t)lut_row[cells] * (N + 1);
@@ -1263,7 +1243,7 @@ __global__ __launch_bounds__(1024) void k_keep_top(int n, int64_t cap, int32_t *
 // Counts for explicit (node, parent mask) queries, with the build's counting code.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_counts(
-    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar, int n,
+    const uint8_t *__restrict__ data, int64_t N, int64_t N_pad, const int32_t *__restrict__ ar,
     int Q, const int32_t *__restrict__ qnode, const uint64_t *__restrict__ qmask,
     const int64_t *__restrict__ qoff, int cells_cap, uint32_t *__restrict__ out)
 {
@@ -1891,9 +1871,9 @@ extern "C" bnos_status bnos_counts(bnos_table h, int32_t Q, const int32_t *nodes
         else hipLaunchKernelGGL(k_counts_joint<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q,
                                 d_nodes, d_masks, d_off, cap_cells, d_out);
     } else {
-        if (four) hipLaunchKernelGGL(k_counts<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q,
+        if (four) hipLaunchKernelGGL(k_counts<4>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q,
                                      d_nodes, d_masks, d_off, cap_cells, d_out);
-        else hipLaunchKernelGGL(k_counts<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, t->n, Q, d_nodes,
+        else hipLaunchKernelGGL(k_counts<1>, grid, block, lds, 0, t->d_data, t->N, t->N_pad, t->d_ar, Q, d_nodes,
                                 d_masks, d_off, cap_cells, d_out);
     }
     CK(hipGetLastError());

@@ -17,17 +17,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ device helpers
 
-// Wavefront reductions on the data-parallel-primitive (DPP) lane network:
-// quad permutes (lane ^ 1, lane ^ 2), row shifts by 4 and 8 and the two row
-// broadcasts (lane 15 of a row to the next row, lane 31 to rows 2 and 3) leave
-// the reduction of all 64 lanes in lane 63, one VALU instruction per level; a
-// lane whose source does not exist reads the identity.  The association is
-// fixed, so the result does not depend on scheduling; readlane makes it uniform.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t identity)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, CTRL, 0xf, 0xf, false);
-}
+// (Wavefront reductions: see dpp_u32.)
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v, float identity)
 {
@@ -1127,24 +1117,6 @@ struct KeptAcc {
     uint64_t bm;
     uint64_t s;      // sum of the rounded terms in units of 2^-47
 };
-
-// Sum of a 64-bit integer over the wavefront, uniform.
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp_u64(uint64_t v)
-{
-    return ((uint64_t)dpp_u32<CTRL>((uint32_t)(v >> 32), 0u) << 32) | dpp_u32<CTRL>((uint32_t)v, 0u);
-}
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
-{
-    v += dpp_u64<0xb1>(v);
-    v += dpp_u64<0x4e>(v);
-    v += dpp_u64<0x114>(v);
-    v += dpp_u64<0x118>(v);
-    v += dpp_u64<0x142>(v);
-    v += dpp_u64<0x143>(v);
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
-}
 
 // A step's loads are issued, whether it will be needed or not, before the step in front of
 // it is folded: a step folds in a few hundred cycles, about what a load from L2 takes.
