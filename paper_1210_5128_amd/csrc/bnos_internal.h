@@ -263,8 +263,8 @@ constexpr uint32_t kMagic = 0xB0A5C0DEu;
 void set_error(const std::string &msg);
 bool handle_live(const TableT *t);
 void register_handle(TableT *t);
-void unregister_handle(TableT *t);
-
+bool unregister_handle(TableT *t);     // true when it was the last one
+void trim_result_buffers();            // after that: see take_result_buffer
 
 }  // namespace bnos
 

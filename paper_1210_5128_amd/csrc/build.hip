@@ -37,10 +37,11 @@ void register_handle(TableT *t)
     g_handles.insert(t);
 }
 
-void unregister_handle(TableT *t)
+bool unregister_handle(TableT *t)
 {
     std::lock_guard<std::mutex> lk(g_handles_mu);
     g_handles.erase(t);
+    return g_handles.empty();
 }
 
 int64_t TableT::device_bytes() const
@@ -1777,11 +1778,12 @@ extern "C" void bnos_table_free(bnos_table h)
 {
     TableT *t = reinterpret_cast<TableT *>(h);
     if (!t || !handle_live(t)) return;
-    unregister_handle(t);
+    const bool last = unregister_handle(t);
     hipDeviceSynchronize();
     t->magic = 0;
     free_device(t);
     delete t;
+    if (last) trim_result_buffers();
 }
 
 extern "C" bnos_status bnos_table_info(bnos_table h, int32_t *n, int32_t *K, int64_t *S, int64_t *bytes)

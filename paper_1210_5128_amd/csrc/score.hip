@@ -570,6 +570,65 @@ __global__ void k_order_in(HostOrder in, int32_t *__restrict__ order)
     order[threadIdx.x] = in.v[threadIdx.x];
 }
 
+// Pinned buffers of kHostResult bytes that a call takes and gives back, for all tables, devices and
+// threads.  At most kResultBuffers are kept while a table is live and one after the last is freed:
+// pinning and giving back take 60 us, which a program with one table at a time would pay for each
+// (build, first call and free of an 8-node table: 303 us with a buffer per table, 277 without any).
+constexpr size_t kResultBuffers = 8;
+struct ResultBuffers {
+    std::mutex mu;
+    std::vector<char *> kept;
+};
+static ResultBuffers &result_buffers()
+{
+    static ResultBuffers *const b = new ResultBuffers;       // not destroyed: a thread may still score at exit
+    return *b;
+}
+
+static char *take_result_buffer()
+{
+    ResultBuffers &b = result_buffers();
+    {
+        std::lock_guard<std::mutex> lk(b.mu);
+        if (!b.kept.empty()) {
+            char *p = b.kept.back();
+            b.kept.pop_back();
+            return p;
+        }
+    }
+    char *p = nullptr;
+    if (hipHostMalloc((void **)&p, kHostResult, hipHostMallocPortable) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+static void give_result_buffer(char *p)
+{
+    ResultBuffers &b = result_buffers();
+    {
+        std::lock_guard<std::mutex> lk(b.mu);
+        if (b.kept.size() < kResultBuffers) {
+            b.kept.push_back(p);
+            return;
+        }
+    }
+    hipHostFree(p);
+}
+
+void trim_result_buffers()
+{
+    ResultBuffers &b = result_buffers();
+    std::vector<char *> drop;
+    {
+        std::lock_guard<std::mutex> lk(b.mu);
+        while (b.kept.size() > 1) {
+            drop.push_back(b.kept.back());
+            b.kept.pop_back();
+        }
+    }
+    for (char *p : drop) hipHostFree(p);
+}
+
 static bnos_status score_impl(TableT *t, const int32_t *orders, int B, double *lse, double *maxs,
                               uint64_t *best, double *node_lse, float *node_second, hipStream_t st)
 {
@@ -623,21 +682,34 @@ extern "C" bnos_status bnos_score_order(bnos_table h, const int32_t *order, doub
         seen |= 1ull << order[p];
     }
     BNOS_HIP(hipSetDevice(t->device));
-    // The order rides in a launch's arguments, and the results come back from the table's own buffer in one
-    // copy, which waits: 21 us at 8 nodes (57 us with three device buffers and as many copies per call),
-    // 24 us on a table's first call (71).  Results written to pinned memory took as long, but
-    // 63 to 85 us on the first call, which made that memory, and 20 us more to free the table.
+    // The order rides in a launch's arguments, and the results are written to host memory, so a call
+    // waits once and copies nothing: 20 us at 8 nodes (57 us with three device buffers and as many
+    // copies per call, 22 us with one copy from the table's own buffer, which serves where there is
+    // no host memory to be had).
     HostOrder in = {};
     for (int p = 0; p < n; ++p) in.v[p] = (uint8_t)order[p];
     std::lock_guard<std::mutex> lk(t->host_mu);
-    double *sums = t->d_result;
+    char *shared = take_result_buffer();
+    double *sums = shared ? reinterpret_cast<double *>(shared) : t->d_result;
     hipLaunchKernelGGL(k_order_in, dim3(1), dim3(64), 0, nullptr, in, t->d_order);
-    BNOS_HIP(hipGetLastError());
-    const bnos_status s = score_impl(t, t->d_order, 1, sums, sums + 1, reinterpret_cast<uint64_t *>(sums + 2), nullptr,
-                                     nullptr, nullptr);
-    if (s != BNOS_OK) return s;
+    hipError_t e = hipGetLastError();
+    bnos_status s = BNOS_OK;
+    if (e == hipSuccess)
+        s = score_impl(t, t->d_order, 1, sums, sums + 1, reinterpret_cast<uint64_t *>(sums + 2), nullptr, nullptr, nullptr);
     char host[kHostResult];
-    BNOS_HIP(hipMemcpy(host, sums, kHostResult, hipMemcpyDeviceToHost));
+    hipError_t done = hipSuccess;
+    if (shared) {
+        done = hipStreamSynchronize(nullptr);
+        if (done == hipSuccess) {                // (else kernels may still write to it)
+            std::memcpy(host, shared, kHostResult);
+            give_result_buffer(shared);
+        }
+    } else if (e == hipSuccess && s == BNOS_OK) {
+        done = hipMemcpy(host, sums, kHostResult, hipMemcpyDeviceToHost);
+    }
+    if (s != BNOS_OK) return s;
+    BNOS_HIP(e);
+    BNOS_HIP(done);
     std::memcpy(lse, host, sizeof(double));
     std::memcpy(maxs, host + sizeof(double), sizeof(double));
     if (best_parents) std::memcpy(best_parents, host + 2 * sizeof(double), sizeof(uint64_t) * n);

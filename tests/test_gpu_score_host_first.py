@@ -1,6 +1,7 @@
 """Scoring one order from host arrays on a table that has scored none: right, and without a set-up that costs
 several calls (a program may score one order per table)."""
 import statistics
+import threading
 import time
 
 import numpy as np
@@ -44,3 +45,35 @@ def test_first_call_on_a_table(n, K):
     a, b = statistics.median(first), statistics.median(second)
     print("first %.1f us, second %.1f us" % (a * 1e6, b * 1e6))
     assert a < 2.2 * b
+
+
+def test_tables_in_many_threads():
+    # 12 threads, each with its own tables one after the other: more calls at once than buffers are kept
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1210_5128_amd import bnos
+    nets = [datagen.random_network(9, 150, (2, 3), 3, seed=k) for k in range(12)]
+    orders = datagen.random_orders(9, 6, 3)
+    want, got = [], [None] * 12
+
+    def scores(net):
+        out = []
+        for _ in range(3):
+            t = bnos.build_score_table(net.data, net.arities, 3)
+            out += [t.score_order(o) for o in orders]
+            t.free()
+        return out
+
+    def work(k):
+        got[k] = scores(nets[k])
+
+    for net in nets:
+        want.append(scores(net))
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(12)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for k in range(12):
+        for a, b in zip(want[k], got[k]):
+            assert a[:2] == b[:2] and np.array_equal(a[2], b[2]), k
