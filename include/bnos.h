@@ -125,8 +125,8 @@ bnos_status bnos_table_info(bnos_table t, int32_t *n, int32_t *K, int64_t *entri
  * (more per row on average than a sixteenth of it, at least 6,144 and at most
  * 16,384, or no memory for them within BNOS_MAX_DEVICE_BYTES); the streaming pass
  * then serves it.  Chains with uniform swaps on a table with many kept entries are
- * streamed too when they are few (1 to 3, 4 to 15 or more have their own lines), so
- * there the number of chains can move a chain's log-sum-exps in the last bits, as a
+ * streamed too when they are few (1 to 3 and 4 to 15 have their own lines), so there
+ * the number of chains can move a chain's log-sum-exps in the last bits, as a
  * launch shape can (bnos_chains_autotune).
  */
 bnos_status bnos_table_kept(bnos_table t, int64_t *entries);

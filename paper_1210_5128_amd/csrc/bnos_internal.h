@@ -77,7 +77,8 @@ constexpr int64_t kept_mean(int64_t S)
 // chains_fold_kept.
 constexpr int64_t kept_chain_steps(int C, int64_t S)
 {
-    const int64_t least = C < 4 ? 600 : (C < 16 ? 800 : 1600), share = S / (C < 4 ? 256 : (C < 16 ? 150 : 100));
+    if (C >= 16) return INT64_MAX;
+    const int64_t least = C < 4 ? 600 : 1600, share = S / (C < 4 ? 256 : 100);
     return least > share ? least : share;
 }
 constexpr int kKeptCap = 1 << 19;         // entries of one row
@@ -211,10 +212,13 @@ struct TableT {
     // chains; streamed, it takes the longer the longer the rows, and the more chains.  Kept / streamed us
     // per iteration: 57 nodes, 1,665 steps, 1 chain 48 / 31, 4 chains 48 / 44, 16 48 / 79, 256 52 / 314;
     // 45 nodes and 14,235 entries per row, 753 steps, 26 / 21, 28 / 25, 28 / 37, 31 / 62; 60 nodes, 1,480 steps,
-    // 1 chain 30 / 61.  Of the 1,044 tables of kept_mean(), on this side of the lines 1 is over 5% slower
-    // kept for 1 to 3 chains, 6 (table, count) pairs for 4 to 15 and 1 for more; with one line of 1,600
-    // steps below 4 chains and none above it was 65, 39 and 7.  The learned proposal's streamed
-    // step takes 40 to 60 us alone: on 347 tables of 500 kept steps and more, one chain is slower kept on 8.
+    // 1 chain 30 / 61.  Of the 1,044 tables of kept_mean(), on this side of the lines 1 (table, count) pair
+    // is over 5% slower kept for 1 to 3 chains and 24 (of 3,132) are for 4 to 15; with one line of 1,600
+    // steps below 4 chains and none above it was 65 and 39.  16 chains and more always take them: 7 of
+    // 3,132 are slower, up to 1.6 times, and a call on many tables waits for those it streams (32 tables
+    // of 20 to 60 nodes, 64 chains: 61 us per iteration, 114 with the longest few streamed).  The learned
+    // proposal's streamed step takes 40 to 60 us alone: on 347 tables of 500 kept steps and more, one
+    // chain is slower kept on 8.
     bool chains_fold_kept(int C, bool learned) const
     {
         return d_kmask != nullptr && (learned || kept_steps <= kept_chain_steps(C, S));

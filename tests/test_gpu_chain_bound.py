@@ -10,7 +10,7 @@ from paper_1210_5128_amd import datagen
 pytestmark = pytest.mark.gpu
 
 
-# 1,665 steps of kept rows: streamed below 4 chains; 753, streamed below 4 too; 3,287: streamed below 16
+# 1,665 and 753 steps of kept rows: streamed below 4 chains; 3,287 steps of rows of 425,924 entries
 @pytest.mark.parametrize("n,K,N,seed,chains", [(57, 4, 1066, 68, 1), (57, 4, 1066, 68, 3), (57, 4, 1066, 68, 4),
                                                (57, 4, 1066, 68, 9), (45, 3, 290, 1, 3), (45, 3, 290, 1, 4),
                                                (58, 4, 587, 2, 15), (58, 4, 587, 2, 16)])
