@@ -648,7 +648,8 @@ struct ChainLds {
 // t0 == t_first, the starting orders in `prop`) are scored first, which rebuilds the caches.
 // What bounds it: latency, of the dependent scan steps (about 0.4 us per 256 entries from L2) and of
 // the draw, sums and barriers of a round (1.5 us).  Per iteration, 256 chains: 8 nodes 2.7 us, 40 nodes
-// (3,600 kept entries per row) 9.1 us, 60 nodes 8 to 18 us (1,500 to 5,100 per row), where the
+// (1,800 to 3,400 kept entries per row) 9 to 13 us, 60 nodes 13 to 21 us (2,300 to 8,400 per row; 7 to 8
+// burned in), where the
 // three launches per iteration took 14, 70 and 320 us.
 template <int KP, bool LEARNED, int W>
 __global__ __launch_bounds__(W * 64) void k_chain_run(const TabView *__restrict__ tviews,

@@ -123,8 +123,8 @@ __global__ __launch_bounds__(kKeptWaves * 64) void k_score_kept(ScoreArgs A)
 // The kept row's partial of every (order, node), to slot 0: W wavefronts per pair, the nodes with
 // the longest rows first.  What bounds it: the dependent steps of the longest row for few
 // orders, the vector instructions of the fold for many.  At n = 60, N = 5,000 one order takes
-// 10.4 us per call with its merge (the streaming pass: 88 us in its default shape) and 256
-// orders 22 to 38 us (755 us streamed).  STOP: down to the gap; else the whole row, for launches whose
+// 11 us per call with its merge (the streaming pass: 88 us in its default shape) and 256
+// orders 28 to 90 us by the longest rows, 170 us with one of 1,438 steps (710 us streamed).  STOP: down to the gap; else the whole row, for launches whose
 // streaming pass adds the other entries.
 template <int W, bool STOP>
 __global__ __launch_bounds__(W * 64) void k_kept_partials(ScoreArgs A)
