@@ -118,9 +118,10 @@ def cpu_baseline(net, prior, K: int, sample_nodes=(7, 41), seed: int = 3):
 
 
 def measured_traffic(batch: int, mode: str):
-    """HBM bytes per k_score launch ("full" scan or tile "skip") from the committed
-    rocprofv3 counter runs, or None when the scoring sources changed since they
-    were taken or no run matches the batch size."""
+    """HBM bytes of a scoring launch's timed kernels ("skip": the kept rows' pass; "full" scan: that
+    pass over whole kept rows and the streaming pass) from the committed rocprofv3 counter
+    runs, or None when the scoring sources changed since they were taken or no run matches the
+    batch size."""
     import hashlib
     try:
         recs = json.load(open(os.path.join(ROOT, "profiles", "traffic.json")))
