@@ -398,7 +398,9 @@ bnos_status bnos_run_chains(bnos_table t, const bnos_chain_cfg *cfg, bnos_chain_
  * per-iteration launch that lists each node's chains also holds one
  * wavefront per (chain, node) pair; a call whose pairs (summed over the
  * tables) exceed that launch's 2^32 work-items returns BNOS_E_RANGE before
- * any kernel runs.
+ * any kernel runs, and so does one of more than a launch holds: 2^22 chains on
+ * tables that are streamed, 2^23 on those whose chains run in one launch, or 2^24
+ * blocks of (node, chunk) over the streamed tables.
  */
 bnos_status bnos_run_chains_multi(const bnos_table *tables, int32_t T, const bnos_chain_cfg *cfg,
                                   bnos_chain_state *states, void *stream);

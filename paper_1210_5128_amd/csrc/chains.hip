@@ -1301,6 +1301,14 @@ static bnos_status run_chains_impl(const bnos_table *hs, int32_t T, const bnos_c
             return BNOS_E_RANGE;
         }
     }
+    // a launch of more work-items than 2^32 would run a part of its blocks and report nothing
+    if ((int64_t)run_chains * (run_chains <= 512 ? 1024 : 512) > (int64_t)UINT32_MAX ||
+        (int64_t)total_chains * kStepWaves * 64 > (int64_t)UINT32_MAX ||
+        (blk_base[Ts] + kXcds) * kScoreThreads > (int64_t)UINT32_MAX) {
+        set_error("too many chains or table chunks for one launch: lower the chains or the tables per call");
+        cleanup();
+        return BNOS_E_RANGE;
+    }
     bool any_bound = false, any_kept = false;    // of the streamed tables
     int kept_max = 0;                            // and their longest kept row, in steps
     for (int q = Tk; q < T; ++q) {

@@ -69,3 +69,26 @@ def test_most_orders_on_64_nodes(bnos):
         assert read == sum(t.count_tiles(orders[b:b + step])[0] for b in range(0, B, step))
     finally:
         t.free()
+
+
+def test_more_chains_than_a_launch_holds_is_an_error(bnos):
+    # 65 tables x 65,536 chains, a block of 1,024 threads each in the streamed sweep: 4.4e9 work-items, of
+    # which a launch runs what is left modulo 2^32; the call is refused before any kernel runs
+    n, C, T = 8, 65536, 65
+    tabs, states = [], []
+    try:
+        for k in range(T):
+            net = datagen.random_network(n, 40, (2,), 3, seed=k)
+            t = bnos.build_score_table(net.data, net.arities, 1)
+            tabs.append(t)
+            t.score_bound(False)
+            states.append(t.new_chain_state(C, 1))
+        with pytest.raises(bnos.BnosError) as e:
+            bnos.run_chains_multi(tabs, states, 1, 3)
+        assert e.value.status == bnos.E_RANGE
+        ref = tabs[0].new_chain_state(C, 1)               # and the next call is not disturbed
+        tabs[0].run_chains(ref, 1, 3)
+        assert torch.all(torch.isfinite(ref["scores"]))
+    finally:
+        for t in tabs:
+            t.free()
