@@ -35,7 +35,8 @@ __global__ __launch_bounds__(kMergeWaves * 64) void k_merge(ScoreArgs A)
 // (a node's row is streamed by many blocks).
 __global__ __launch_bounds__(kScoreThreads) void k_bound_pre(ScoreArgs A)
 {
-    const int64_t g = (int64_t)blockIdx.x * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;      // (see launch_stream)
+    const int64_t g = block * (kScoreThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int n = A.n;
     if (g >= (int64_t)A.B * n) return;            // uniform per wavefront
@@ -495,9 +496,10 @@ bnos_status launch_stream(TableT *t, const ScoreArgs &A, hipStream_t st, int bt,
     }
     if (bt > 1 && A.tmax && A.tand && A.cut_ws) {
         // every (order, node) cut once, before the blocks that stream the node's row
-        const int64_t pairs = (int64_t)A.B * A.n;
-        hipLaunchKernelGGL(k_bound_pre, dim3((unsigned)((pairs + kScoreThreads / 64 - 1) / (kScoreThreads / 64))),
-                           dim3(kScoreThreads), 0, st, A);
+        // (2^20 blocks in x: all of them there could be 2^32 work-items, which a launch does not hold)
+        const int64_t blocks = ((int64_t)A.B * A.n + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
+        const int64_t gx = blocks < (1 << 20) ? blocks : (1 << 20);
+        hipLaunchKernelGGL(k_bound_pre, dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx)), dim3(kScoreThreads), 0, st, A);
         A2.cuts = A.cut_ws;
     }
     if (bt == 8) launch_bt<8>(A2, nbx, st, e0, e1);

@@ -92,3 +92,36 @@ def test_more_chains_than_a_launch_holds_is_an_error(bnos):
     finally:
         for t in tabs:
             t.free()
+
+
+def test_most_orders_on_64_nodes_streamed(bnos, monkeypatch):
+    # the same 2^26 pairs where the score bound's cuts are computed ahead of the streaming pass
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("the partials of 2^20 orders take 104 GB")
+    n, B, step = 64, 1 << 20, 1 << 17
+    net = datagen.random_network(n, 129, (2,), 3, seed=84)
+    t = bnos.build_score_table(net.data, net.arities, 2, chunk_steps=2)
+    held = t.info()["device_bytes"]
+    t.free()
+    monkeypatch.setenv("BNOS_MAX_DEVICE_BYTES", str(held - 1))
+    t = bnos.build_score_table(net.data, net.arities, 2, chunk_steps=2)
+    monkeypatch.delenv("BNOS_MAX_DEVICE_BYTES")
+    try:
+        assert t.kept_entries() == 0
+        g = torch.Generator(device="cuda").manual_seed(1)
+        orders = torch.cat([torch.rand((step, n), device="cuda", generator=g).argsort(dim=1).to(torch.int32)
+                            for _ in range(B // step)])
+
+        def score(o):
+            lse = torch.empty(o.shape[0], dtype=torch.float64, device="cuda")
+            mx, best = torch.empty_like(lse), torch.empty(o.shape, dtype=torch.int64, device="cuda")
+            t.score_orders(o, lse, mx, best)
+            return lse, mx, best
+
+        parts = [score(orders[b:b + step]) for b in range(0, B, step)]
+        whole = score(orders)
+        for k, b in enumerate(range(0, B, step)):
+            for w, p in zip(whole, parts[k]):
+                assert torch.equal(w[b:b + step], p), b
+    finally:
+        t.free()
