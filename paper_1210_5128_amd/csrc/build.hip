@@ -987,7 +987,7 @@ __global__ __launch_bounds__(1024) void k_keep_subsets(const float *__restrict__
 }
 
 // b - kBoundGap, or -inf where FP32 cannot hold that gap below b or rounds it towards b: the entries
-// below b are all kept then (the scans' gap_below takes the next float down instead).
+// below b are all kept then (the scans' gap_below is lowered instead).
 __device__ __forceinline__ float keep_gap_below(float b)
 {
     const float g = b - kBoundGap;

@@ -498,19 +498,17 @@ __device__ __forceinline__ void bound_candidate(const TabView &V, int node, int 
     cm = V.cmask[c];
 }
 
-// The largest float at least kBoundGap below b.  Where b - kBoundGap has a larger
-// exponent than b, the difference can round towards b, and the next float down is
-// it: without that step a best score in such a place (-4,096 to -4,036, -1,024 to -964,
-// ...) had no gap at all and its row was read to the end.  One order of 57 nodes
-// with a kept row of 318,000 entries took 68 us so (streamed 26), and of
+// A float at least kBoundGap below b, by two units in its last place at most (for -inf: -inf).
+// The difference can round towards b where it has a larger exponent, so it is lowered by
+// one or two units.  Without that a best score in such a place (-4,096 to -4,036, -1,024 to
+// -964, ...) had no gap at all and its row was read to the end: one order of 57 nodes
+// with a kept row of 318,000 entries took 68 us so (streamed 26, now 10), and of
 // 1,050 (table, batch) pairs of 175 drawn tables of 36 to 60 nodes, 32 were over 5% slower than
 // streamed, now 14.
 __device__ __forceinline__ float gap_below(float b)
 {
     const float g = b - kBoundGap;
-    if (b - g >= kBoundGap) return g;
-    const float h = __builtin_bit_cast(float, __builtin_bit_cast(int, g) + (g < 0.f ? 1 : -1));
-    return (b - h >= kBoundGap) ? h : -INFINITY;
+    return fmaf(-fabsf(g), 0x1p-23f, g);
 }
 
 // The score below which a tile is left out, for predecessor complement np

@@ -11,12 +11,12 @@ pytestmark = pytest.mark.gpu
 STEP, GAP = 256, np.float32(60)
 
 
-def gap_below(b, one_lower=True):
-    """60 below b: the nearest float, or the next one where that is less than 60 away; the build's list of
-    kept entries leaves none out there."""
+def gap_below(b, scan=True):
+    """60 below b: lowered by a unit or two in the last place for a scan; as it rounds for the build's list of
+    kept entries, which leaves none out where that is less than 60 away."""
     g = np.float32(b - GAP)
-    if one_lower and np.float32(b - g) < GAP:
-        g = np.nextafter(g, np.float32(-np.inf))
+    if scan:
+        return np.float32(np.float64(g) - abs(np.float64(g)) * 2.0 ** -23)
     return g if np.float32(b - g) >= GAP else np.float32(-np.inf)
 
 
